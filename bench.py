@@ -51,7 +51,8 @@ def _alg_bytes(wl) -> dict:
 
 
 _SOURCES = {"collide_stream": ("lbm.hip", "lbm_device.h"),
-            "transport": ("transport_tiled.h", "transport_tiled.hip", "transport_device.h")}
+            "transport": ("transport_tiled.h", "transport_tiled_unit.hip", "transport_tiled.hip",
+                          "transport_face.h", "transport_device.h")}
 
 
 def _kernel_hash(kind: str = "collide_stream") -> str:

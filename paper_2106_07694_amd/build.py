@@ -18,20 +18,26 @@ LIB = os.path.join(HERE, "liblbw.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["lbm.hip", "transport.hip", "transport_tiled.hip", "transport_tiled_vs.hip",
-           "reduce.hip", "adjoint.hip", "api.cpp"]
+# (source, object name, preprocessor definitions); the tiled transport builds one unit per
+# element type, dimension and settling form, all in parallel
+TILED = [("transport_tiled_unit.hip", f"transport_tiled_{d}d_{t}{'_vs' if v else ''}",
+          [f"-DLBW_T={t}", f"-DLBW_D={d}", f"-DLBW_VSS={v}"])
+         for t in ("double", "float") for d in (3, 2) for v in (0, 1)]
+SOURCES = TILED + [(src, os.path.splitext(src)[0], []) for src in (
+    "adjoint.hip", "lbm.hip", "transport.hip", "transport_tiled.hip", "reduce.hip", "api.cpp")]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-Wall", "-Wno-unused-function", "-I", os.path.join(HERE, "..", "include")]
 
 
-def _compile(src: str) -> str:
-    out = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *COMMON, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", out]
+def _compile(unit: tuple) -> str:
+    src, name, defs = unit
+    out = os.path.join(OBJ, name + ".o")
+    cmd = [HIPCC, *COMMON, *defs, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", out]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError(f"hipcc failed on {src}:\n{r.stderr}")
+        raise RuntimeError(f"hipcc failed on {src} ({name}):\n{r.stderr}")
     return out
 
 

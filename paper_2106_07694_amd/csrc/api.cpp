@@ -43,6 +43,7 @@ struct lbw_handle {
     int *d_blk = nullptr, *d_tiles = nullptr;
     std::vector<int> blk_start, tile_start;
     std::vector<lbw::RunDev> views;
+    lbw::TileShape shape{0, 0, 0};
     int grid_lbm = 0, grid_tr = 0;
     // graph replay
     hipGraph_t graph = nullptr;
@@ -150,9 +151,10 @@ int upload_tables(lbw_handle *h) {
         for (int i = 0; i < h->run[b].ncls; ++i) h->views.push_back(class_view(h, h->run[b], b, i));
     }
     const int nviews = (int)h->views.size();
+    h->shape = lbw::resolve_tile_shape(h->dim, h->precision, h->launch, h->views.data(), nviews);
     h->tile_start.assign(nviews + 1, 0);
     for (int v = 0; v < nviews; ++v) {
-        const int64_t nt = lbw::transport_tiles(h->dim, h->views[v], h->launch);
+        const int64_t nt = lbw::transport_tiles(h->dim, h->views[v], h->shape);
         if ((int64_t)h->tile_start[v] + nt > 0x7fffffff)
             return fail(LBW_ERR_INVAL, "batched work list too large");
         h->tile_start[v + 1] = h->tile_start[v] + (int)nt;
@@ -281,8 +283,13 @@ lbw::RunDev make_run(const lbw_config &c, const lbw_buffers &b) {
 // short chunks and tiles that fit its lateral sizes badly could exceed that.
 int check_tile_launch(const lbw_handle *h, const lbw_launch &l) {
     if (h->nbatch > 1 || l.variant == 1) return LBW_OK;   // persistent grid / one thread per node
-    const lbw::TileShape s = lbw::resolve_tile_shape(h->dim, l);
-    const int64_t items = lbw::transport_tiles(h->dim, h->run[0], l) * s.tx * s.ty;
+    // fields left at 0 count as 32x8 columns by 64 planes (256 by 32 in 2D):
+    // a shape chosen for the run's size never needs more than that allows
+    lbw_launch f = l;
+    if (!f.tile_x) f.tile_x = h->dim == 3 ? 32 : 256;
+    if (!f.tile_y) f.tile_y = h->dim == 3 ? 64 : 32;
+    const lbw::TileShape s = lbw::resolve_tile_shape(h->dim, h->precision, f, &h->run[0], 1);
+    const int64_t items = lbw::transport_tiles(h->dim, h->run[0], s) * s.tx * s.ty;
     if (items >= ((int64_t)1 << 32))
         return fail(LBW_ERR_INVAL, "the transport launch would need %lld work-items (at most 2^32 - 1): "
                                    "choose a longer vertical chunk (tile_y)", (long long)items);
@@ -484,10 +491,10 @@ int enqueue_step(lbw_handle *h) {
         a.tile_start = h->d_tiles;
         a.host_runs = h->views.data();
         a.nbatch = (int)h->views.size();
-        a.chunk = lbw::resolve_tile_shape(h->dim, h->launch).chunk;
+        a.shape = h->shape;
         a.sflip = h->sflip ? 1 : 0;
         a.grid = h->grid_tr;
-        hipError_t e = lbw::launch_transport_batched(h->dim, h->precision, a, h->launch, h->stream);
+        hipError_t e = lbw::launch_transport_batched(h->dim, h->precision, a, h->stream);
         if (e != hipSuccess) return hip_fail(e, "batched transport launch");
     } else {
         for (int b = 0; b < h->nbatch; ++b) {

@@ -64,7 +64,8 @@ struct RunDev {
     double phi_c;        // volume fraction per unit C in the (1 - phi) of eq. 10
 };
 
-// Tile shape of the tiled transport kernels for a launch choice.
+// Tile shape of the tiled transport kernels: tx x ty columns marching `chunk`
+// vertical planes.
 struct TileShape {
     int tx, ty, chunk;
 };
@@ -77,7 +78,7 @@ struct BatchArgs {
     const int *tile_start;     // device prefix sum of tiles per entry (nbatch + 1)
     const RunDev *host_runs;   // host copy of the same table
     int nbatch;                // entries
-    int chunk;
+    TileShape shape;
     int sflip;                 // 1: S and its work buffer are swapped
     int grid;                  // persistent grid size
     int stage = 0;             // 0: the three RK stages and the S update; 1-3: that stage only
@@ -104,14 +105,19 @@ hipError_t launch_s_update(int dim, int precision, const RunDev &r, hipStream_t 
 // with a constant settling speed).
 hipError_t launch_one_stage(int dim, int precision, const RunDev &r, const lbw_launch &l,
                             int stage, hipStream_t st);
-TileShape resolve_tile_shape(int dim, const lbw_launch &l);
-int64_t transport_tiles(int dim, const RunDev &r, const lbw_launch &l);
-hipError_t launch_transport_batched(int dim, int precision, const BatchArgs &b, const lbw_launch &l,
-                                    hipStream_t st);
-// The tiled stages of runs whose settling speed depends on S (b: batched
-// entries, or NULL for the single run r).
-hipError_t launch_transport_tiled_vs(int dim, int precision, const RunDev &r, const lbw_launch &l,
-                                     hipStream_t st, const BatchArgs *b);
+// The launch's tile shape for n runs advanced together; fields the caller left
+// at 0 are chosen for those runs' sizes.
+TileShape resolve_tile_shape(int dim, int precision, const lbw_launch &l, const RunDev *runs, int n);
+// Tiles (blocks) of one run in that shape, over all vertical chunks.
+int64_t transport_tiles(int dim, const RunDev &r, const TileShape &s);
+hipError_t launch_transport_batched(int dim, int precision, const BatchArgs &b, hipStream_t st);
+// The tiled stages in one unit per dimension, element type and settling form
+// (VSS: a settling speed that depends on S), of the single run r or, when b is
+// not NULL, of the batched entries.  stage 0: all three; 1-3: that one only
+// (single runs).
+template <typename T, int D, bool VSS>
+hipError_t tiled_unit(const RunDev &r, const TileShape &sh, int stage, hipStream_t st,
+                      const BatchArgs *b);
 // nodes: total nodes of the batch (chooses the cache policy of the
 // population accesses)
 hipError_t launch_collide_stream_batched(int q, int precision, const RunDev *runs, const int *blk_start,

@@ -1,6 +1,6 @@
 // transport_tiled.h -- the tiled RK3 stage kernels of the particle
-// transport, as templates shared by the two units that build them
-// (constant settling speed, and a settling speed set by S).
+// transport, as templates shared by the units that build them (one per
+// dimension, element type and settling form: transport_tiled_unit.hip).
 //
 // RK3 stage kernels of the particle transport, tiled for CDNA: a block owns a TX x TY tile of vertical columns and marches up a
 // chunk of the vertical axis.  Per plane:
@@ -21,125 +21,10 @@
 // the hardware reciprocal.
 #pragma once
 
-#include "transport_device.h"
+#include "transport_face.h"
 
 namespace lbw {
 namespace {
-
-template <typename T> __device__ __forceinline__ T fast_rcp(T x) { return (T)1 / x; }
-template <> __device__ __forceinline__ float fast_rcp<float>(float x) { return __builtin_amdgcn_rcpf(x); }
-
-// WENO5-JS face value (the formula of weno5_face) rearranged for issue
-// count, with one reciprocal.  The normalised weights are ratios, so every
-// indicator may be scaled by one constant and every ideal weight by another:
-// with e_k = (12/13)(eps + beta_k) = t_k^2 + (3/13) s_k^2 + (12/13) eps
-// (t_k the second difference, s_k the one-sided first difference of
-// sub-stencil k, both built from the four first differences) and the
-// weights multiplied through by 10 e_0^2 e_1^2 e_2^2, the face value is
-//   (P q_0 + Q q_1' + R q_2') / (P + 6 Q + 3 R),
-//   P = e_1^2 e_2^2, Q = e_0^2 e_2^2, R = e_0^2 e_1^2,
-// where q_0 is the first candidate and q_1' = 6 q_1, q_2' = 3 q_2.
-// eps12 is (12/13) eps.  With e_k >= eps12 and concentrations of order one
-// every product stays far inside the single-precision range.
-template <typename T>
-__device__ __forceinline__ T weno5_rcp(T h0, T h1, T h2, T h3, T h4, T a0, T a1, T a2, T a3, T a4,
-                                       T eps12) {
-    const T g0 = a1 - a0, g1 = a2 - a1, g2 = a3 - a2, g3 = a4 - a3;
-    const T t0 = g1 - g0, t1 = g2 - g1, t2 = g3 - g2;
-    const T s0 = t0 + (T)2 * g1;          // a0 - 4 a1 + 3 a2
-    const T s1 = g1 + g2;                 // a3 - a1
-    const T s2 = t2 - (T)2 * g2;          // 3 a2 - 4 a3 + a4
-    constexpr T k = (T)(3.0 / 13.0);
-    const T e0 = t0 * t0 + (k * s0 * s0 + eps12);
-    const T e1 = t1 * t1 + (k * s1 * s1 + eps12);
-    const T e2 = t2 * t2 + (k * s2 * s2 + eps12);
-    const T S0 = e0 * e0, S1 = e1 * e1, S2 = e2 * e2;
-    const T P = S1 * S2, Q = S0 * S2, R = S0 * S1;
-    const T q0 = (T)(1.0 / 3.0) * h0 - (T)(7.0 / 6.0) * h1 + (T)(11.0 / 6.0) * h2;
-    const T q1 = (T)5 * h2 - h1 + (T)2 * h3;
-    const T q2 = h2 + (T)2.5 * h3 - (T)0.5 * h4;
-    return (P * q0 + Q * q1 + R * q2) * fast_rcp<T>(P + (T)6 * Q + (T)3 * R);
-}
-
-template <typename T>
-__device__ __forceinline__ T weno3_rcp(T h0, T h1, T h2, T a0, T a1, T a2, T eps) {
-    const T qu = (T)0.5 * ((T)3 * h1 - h0);
-    const T qc = (T)0.5 * (h1 + h2);
-    const T eu = eps + (a1 - a0) * (a1 - a0);
-    const T ec = eps + (a2 - a1) * (a2 - a1);
-    const T au = (T)(1.0 / 3.0) * fast_rcp<T>(eu * eu);
-    const T ac = (T)(2.0 / 3.0) * fast_rcp<T>(ec * ec);
-    return (au * qu + ac * qc) * fast_rcp<T>(au + ac);
-}
-
-// Face flux from six nodes j-2..j+3 (a and w given as separate scalars):
-// the upwind side is chosen by selects, not branches, so lanes of a wave
-// with different face-velocity signs do not diverge.
-template <typename T, int SCHEME>
-__device__ __forceinline__ T face6(T a0, T a1, T a2, T a3, T a4, T a5, T w0, T w1, T w2, T w3,
-                                   T w4, T w5, T kappa, T eps) {
-    const bool pos = (w2 + w3) >= (T)0;
-    T hh;
-    if constexpr (SCHEME == LBW_WENO5) {
-        const T A0 = pos ? a0 : a5, A1 = pos ? a1 : a4, A2 = pos ? a2 : a3, A3 = pos ? a3 : a2,
-                A4 = pos ? a4 : a1;
-        const T W0 = pos ? w0 : w5, W1 = pos ? w1 : w4, W2 = pos ? w2 : w3, W3 = pos ? w3 : w2,
-                W4 = pos ? w4 : w1;
-        hh = weno5_rcp<T>(W0 * A0, W1 * A1, W2 * A2, W3 * A3, W4 * A4, A0, A1, A2, A3, A4,
-                          (T)(12.0 / 13.0) * eps);
-    } else if constexpr (SCHEME == LBW_WENO3) {
-        const T A0 = pos ? a1 : a4, A1 = pos ? a2 : a3, A2 = pos ? a3 : a2;
-        const T W0 = pos ? w1 : w4, W1 = pos ? w2 : w3, W2 = pos ? w3 : w2;
-        hh = weno3_rcp<T>(W0 * A0, W1 * A1, W2 * A2, A0, A1, A2, eps);
-    } else {
-        hh = pos ? w2 * a2 : w3 * a3;
-    }
-    return hh - kappa * (a3 - a2);
-}
-
-// WENO5 with the work of each node done once (the arithmetic of weno5_rcp
-// regrouped by node).  Node m is the centre of three sub-stencils that faces
-// read: with t = a_{m+1} - 2 a_m + a_{m-1} and c = a_{m+1} - a_{m-1}, their
-// scaled indicators are
-//   e_c = t^2 + (3/13) c^2 + eps12        (the face's centre sub-stencil),
-//   e_l = e_c + (12/13) t (t + c)          (one-sided difference 2t + c, at m+1),
-//   e_r = e_c + (12/13) t (t - c)          (one-sided difference 2t - c, at m-1),
-// the last two being t^2 + (3/13)(2t +- c)^2 + eps12 expanded (each stays
-// within a few units in the last place of its value: e_l, e_r >= t^2 + eps12
-// and the cancelling part is at most 2 t^2).  A face takes three of them and
-// five node fluxes h = w a, chosen by its upwind side.  Contraction is pinned
-// per expression, so every kernel that inlines these gives the same bits.
-template <typename T>
-__device__ __forceinline__ void weno5_node(T dl, T dr, T eps12, T &el, T &ec, T &er) {
-#pragma clang fp contract(on)
-    const T t = dr - dl, c = dr + dl;            // dl = a_m - a_{m-1}, dr = a_{m+1} - a_m
-    ec = t * t + ((T)(3.0 / 13.0) * c * c + eps12);
-    const T kt = (T)(12.0 / 13.0) * t;
-    el = kt * (t + c) + ec;
-    er = kt * (t - c) + ec;
-}
-
-// Total flux through face j+1/2 from node data: fluxes h at j-2 .. j+3, e_l
-// at j-1 and j, e_c at j and j+1, e_r at j+1 and j+2, the upwind side (pos:
-// the face velocity w_j + w_{j+1} >= 0) and d = a_{j+1} - a_j for diffusion.
-// Upwind from j the sub-stencils are centred at j-1 (as the upwind-most), j,
-// j+1 (as the downwind-most); upwind from j+1 at j+2, j+1, j, mirrored.
-template <typename T>
-__device__ __forceinline__ T weno5_flux_nodes(bool pos, T h0, T h1, T h2, T h3, T h4, T h5,
-                                              T el_jm1, T el_j, T ec_j, T ec_jp1, T er_jp1,
-                                              T er_jp2, T d, T kappa) {
-#pragma clang fp contract(on)
-    const T H0 = pos ? h0 : h5, H1 = pos ? h1 : h4, H2 = pos ? h2 : h3, H3 = pos ? h3 : h2,
-            H4 = pos ? h4 : h1;
-    const T e0 = pos ? el_jm1 : er_jp2, e1 = pos ? ec_j : ec_jp1, e2 = pos ? er_jp1 : el_j;
-    const T S0 = e0 * e0, S1 = e1 * e1, S2 = e2 * e2;
-    const T P = S1 * S2, Q = S0 * S2, R = S0 * S1;
-    const T q0 = (T)(1.0 / 3.0) * H0 - (T)(7.0 / 6.0) * H1 + (T)(11.0 / 6.0) * H2;
-    const T q1 = (T)5 * H2 - H1 + (T)2 * H3;
-    const T q2 = H2 + (T)2.5 * H3 - (T)0.5 * H4;
-    const T hh = (P * q0 + Q * q1 + R * q2) * fast_rcp<T>(P + (T)6 * Q + (T)3 * R);
-    return hh - kappa * d;
-}
 
 struct TileGeom {
     int nx, ny, nv;     // lateral sizes (ny = 1 in 2D) and vertical extent
@@ -348,11 +233,7 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
     }
     const T *__restrict__ sin = (const T *)(FS && s_entry ? r.s : r.c);
     const T kaps = (T)r.kappa_s;
-    // S face between nodes j (a2, w2) and j + 1 (a3, w3)
-    auto sface = [&](T a2, T a3, T w2, T w3) -> T {
-        const T hh = ((T)0.5 * (w2 + w3) >= (T)0) ? w2 * a2 : w3 * a3;
-        return hh - kaps * (a3 - a2);
-    };
+    auto sface = [&](T a2, T a3, T w2, T w3) -> T { return s_face<T>(a2, a3, w2, w3, kaps); };
 
     constexpr int NEX = (D == 3) ? TX + TY : 1;   // faces on the tile's far edges
 
@@ -730,25 +611,15 @@ void launch_stage1(const RunDev &r, const TileGeom &g, unsigned nb, hipStream_t 
     else launch_stage<T, D, SCHEME, 1, TX, TY, VSS, false>(r, g, nb, st);
 }
 
+// The three stages (stage 0) or one of them of a single run.
 template <typename T, int D, int SCHEME, int TX, int TY, bool VSS>
-hipError_t stages(const RunDev &r, int chunk, hipStream_t st) {
+hipError_t stages(const RunDev &r, int chunk, int stage, hipStream_t st) {
     const TileGeom g = make_geom<D>(r, chunk, TX, TY);
     const int64_t nb = (int64_t)g.gx * g.gy * g.gz;
     if (nb > 0x7fffffff) return hipErrorInvalidValue;
-    launch_stage1<T, D, SCHEME, TX, TY, VSS>(r, g, (unsigned)nb, st);
-    launch_stage<T, D, SCHEME, 2, TX, TY, VSS>(r, g, (unsigned)nb, st);
-    launch_stage<T, D, SCHEME, 3, TX, TY, VSS>(r, g, (unsigned)nb, st);
-    return hipGetLastError();
-}
-
-template <typename T, int D, int SCHEME, int TX, int TY>
-hipError_t one_stage_t(const RunDev &r, int chunk, int stage, hipStream_t st) {
-    const TileGeom g = make_geom<D>(r, chunk, TX, TY);
-    const int64_t nb = (int64_t)g.gx * g.gy * g.gz;
-    if (nb > 0x7fffffff) return hipErrorInvalidValue;
-    if (stage == 1) launch_stage1<T, D, SCHEME, TX, TY, false>(r, g, (unsigned)nb, st);
-    else if (stage == 2) launch_stage<T, D, SCHEME, 2, TX, TY, false>(r, g, (unsigned)nb, st);
-    else launch_stage<T, D, SCHEME, 3, TX, TY, false>(r, g, (unsigned)nb, st);
+    if (stage == 0 || stage == 1) launch_stage1<T, D, SCHEME, TX, TY, VSS>(r, g, (unsigned)nb, st);
+    if (stage == 0 || stage == 2) launch_stage<T, D, SCHEME, 2, TX, TY, VSS>(r, g, (unsigned)nb, st);
+    if (stage == 0 || stage == 3) launch_stage<T, D, SCHEME, 3, TX, TY, VSS>(r, g, (unsigned)nb, st);
     return hipGetLastError();
 }
 
@@ -772,24 +643,6 @@ hipError_t with_tile(const TileShape &sh, F &&fn) {
     }
 }
 
-template <typename T, int D, int SCHEME>
-hipError_t one_stage_shape(const RunDev &r, const lbw_launch &l, int stage, hipStream_t st) {
-    const TileShape sh = resolve_tile_shape(D, l);
-    return with_tile<D>(sh, [&](auto tx, auto ty) {
-        return one_stage_t<T, D, SCHEME, decltype(tx)::value, decltype(ty)::value>(r, sh.chunk, stage, st);
-    });
-}
-
-template <typename T, int D>
-hipError_t one_stage_d(const RunDev &r, const lbw_launch &l, int stage, hipStream_t st) {
-    switch (r.scheme) {
-        case LBW_WENO5: return one_stage_shape<T, D, LBW_WENO5>(r, l, stage, st);
-        case LBW_WENO3: return one_stage_shape<T, D, LBW_WENO3>(r, l, stage, st);
-        case LBW_UPWIND1: return one_stage_shape<T, D, LBW_UPWIND1>(r, l, stage, st);
-    }
-    return hipErrorInvalidValue;
-}
-
 template <typename T, int D, int SCHEME, int TX, int TY, bool VSS>
 hipError_t stages_batched(const BatchArgs &a, hipStream_t st) {
     bool any_s = false;
@@ -797,16 +650,16 @@ hipError_t stages_batched(const BatchArgs &a, hipStream_t st) {
     auto stage = [&](int k) {
         if (k == 1 && any_s)
             k_stage_batched<T, D, SCHEME, 1, TX, TY, VSS, true><<<a.grid, TX * TY, 0, st>>>(
-                a.runs, a.tile_start, a.nbatch, a.chunk, a.sflip, a.form);
+                a.runs, a.tile_start, a.nbatch, a.shape.chunk, a.sflip, a.form);
         else if (k == 1)
             k_stage_batched<T, D, SCHEME, 1, TX, TY, VSS><<<a.grid, TX * TY, 0, st>>>(
-                a.runs, a.tile_start, a.nbatch, a.chunk, a.sflip, a.form);
+                a.runs, a.tile_start, a.nbatch, a.shape.chunk, a.sflip, a.form);
         else if (k == 2)
             k_stage_batched<T, D, SCHEME, 2, TX, TY, VSS><<<a.grid, TX * TY, 0, st>>>(
-                a.runs, a.tile_start, a.nbatch, a.chunk, a.sflip, a.form);
+                a.runs, a.tile_start, a.nbatch, a.shape.chunk, a.sflip, a.form);
         else
             k_stage_batched<T, D, SCHEME, 3, TX, TY, VSS><<<a.grid, TX * TY, 0, st>>>(
-                a.runs, a.tile_start, a.nbatch, a.chunk, a.sflip, a.form);
+                a.runs, a.tile_start, a.nbatch, a.shape.chunk, a.sflip, a.form);
         return hipGetLastError();
     };
     if (a.stage != 0) return stage(a.stage);
@@ -817,33 +670,26 @@ hipError_t stages_batched(const BatchArgs &a, hipStream_t st) {
 }
 
 template <typename T, int D, int SCHEME, bool VSS>
-hipError_t stages_shape(const RunDev &r, const lbw_launch &l, hipStream_t st, const BatchArgs *batch) {
-    const TileShape sh = resolve_tile_shape(D, l);
+hipError_t stages_shape(const RunDev &r, const TileShape &sh, int stage, hipStream_t st,
+                        const BatchArgs *batch) {
     return with_tile<D>(sh, [&](auto tx, auto ty) {
         constexpr int TX = decltype(tx)::value, TY = decltype(ty)::value;
         return batch ? stages_batched<T, D, SCHEME, TX, TY, VSS>(*batch, st)
-                     : stages<T, D, SCHEME, TX, TY, VSS>(r, sh.chunk, st);
+                     : stages<T, D, SCHEME, TX, TY, VSS>(r, sh.chunk, stage, st);
     });
 }
 
+}  // namespace
+
 template <typename T, int D, bool VSS>
-hipError_t tiled_d(const RunDev &r, const lbw_launch &l, hipStream_t st, const BatchArgs *b) {
+hipError_t tiled_unit(const RunDev &r, const TileShape &sh, int stage, hipStream_t st,
+                      const BatchArgs *b) {
     switch (r.scheme) {
-        case LBW_WENO5: return stages_shape<T, D, LBW_WENO5, VSS>(r, l, st, b);
-        case LBW_WENO3: return stages_shape<T, D, LBW_WENO3, VSS>(r, l, st, b);
-        case LBW_UPWIND1: return stages_shape<T, D, LBW_UPWIND1, VSS>(r, l, st, b);
+        case LBW_WENO5: return stages_shape<T, D, LBW_WENO5, VSS>(r, sh, stage, st, b);
+        case LBW_WENO3: return stages_shape<T, D, LBW_WENO3, VSS>(r, sh, stage, st, b);
+        case LBW_UPWIND1: return stages_shape<T, D, LBW_UPWIND1, VSS>(r, sh, stage, st, b);
     }
     return hipErrorInvalidValue;
 }
 
-// Both precisions and dimensions for one settling form.
-template <bool VSS>
-hipError_t tiled_any(int dim, int precision, const RunDev &r, const lbw_launch &l, hipStream_t st,
-                     const BatchArgs *b) {
-    if (precision == LBW_FP32_SHIFTED)
-        return dim == 2 ? tiled_d<float, 2, VSS>(r, l, st, b) : tiled_d<float, 3, VSS>(r, l, st, b);
-    return dim == 2 ? tiled_d<double, 2, VSS>(r, l, st, b) : tiled_d<double, 3, VSS>(r, l, st, b);
-}
-
-}  // namespace
 }  // namespace lbw

@@ -1,61 +1,156 @@
-// transport_tiled.hip -- launchers of the tiled RK3 stage kernels
-// (transport_tiled.h) and the kernels with a constant settling speed.
-#include "transport_tiled.h"
+// transport_tiled.hip -- launch shapes and launchers of the tiled RK3 stage
+// kernels (transport_tiled.h, built in transport_tiled_unit.hip).
+#include <algorithm>
+
+#include "lbw_internal.h"
 
 namespace lbw {
 
-TileShape resolve_tile_shape(int dim, const lbw_launch &l) {
-    TileShape s;
+namespace {
+
+int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// Columns of a run covered by whole tx x ty tiles.
+int64_t padded_columns(int dim, const RunDev &r, int tx, int ty) {
+    const int64_t ny = dim == 3 ? r.ny : 1;
+    return ceil_div(r.nx, tx) * tx * ceil_div(ny, ty) * ty;
+}
+
+int64_t padded_columns(int dim, const RunDev *runs, int n, int tx, int ty) {
+    int64_t c = 0;
+    for (int i = 0; i < n; ++i) c += padded_columns(dim, runs[i], tx, ty);
+    return c;
+}
+
+int planes(int dim, const RunDev &r) { return dim == 3 ? r.nz : r.ny; }
+
+// Tile for runs whose caller chose none.  2D: the widest row (512 columns, 256
+// in double precision, whose 512-thread blocks measured 10-15% slower on small
+// grids) that pads the runs' columns no more than a narrower one.  3D: 64x8
+// (one block of eight waves stages fewer halo columns per cell than 32x8: 59.7
+// against 65.2 us per step's transport on 128x96x160), unless its padding
+// exceeds that of 32x8 by a tenth (200 columns: 42.1 against 40.2 us).
+TileShape default_tile(int dim, int precision, const RunDev *runs, int n) {
     if (dim == 3) {
-        s.tx = (l.tile_x == 64 || l.tile_x == 128) ? l.tile_x : 32;
-        s.ty = 256 / s.tx;
-        if ((s.tx == 32 && l.tile_rows == 16) || (s.tx == 64 && l.tile_rows == 8)) s.ty = l.tile_rows;
-    } else {
-        s.tx = (l.tile_x == 64 || l.tile_x == 128 || l.tile_x == 512) ? l.tile_x : 256;
-        s.ty = 1;
+        const int64_t wide = padded_columns(3, runs, n, 64, 8), narrow = padded_columns(3, runs, n, 32, 8);
+        return wide * 10 <= narrow * 11 ? TileShape{64, 8, 0} : TileShape{32, 8, 0};
     }
-    s.chunk = l.tile_y > 0 ? l.tile_y : (dim == 3 ? 64 : 32);
+    TileShape s{64, 1, 0};
+    int64_t least = padded_columns(2, runs, n, 64, 1);
+    for (int tx : {128, 256, 512}) {
+        if (tx == 512 && precision != LBW_FP32_SHIFTED) break;
+        const int64_t c = padded_columns(2, runs, n, tx, 1);
+        if (c <= least) {
+            least = c;
+            s.tx = tx;
+        }
+    }
     return s;
 }
 
-int64_t transport_tiles(int dim, const RunDev &r, const lbw_launch &l) {
-    const TileShape s = resolve_tile_shape(dim, l);
-    const TileGeom g = dim == 3 ? make_geom<3>(r, s.chunk, s.tx, s.ty) : make_geom<2>(r, s.chunk, s.tx, s.ty);
-    return (int64_t)g.gx * g.gy * g.gz;
+// Vertical chunk for runs whose caller chose none: the shortest with which the
+// blocks still start together.  A plane of a march takes 0.7-1.4 us however
+// few blocks there are, so a chip that is not full wants more blocks, down to
+// one plane each; once it is full, shorter chunks only repeat the prologue
+// (seven planes of the vertical stencil).  us per step of transport, measured:
+// 2D 64x128 in double precision 102 at 32 planes, 15 at one; 512x1024 99 at
+// 32, 25 at two; 1024x2048 102 at 32, 46 at eight, 48 at four; 3D 64x48x96 250
+// at 64, 29 at three; 128x128x192 251 at 64, 78 at eight; 256x256x400 620 at
+// 64, 528 at 24, 572 at eight.  Full means 16 waves a CU in 2D and the blocks
+// that fit beside each other in 3D (registers: three of 64x8 in single
+// precision, two in double).
+int default_chunk(int dim, int precision, const TileShape &s, const RunDev *runs, int n) {
+    int64_t blocks = 0;                 // at one plane per block
+    for (int i = 0; i < n; ++i)
+        blocks += padded_columns(dim, runs[i], s.tx, s.ty) / (s.tx * s.ty) * planes(dim, runs[i]);
+    constexpr int64_t cus = 256;
+    int64_t full, lo, hi;
+    if (dim == 2) {
+        full = cus * 16 * 64 / s.tx;
+        lo = 1;
+        hi = 32;
+    } else {
+        const bool eight_waves = s.tx * s.ty == 512;
+        if (precision == LBW_FP32_SHIFTED) full = cus * (eight_waves ? 3 : 5);
+        else full = cus * (eight_waves ? 2 : 4);
+        lo = eight_waves ? 3 : 2;
+        hi = eight_waves ? 24 : 16;
+    }
+    return (int)std::min(hi, std::max(lo, ceil_div(blocks, full)));
 }
+
+}  // namespace
+
+// A field the caller set is used as given.  The shape never needs 2^32
+// work-items for a run that could launch with 32x8 columns and 64 planes (256
+// and 32 in 2D) in place of the fields left at 0: those are what creation and
+// lbw_set_launch check.
+TileShape resolve_tile_shape(int dim, int precision, const lbw_launch &l, const RunDev *runs, int n) {
+    TileShape s;
+    if (l.tile_x || l.tile_rows) {
+        s.tx = l.tile_x ? l.tile_x : (dim == 3 ? 32 : 256);
+        s.ty = dim == 2 ? 1 : (l.tile_rows ? l.tile_rows : 256 / s.tx);
+    } else {
+        s = default_tile(dim, precision, runs, n);
+    }
+    s.chunk = l.tile_y > 0 ? l.tile_y : default_chunk(dim, precision, s, runs, n);
+    if (n == 1) {
+        auto too_many = [&] { return transport_tiles(dim, runs[0], s) * s.tx * s.ty >= ((int64_t)1 << 32); };
+        if (!l.tile_x && !l.tile_rows && l.tile_y > 0 && dim == 3 && too_many()) s.tx = 32;
+        while (l.tile_y == 0 && s.chunk < planes(dim, runs[0]) && too_many()) s.chunk *= 2;
+    }
+    return s;
+}
+
+int64_t transport_tiles(int dim, const RunDev &r, const TileShape &s) {
+    const int nv = planes(dim, r), chunk = std::min(s.chunk, nv);
+    return padded_columns(dim, r, s.tx, s.ty) / (s.tx * s.ty) * ceil_div(nv, chunk);
+}
+
+namespace {
+
+hipError_t tiled_any(int dim, int precision, bool vss, const RunDev &r, const TileShape &sh, int stage,
+                     hipStream_t st, const BatchArgs *b) {
+    if (precision == LBW_FP32_SHIFTED) {
+        if (dim == 2) return vss ? tiled_unit<float, 2, true>(r, sh, stage, st, b) : tiled_unit<float, 2, false>(r, sh, stage, st, b);
+        return vss ? tiled_unit<float, 3, true>(r, sh, stage, st, b) : tiled_unit<float, 3, false>(r, sh, stage, st, b);
+    }
+    if (dim == 2) return vss ? tiled_unit<double, 2, true>(r, sh, stage, st, b) : tiled_unit<double, 2, false>(r, sh, stage, st, b);
+    return vss ? tiled_unit<double, 3, true>(r, sh, stage, st, b) : tiled_unit<double, 3, false>(r, sh, stage, st, b);
+}
+
+}  // namespace
 
 hipError_t launch_transport_tiled(int dim, int precision, const RunDev &r, const lbw_launch &l,
                                   hipStream_t st) {
-    if (r.vs_s != 0.0) return launch_transport_tiled_vs(dim, precision, r, l, st, nullptr);
-    return tiled_any<false>(dim, precision, r, l, st, nullptr);
+    const TileShape sh = resolve_tile_shape(dim, precision, l, &r, 1);
+    return tiled_any(dim, precision, r.vs_s != 0.0, r, sh, 0, st, nullptr);
 }
 
 hipError_t launch_one_stage(int dim, int precision, const RunDev &r, const lbw_launch &l,
                             int stage, hipStream_t st) {
-    if (r.vs_s != 0.0) return hipErrorInvalidValue;   // built for a constant settling speed
-    if (precision == LBW_FP32_SHIFTED)
-        return dim == 2 ? one_stage_d<float, 2>(r, l, stage, st) : one_stage_d<float, 3>(r, l, stage, st);
-    return dim == 2 ? one_stage_d<double, 2>(r, l, stage, st) : one_stage_d<double, 3>(r, l, stage, st);
+    if (r.vs_s != 0.0) return hipErrorInvalidValue;   // constant settling speed only
+    const TileShape sh = resolve_tile_shape(dim, precision, l, &r, 1);
+    // one block per tile and chunk, fewer than 2^32 work-items a launch
+    if (transport_tiles(dim, r, sh) * sh.tx * sh.ty >= ((int64_t)1 << 32)) return hipErrorInvalidConfiguration;
+    return tiled_any(dim, precision, false, r, sh, stage, st, nullptr);
 }
 
-hipError_t launch_transport_batched(int dim, int precision, const BatchArgs &b, const lbw_launch &l,
-                                    hipStream_t st) {
+hipError_t launch_transport_batched(int dim, int precision, const BatchArgs &b, hipStream_t st) {
     const RunDev &r = b.host_runs[0];
     bool any_var = false, any_const = false;
     for (int i = 0; i < b.nbatch; ++i) (b.host_runs[i].vs_s != 0.0 ? any_var : any_const) = true;
-    if (!any_var) return tiled_any<false>(dim, precision, r, l, st, &b);
-    if (!any_const) return launch_transport_tiled_vs(dim, precision, r, l, st, &b);
+    if (!any_var || !any_const) return tiled_any(dim, precision, any_var, r, b.shape, 0, st, &b);
     // both settling forms: each stage runs once per form, each kernel over
     // its own entries, so every run takes the kernels it takes alone
     BatchArgs x = b;
     for (int k = 1; k <= 3; ++k) {
-        hipError_t e = hipSuccess;
         x.stage = k;
-        x.form = 0;
-        if (e == hipSuccess) e = tiled_any<false>(dim, precision, r, l, st, &x);
-        x.form = 1;
-        if (e == hipSuccess) e = launch_transport_tiled_vs(dim, precision, r, l, st, &x);
-        if (e != hipSuccess) return e;
+        for (int form = 0; form < 2; ++form) {
+            x.form = form;
+            const hipError_t e = tiled_any(dim, precision, form == 1, r, b.shape, 0, st, &x);
+            if (e != hipSuccess) return e;
+        }
     }
     return hipSuccess;
 }
