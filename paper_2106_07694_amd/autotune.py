@@ -50,7 +50,10 @@ def tune(cfgs, setup, steps: int = 20, graph: bool = False, log=print) -> dict:
         log(f"  lbm_block={blk}: {ms * 1e3:.1f} us/step")
         if ms < best_lbm_ms:
             best_lbm, best_lbm_ms = blk, ms
-    best_tile, best_tr_ms = None, float("inf")
+    # first with no shape set (the library's own choice for the grid): once
+    # set, a tile cannot be unset
+    best_tile, best_tr_ms = (0, 0, 0), _time_phases(sol, steps)["transport_ms"] / steps
+    log(f"  tile chosen by the library: {best_tr_ms * 1e3:.1f} us/step")
     for tx, rows in TILES[dim]:
         for ch in CHUNKS[dim]:
             sol.set_launch(lbm_block=best_lbm, tile_x=tx, tile_y=ch, tile_rows=rows)
@@ -59,8 +62,9 @@ def tune(cfgs, setup, steps: int = 20, graph: bool = False, log=print) -> dict:
             if ms < best_tr_ms:
                 best_tile, best_tr_ms = (tx, rows, ch), ms
     sol.close()
-    out = {"lbm_block": best_lbm, "tile_x": best_tile[0], "tile_rows": best_tile[1],
-           "tile_y": best_tile[2]}
+    out = {"lbm_block": best_lbm}
+    if best_tile[0]:
+        out.update(tile_x=best_tile[0], tile_rows=best_tile[1], tile_y=best_tile[2])
     if graph:
         out["graph"] = 1
     out["_ms"] = {"collide_stream": best_lbm_ms, "transport": best_tr_ms}

@@ -24,7 +24,7 @@ TILED = [("transport_tiled_unit.hip", f"transport_tiled_{d}d_{t}{'_vs' if v else
           [f"-DLBW_T={t}", f"-DLBW_D={d}", f"-DLBW_VSS={v}"])
          for t in ("double", "float") for d in (3, 2) for v in (0, 1)]
 SOURCES = TILED + [(src, os.path.splitext(src)[0], []) for src in (
-    "adjoint.hip", "lbm.hip", "transport.hip", "transport_tiled.hip", "reduce.hip", "api.cpp")]
+    "adjoint.hip", "lbm.hip", "transport.hip", "transport_tiled.hip", "transport_fused.hip", "reduce.hip", "api.cpp")]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -48,7 +48,7 @@ struct lbw_handle {
     // graph replay
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
-    bool graph_odd = false, graph_sflip = false;
+    bool graph_odd = false, graph_sflip = false, graph_fused = false;
 };
 
 namespace {
@@ -108,6 +108,16 @@ lbw::RunDev current(const lbw_handle *h, int b) {
     lbw::RunDev r = h->run[b];
     if (h->sflip) std::swap(r.s, r.s2);
     return r;
+}
+
+// Where a step with the whole transport in one launch reads C, writes it, and
+// writes the RK stages (NULL: not kept).  Every array holds the run's classes.
+struct FusedStep {
+    void *c_in, *c_out, *a1, *a2;
+};
+
+bool fused_applies(const lbw_handle *h) {
+    return h->nbatch == 1 && lbw::rk3_fused2d_applies(h->dim, h->run[0], h->launch);
 }
 
 // Size class i of a run as the transport kernels see it: its C field and
@@ -465,8 +475,10 @@ int span_close(lbw_handle *h, int idx, hipStream_t st) {
 
 namespace {
 // Enqueue one coupled step on the handle's stream and advance the host-side
-// state (streaming parity, S buffer roles, step count).
-int enqueue_step(lbw_handle *h) {
+// state (streaming parity, S buffer roles, step count).  With `fused` the
+// transport is one launch over those buffers; otherwise the three stages run
+// in the run's own, C in place.
+int enqueue_step(lbw_handle *h, const FusedStep *fused = nullptr) {
     int rc;
     int sp = span_open(h, LBW_PHASE_COLLIDE_STREAM, h->stream);
     if (h->fluid_mode == LBW_FLUID_LBM) {
@@ -478,9 +490,11 @@ int enqueue_step(lbw_handle *h) {
                                                    h->sflip ? 1 : 0, h->odd, h->launch.lbm_block,
                                                    h->grid_lbm, nodes, h->stream);
         }
-        else
-            e = lbw::launch_collide_stream(h->q, h->precision, current(h, 0), h->odd,
-                                           h->launch.lbm_block, h->stream);
+        else {
+            lbw::RunDev r = current(h, 0);
+            if (fused) r.c = fused->c_in;
+            e = lbw::launch_collide_stream(h->q, h->precision, r, h->odd, h->launch.lbm_block, h->stream);
+        }
         if (e != hipSuccess) return hip_fail(e, "collide-stream launch");
     }
     if ((rc = span_close(h, sp, h->stream))) return rc;
@@ -496,6 +510,18 @@ int enqueue_step(lbw_handle *h) {
         a.grid = h->grid_tr;
         hipError_t e = lbw::launch_transport_batched(h->dim, h->precision, a, h->stream);
         if (e != hipSuccess) return hip_fail(e, "batched transport launch");
+    } else if (fused) {
+        const lbw::RunDev r = current(h, 0);
+        const size_t es = elem_size(h->precision);
+        for (int i = 0; i < r.ncls; ++i) {
+            const size_t off = (size_t)i * r.N * es;
+            auto at = [&](void *p) -> void * { return p ? (char *)p + off : nullptr; };
+            lbw::RunDev v = class_view(h, r, 0, i);
+            v.c = at(fused->c_in);
+            hipError_t e = lbw::launch_rk3_fused2d(h->precision, v, at(fused->c_out), at(fused->a1),
+                                                   at(fused->a2), h->stream);
+            if (e != hipSuccess) return hip_fail(e, "fused transport launch");
+        }
     } else {
         for (int b = 0; b < h->nbatch; ++b) {
             const lbw::RunDev r = current(h, b);
@@ -514,16 +540,24 @@ int enqueue_step(lbw_handle *h) {
     return LBW_OK;
 }
 
+// Two steps; fused: C goes from its own buffer to the first stage's and back,
+// and neither step keeps its stages.
+int enqueue_pair(lbw_handle *h, bool fused) {
+    const lbw::RunDev &r = h->run[0];
+    const FusedStep there{r.c, r.c1, nullptr, nullptr}, back{r.c1, r.c, nullptr, nullptr};
+    const int rc = enqueue_step(h, fused ? &there : nullptr);
+    return rc ? rc : enqueue_step(h, fused ? &back : nullptr);
+}
+
 // Capture two steps from the current state into a graph (the state returns
 // to where it was: two steps restore the parity and the S roles).
-int build_graph(lbw_handle *h) {
+int build_graph(lbw_handle *h, bool fused) {
     release_graph(h);
     const bool odd = h->odd, sflip = h->sflip;
     const int64_t steps = h->steps;
     hipError_t e = hipStreamBeginCapture(h->stream, hipStreamCaptureModeRelaxed);
     if (e != hipSuccess) return hip_fail(e, "graph capture begin");
-    int rc = enqueue_step(h);
-    if (!rc) rc = enqueue_step(h);
+    const int rc = enqueue_pair(h, fused);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(h->stream, &g);
     h->odd = odd;
@@ -542,6 +576,7 @@ int build_graph(lbw_handle *h) {
     }
     h->graph_odd = odd;
     h->graph_sflip = sflip;
+    h->graph_fused = fused;
     return LBW_OK;
 }
 }  // namespace
@@ -550,15 +585,24 @@ int lbw_step(lbw_handle *h, int32_t nsteps) {
     if (!h) return fail(LBW_ERR_INVAL, "NULL handle");
     if (nsteps < 0) return fail(LBW_ERR_INVAL, "nsteps must be >= 0");
     int rc;
-    if (h->launch.graph && !h->timing && nsteps >= 2) {
-        if (!h->stream) return fail(LBW_ERR_UNSUPPORTED, "graph replay needs a non-null stream");
-        if (!h->gexec || h->graph_odd != h->odd || h->graph_sflip != h->sflip)
-            if ((rc = build_graph(h))) return rc;
-        while (nsteps >= 2) {
+    const bool graph = h->launch.graph && !h->timing && nsteps >= 2;
+    if (graph && !h->stream) return fail(LBW_ERR_UNSUPPORTED, "graph replay needs a non-null stream");
+    // pairs of steps: with the fused transport all but the call's last one or
+    // two steps, which run the stages one by one and so leave the stage
+    // buffers as every step does; else, replaying a graph, every pair
+    const bool fused = nsteps >= 3 && fused_applies(h);
+    int32_t pairs = fused ? (nsteps - 1) / 2 : (graph ? nsteps / 2 : 0);
+    nsteps -= 2 * pairs;
+    if (graph && pairs && (!h->gexec || h->graph_odd != h->odd || h->graph_sflip != h->sflip ||
+                           h->graph_fused != fused))
+        if ((rc = build_graph(h, fused))) return rc;
+    for (; pairs > 0; --pairs) {
+        if (graph) {
             hipError_t e = hipGraphLaunch(h->gexec, h->stream);
             if (e != hipSuccess) return hip_fail(e, "graph launch");
             h->steps += 2;
-            nsteps -= 2;
+        } else if ((rc = enqueue_pair(h, fused))) {
+            return rc;
         }
     }
     for (int32_t s = 0; s < nsteps; ++s)
@@ -709,13 +753,20 @@ int lbw_replay(lbw_handle *h, int32_t run, int32_t n, void *const *c_out, void *
     for (int i = 0; i < n; ++i)
         if (!c_out[i] || !a1_out[i] || !a2_out[i] || (lbm && (!u_out[i] || !rho_out[i])))
             return fail(LBW_ERR_INVAL, "NULL buffer for replayed step %d", i);
+    // fused: step i reads C from c_out[i] and writes it straight to c_out[i + 1]
+    // (the last step to the run's own buffer), so only the first is copied;
+    // needs the C buffers to differ from step to step
+    bool fused = n > 0 && fused_applies(h);
+    for (int i = 0; i < n && fused; ++i) fused = c_out[i] != (i + 1 < n ? c_out[i + 1] : h->run[run].c);
     for (int i = 0; i < n && !rc; ++i) {
-        rc = lbw_export(h, run, LBW_FIELD_C, c_out[i]);
+        if (!fused || i == 0) rc = lbw_export(h, run, LBW_FIELD_C, c_out[i]);
         if (!rc && lbm) rc = lbw_rebind(h, run, LBW_FIELD_U, u_out[i]);
         if (!rc && lbm) rc = lbw_rebind(h, run, LBW_FIELD_RHO, rho_out[i]);
         if (!rc) rc = lbw_rebind(h, run, LBW_FIELD_STAGE1, a1_out[i]);
         if (!rc) rc = lbw_rebind(h, run, LBW_FIELD_STAGE2, a2_out[i]);
-        if (!rc) rc = lbw_step(h, 1);
+        if (rc) break;
+        const FusedStep step{c_out[i], i + 1 < n ? c_out[i + 1] : h->run[run].c, a1_out[i], a2_out[i]};
+        rc = fused ? enqueue_step(h, &step) : lbw_step(h, 1);
     }
     // bind the per-step outputs back to the handle's own buffers
     int rb = lbw_rebind(h, run, LBW_FIELD_STAGE1, nullptr);

@@ -107,6 +107,13 @@ hipError_t launch_one_stage(int dim, int precision, const RunDev &r, const lbw_l
                             int stage, hipStream_t st);
 // The launch's tile shape for n runs advanced together; fields the caller left
 // at 0 are chosen for those runs' sizes.
+// Whether a run takes the fused transport: 2D, no launch shape set, and a grid
+// small enough.
+bool rk3_fused2d_applies(int dim, const RunDev &r, const lbw_launch &l);
+// The whole transport of a 2D step in one launch: reads C from r.c, writes the
+// result to cout (another buffer) and, where given, the stages to a1 and a2.
+hipError_t launch_rk3_fused2d(int precision, const RunDev &r, void *cout, void *a1, void *a2,
+                              hipStream_t st);
 TileShape resolve_tile_shape(int dim, int precision, const lbw_launch &l, const RunDev *runs, int n);
 // Tiles (blocks) of one run in that shape, over all vertical chunks.
 int64_t transport_tiles(int dim, const RunDev &r, const TileShape &s);

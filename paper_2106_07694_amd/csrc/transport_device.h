@@ -88,4 +88,17 @@ __device__ __forceinline__ T rk3_stage3(T c, T a, T L) {
     return c + (T)(2.0 / 3.0) * ((a - c) + L);
 }
 
+// Mass one bottom cell k settles onto the floor in a step (D += Vs (C/6 +
+// a1/6 + 2 a2/3)), from its C and stages; in FP64, with the cell's own settling
+// speed when it depends on S (vs_s = 0: exactly vs).
+template <typename T, bool VSS>
+__device__ __forceinline__ double deposit_of(const RunDev &r, const T *s, int64_t k, T c, T a1, T a2) {
+#pragma clang fp contract(on)
+    const double vsd = VSS ? r.vs * (1.0 - r.vs_s * (double)s[k]) : r.vs;
+    const double o0 = vsd * (double)c;
+    const double o1 = vsd * (double)a1;
+    const double o2 = vsd * (double)a2;
+    return o0 / 6.0 + o1 / 6.0 + 2.0 / 3.0 * o2;
+}
+
 }  // namespace lbw

@@ -1,0 +1,241 @@
+// transport_fused.hip -- the whole transport of one 2D step (three RK stages,
+// the S update and the deposit) in one launch, for grids too small to fill
+// the chip with three.
+//
+// What bounds it: on such grids a stage launch costs its fixed latency (start,
+// first loads, two barriers, about 4.4 us) whatever the cells in it, and the
+// next stage cannot start before it ends.  Here a block keeps C, the velocity
+// and both intermediate stages of its TX x TY cells in LDS, with the halo the
+// stages reach (nine cells of C, six of stage 1, three of stage 2), and
+// recomputes the halo instead of exchanging it.  The recomputed cells
+// (TX + 12)(TY + 12) + (TX + 6)(TY + 6) cost more arithmetic than three
+// launches spend, so larger grids keep the tiled stages.
+//
+// The step reads C from r.c and writes the result to another buffer (a
+// neighbouring block still reads the old values for its halo), so the caller
+// alternates two buffers over consecutive steps.  Faces and combinations are
+// those of the tiled stages, in the same order: the same bits.
+#include "transport_face.h"
+
+namespace lbw {
+namespace {
+
+// Position outside [0, n) reached by a halo or an overhanging tile, on a
+// periodic axis.
+__device__ __forceinline__ int wrap_index(int j, int n) {
+    j += j < 0 ? n : 0;
+    j -= j >= n ? n : 0;
+    if ((unsigned)j < (unsigned)n) return j;
+    j %= n;                                          // an axis shorter than the reach
+    return j < 0 ? j + n : j;
+}
+
+template <typename T, int SCHEME, bool VSS, bool FS, int TX, int TY, int NT>
+__global__ void __launch_bounds__(NT) k_rk3_2d(RunDev r, T *__restrict__ cout, T *__restrict__ a1out,
+                                               T *__restrict__ a2out) {
+    // C on the tile with nine halo cells, stage 1 with six, stage 2 with three;
+    // the x velocity on stage 1's rows, the vertical transport velocity on
+    // stage 1's columns
+    constexpr int RX = TX + 18, RY = TY + 18, PX = TX + 12, PY = TY + 12, QX = TX + 6, QY = TY + 6;
+    __shared__ T sC[RY * RX], sU[PY * RX], sW[RY * PX], sA1[PY * PX], sA2[QY * QX];
+    __shared__ T sFx[PY * (PX + 1)], sFy[(PY + 1) * PX];
+
+    const int tid = threadIdx.x;
+    const int nx = r.nx, ny = r.ny;
+    const int x0 = (int)blockIdx.x * TX, y0 = (int)blockIdx.y * TY;
+    const bool walls = !r.vper;
+    const T *__restrict__ c = (const T *)r.c;
+    const T *__restrict__ ux = (const T *)r.u;
+    const T *__restrict__ uy = ux + r.N;
+    const T *__restrict__ s = (const T *)r.s;
+    const T vs = (T)r.vs, kap = (T)r.kappa_c, eps = (T)r.eps;
+    auto settle = [&](int k) -> T {
+        if constexpr (VSS) return vs * ((T)1 - (T)r.vs_s * s[k]);
+        else return vs;
+    };
+    // stored row of position p (mirrored beyond a wall; rows further out than
+    // the three that any cell of the grid reads are clamped into range)
+    auto row = [&](int p, bool &ghost) -> int {
+        ghost = false;
+        if (!walls) return wrap_index(p, ny);
+        if (p < 0) { p = -1 - p; ghost = true; }
+        else if (p >= ny) { p = 2 * ny - 1 - p; ghost = true; }
+        return min(max(p, 0), ny - 1);
+    };
+
+    // stage the inputs, every load issued before the first store to LDS
+    constexpr int NC = RY * RX, NU = PY * RX, NW = RY * PX;
+    constexpr int LC = (NC + NT - 1) / NT, LU = (NU + NT - 1) / NT, LW = (NW + NT - 1) / NT;
+    T pc[LC], pu[LU], pw[LW], ps[VSS ? LW : 1];
+    bool gw[LW];
+#pragma unroll
+    for (int q = 0; q < LC; ++q) {
+        const int i = min(tid + q * NT, NC - 1), ry = i / RX, cx = i % RX;
+        bool g;
+        pc[q] = c[wrap_index(x0 - 9 + cx, nx) + nx * row(y0 - 9 + ry, g)];
+    }
+#pragma unroll
+    for (int q = 0; q < LU; ++q) {
+        const int i = min(tid + q * NT, NU - 1), ry = i / RX, cx = i % RX;
+        bool g;
+        pu[q] = ux[wrap_index(x0 - 9 + cx, nx) + nx * row(y0 - 6 + ry, g)];
+    }
+#pragma unroll
+    for (int q = 0; q < LW; ++q) {
+        const int i = min(tid + q * NT, NW - 1), ry = i / PX, cx = i % PX;
+        const int k = wrap_index(x0 - 6 + cx, nx) + nx * row(y0 - 9 + ry, gw[q]);
+        pw[q] = uy[k];
+        if constexpr (VSS) ps[q] = settle(k);
+    }
+#pragma unroll
+    for (int q = 0; q < LC; ++q) {
+        const int i = tid + q * NT;
+        if (i < NC) sC[i] = pc[q];
+    }
+#pragma unroll
+    for (int q = 0; q < LU; ++q) {
+        const int i = tid + q * NT;
+        if (i < NU) sU[i] = pu[q];
+    }
+#pragma unroll
+    for (int q = 0; q < LW; ++q) {
+        const int i = tid + q * NT;
+        if (i < NW) sW[i] = (gw[q] ? -pw[q] : pw[q]) - (VSS ? ps[q] : vs);
+    }
+
+    // S: forward Euler on the tile's own cells, straight from memory
+    if constexpr (FS) {
+        const T kaps = (T)r.kappa_s;
+        for (int i = tid; i < TX * TY; i += NT) {
+            const int x = x0 + i % TX, y = y0 + i / TX;
+            if (x >= nx || y >= ny) continue;
+            const int k = x + nx * y;
+            const int kl = x == 0 ? k + nx - 1 : k - 1, kr = x == nx - 1 ? k - (nx - 1) : k + 1;
+            const int kd = y == 0 ? k + nx * (ny - 1) : k - nx, ku = y == ny - 1 ? k - nx * (ny - 1) : k + nx;
+            const T s0 = s[k], u0 = ux[k], v0 = uy[k];
+            const T gl = s_face<T>(s[kl], s0, ux[kl], u0, kaps), gr = s_face<T>(s0, s[kr], u0, ux[kr], kaps);
+            const T gd = (walls && y == 0) ? (T)0 : s_face<T>(s[kd], s0, uy[kd], v0, kaps);
+            const T gu = (walls && y == ny - 1) ? (T)0 : s_face<T>(s0, s[ku], v0, uy[ku], kaps);
+            T L = -(gr - gl);
+            L -= gu - gd;
+            ((T *)r.s2)[k] = s0 + L;
+        }
+    }
+    __syncthreads();
+
+    // one RK stage on the tile with a halo of H cells; `in` holds its input
+    // with three more
+    auto stage = [&](auto stage_id, auto halo, const T *in) {
+        constexpr int STAGE = decltype(stage_id)::value, H = decltype(halo)::value;
+        constexpr int OX = TX + 2 * H, OY = TY + 2 * H, IX = OX + 6;
+        constexpr int FX = OY * (OX + 1), FY = (OY + 1) * OX;
+        for (int i = tid; i < FX; i += NT) {             // face on the left of cell (cx, ry)
+            const int ry = i / (OX + 1), cx = i % (OX + 1);
+            const T *a = in + (ry + 3) * IX + cx, *w = sU + (ry + 6 - H) * RX + cx + 6 - H;
+            sFx[i] = face6<T, SCHEME>(a[0], a[1], a[2], a[3], a[4], a[5], w[0], w[1], w[2], w[3], w[4],
+                                      w[5], kap, eps);
+        }
+        for (int i = tid; i < FY; i += NT) {             // face below cell (cx, ry)
+            const int ry = i / OX, cx = i % OX, y = y0 - H + ry;
+            if (walls && (y < 0 || y > ny)) continue;    // no cell of the grid reads it
+            const T *a = in + ry * IX + cx + 3, *w = sW + (ry + 6 - H) * PX + cx + 6 - H;
+            T f;
+            if (walls && y == 0) f = -settle(wrap_index(x0 - H + cx, nx)) * a[3 * IX];   // absorbing bottom
+            else if (walls && y == ny) f = (T)0;
+            else
+                f = face6<T, SCHEME>(a[0], a[IX], a[2 * IX], a[3 * IX], a[4 * IX], a[5 * IX], w[0], w[PX],
+                                     w[2 * PX], w[3 * PX], w[4 * PX], w[5 * PX], kap, eps);
+            sFy[i] = f;
+        }
+        __syncthreads();
+        for (int i = tid; i < OX * OY; i += NT) {
+            const int ry = i / OX, cx = i % OX, x = x0 - H + cx, y = y0 - H + ry;
+            if (walls && (y < 0 || y >= ny)) continue;   // rows beyond a wall are mirrored below
+            T L = -(sFy[i + OX] - sFy[i]);
+            L -= sFx[ry * (OX + 1) + cx + 1] - sFx[ry * (OX + 1) + cx];
+            const T a = in[(ry + 3) * IX + cx + 3];
+            const bool own = cx >= H && cx < H + TX && ry >= H && ry < H + TY && x < nx && y < ny;
+            const int k = x + nx * y;
+            if constexpr (STAGE == 3) {
+                const T c0 = sC[(ry + 9) * RX + cx + 9];
+                if (own) {
+                    cout[k] = rk3_stage3<T>(c0, a, L);
+                    if (walls && y == 0) r.dep[x] += deposit_of<T, VSS>(r, s, k, c0, sA1[6 * PX + cx + 6], a);
+                }
+            } else {
+                T *out = STAGE == 1 ? sA1 : sA2, *global = STAGE == 1 ? a1out : a2out;
+                const T v = STAGE == 1 ? a + L : rk3_stage2<T>(sC[(ry + 9 - H) * RX + cx + 9 - H], a, L);
+                out[i] = v;
+                if (walls) {                             // images beyond the walls
+                    const int lo = -1 - y - (y0 - H), hi = 2 * ny - 1 - y - (y0 - H);
+                    if (lo >= 0) out[lo * OX + cx] = v;
+                    if (hi < OY) out[hi * OX + cx] = v;
+                }
+                if (global && own) global[k] = v;
+            }
+        }
+        if constexpr (STAGE != 3) __syncthreads();
+    };
+    using std::integral_constant;
+    stage(integral_constant<int, 1>{}, integral_constant<int, 6>{}, sC);
+    stage(integral_constant<int, 2>{}, integral_constant<int, 3>{}, sA1);
+    stage(integral_constant<int, 3>{}, integral_constant<int, 0>{}, sA2);
+}
+
+template <typename T, int SCHEME, int TX, int TY, int NT>
+hipError_t fused_tile(const RunDev &r, void *cout, void *a1, void *a2, hipStream_t st) {
+    const dim3 grid((unsigned)((r.nx + TX - 1) / TX), (unsigned)((r.ny + TY - 1) / TY));
+    T *o = (T *)cout, *p = (T *)a1, *q = (T *)a2;
+    if (r.vs_s != 0.0 && r.has_s) k_rk3_2d<T, SCHEME, true, true, TX, TY, NT><<<grid, NT, 0, st>>>(r, o, p, q);
+    else if (r.vs_s != 0.0) k_rk3_2d<T, SCHEME, true, false, TX, TY, NT><<<grid, NT, 0, st>>>(r, o, p, q);
+    else if (r.has_s) k_rk3_2d<T, SCHEME, false, true, TX, TY, NT><<<grid, NT, 0, st>>>(r, o, p, q);
+    else k_rk3_2d<T, SCHEME, false, false, TX, TY, NT><<<grid, NT, 0, st>>>(r, o, p, q);
+    return hipGetLastError();
+}
+
+// The smallest tile whose blocks find a CU each: a smaller tile recomputes
+// more halo per cell, a larger one leaves CUs idle.  us per step, collide
+// included (16x16, 32x16, 32x32): single precision 128x256 11.4, 12.6, 15.1;
+// 256x512 15.8, 14.7, 17.1; 700x1100 50.9, 42.5, 40.4; double 128x256 13.5,
+// 15.6, 19.6; 256x512 20.9, 19.6, 23.4; 700x1100 78.8, 66.7, 74.5 (32x32 holds
+// 114 KB of LDS there, one block per CU).
+template <typename T, int SCHEME>
+hipError_t fused_scheme(const RunDev &r, void *cout, void *a1, void *a2, hipStream_t st) {
+    auto fits = [&](int tx, int ty) { return (int64_t)((r.nx + tx - 1) / tx) * ((r.ny + ty - 1) / ty) <= 256; };
+    if (fits(16, 16)) return fused_tile<T, SCHEME, 16, 16, 1024>(r, cout, a1, a2, st);
+    if constexpr (sizeof(T) == 4) {
+        if (!fits(32, 16)) return fused_tile<T, SCHEME, 32, 32, 1024>(r, cout, a1, a2, st);
+    }
+    return fused_tile<T, SCHEME, 32, 16, 1024>(r, cout, a1, a2, st);
+}
+
+template <typename T>
+hipError_t fused_t(const RunDev &r, void *cout, void *a1, void *a2, hipStream_t st) {
+    switch (r.scheme) {
+        case LBW_WENO5: return fused_scheme<T, LBW_WENO5>(r, cout, a1, a2, st);
+        case LBW_WENO3: return fused_scheme<T, LBW_WENO3>(r, cout, a1, a2, st);
+        case LBW_UPWIND1: return fused_scheme<T, LBW_UPWIND1>(r, cout, a1, a2, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+// Grids up to 3/4 of 2^20 cells: beyond, three launches of the march fill the
+// chip and the recomputed halo decides.  us per step, fused against march,
+// collide included: 64x128 11.3 against 19.6 (double 13.3, 20.5); 515x1030
+// 34.0, 36.9 (53.2, 58.3); 700x1100 40.4, 44.7 (66.7, 73.8); 1024x1024 47.9,
+// 47.0 (87.2, 79.2).  A launch shape set by the caller asks for the march.  One
+// block row per tile row: 65535 at most.
+bool rk3_fused2d_applies(int dim, const RunDev &r, const lbw_launch &l) {
+    return dim == 2 && l.variant == 0 && !l.tile_x && !l.tile_y && !l.tile_rows &&
+           r.N <= (3 << 18) && r.ny <= 65535 * 16;
+}
+
+hipError_t launch_rk3_fused2d(int precision, const RunDev &r, void *cout, void *a1, void *a2,
+                              hipStream_t st) {
+    return precision == LBW_FP32_SHIFTED ? fused_t<float>(r, cout, a1, a2, st)
+                                         : fused_t<double>(r, cout, a1, a2, st);
+}
+
+}  // namespace lbw

@@ -319,13 +319,8 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
     // done before the march so that no load or store sits on a path of its own
     if constexpr (STAGE == 3) {
         if (walls && v0 == 0 && active) {
-            // the deposit's settling speed in FP64 (vs_s = 0: exactly vs)
-            const double vsd =
-                VSS ? r.vs * (1.0 - r.vs_s * (double)at<T>(plane(r.s, 0), colb)) : r.vs;
-            const double o0 = vsd * (double)at<T>(plane(r.c, 0), colb);
-            const double o1 = vsd * (double)at<T>(plane(r.c1, 0), colb);
-            const double o2 = vsd * (double)a_first;
-            r.dep[col] += o0 / 6.0 + o1 / 6.0 + 2.0 / 3.0 * o2;
+            r.dep[col] += deposit_of<T, VSS>(r, (const T *)r.s, col, at<T>(plane(r.c, 0), colb),
+                                             at<T>(plane(r.c1, 0), colb), a_first);
         }
     }
 
