@@ -14,6 +14,15 @@
 //     node's flux and indicators computed once, as the node enters);
 //   * the next plane's global loads are issued before the current plane is
 //     computed (software pipelining).
+// What bounds it: instruction issue, vector and scalar alike.  A SIMD issues
+// one of each every four cycles, and the march's scalar work (plane addresses,
+// the vertical rule, masks) once outnumbered its vector work, 200 against 142
+// instructions a plane in 2D; kept free of branches, masks and 64-bit products
+// it is about 100 (3D 236 -> 130 against 206).  Measured, us per step: 3D
+// 256x256x512 transport 640 -> 610, 97x63x130 45 -> 38, 2D + S 1024x2048 49.6
+// -> 46.3, the 30-run sweep 250 -> 236 in all; double precision unchanged (its
+// vector work is twice as long).
+//
 // Arithmetic and wall rules are those of the plain kernels (transport.hip):
 // WENO face fluxes from the upwind side, central diffusion, mirror ghosts
 // with a sign flip of the vertical fluid velocity, closed top, absorbing
@@ -104,7 +113,7 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
                   O_S = O_FY + ((D == 3) ? (TY + 1) * TX : 1), O_GX = O_S + (FS ? SXL * SYL : 1),
                   O_GY = O_GX + (FS ? TY * (TX + 1) : 1),
                   O_END = O_GY + ((FS && D == 3) ? (TY + 1) * TX : 1);
-    __shared__ T smem[O_END];
+    __shared__ T smem[O_END + 64];
     T *const sA = smem + O_A;                   // stage input a, plane with halos
     T *const sUx = smem + O_UX;                 // x velocity, rows with x halo
     T *const sUy = smem + O_UY;                 // y velocity, columns with y halo
@@ -119,8 +128,8 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
     const int x0 = bx * TX, y0 = by * TY;
     const int gxl = x0 + tx, gyl = y0 + ty;         // own column (may be outside)
     const bool active = FULL || (gxl < g.nx && (D == 2 || gyl < g.ny));
-    const int xw = active ? gxl : gxl % g.nx;       // wrapped column for loads
-    const int yw = (D == 3) ? (active ? gyl : gyl % g.ny) : 0;
+    const int xw = FULL ? gxl : min(gxl, g.nx - 1); // column for loads
+    const int yw = (D == 3) ? (FULL ? gyl : min(gyl, g.ny - 1)) : 0;
     const int col = xw + g.nx * yw;                 // < nx * ny
     uint32_t colb = (uint32_t)col * (uint32_t)sizeof(T);
     const int v0 = bz * g.chunk;
@@ -132,8 +141,10 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
     const T *__restrict__ uv = ux + (int64_t)(D - 1) * g.N;
     const T vs = (T)r.vs, kap = (T)r.kappa_c, eps = (T)r.eps;
     const bool walls = !g.vper;
+    // (a 32 x 32-bit product: planes and plane bytes both fit)
+    const uint32_t plane_bytes = (uint32_t)(g.sv * (int64_t)sizeof(T));
     auto plane = [&](const void *base, int v) -> const void * {
-        return (const char *)base + (int64_t)v * g.sv * (int64_t)sizeof(T);
+        return (const char *)base + (uint64_t)(uint32_t)v * plane_bytes;
     };
     // settling speed at plane vv of this column
     auto vs_at = [&](int vv) -> T {
@@ -141,29 +152,43 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
         else return vs;
     };
     auto wplane = [&](void *base, int v) -> void * {
-        return (char *)base + (int64_t)v * g.sv * (int64_t)sizeof(T);
+        return (char *)base + (uint64_t)(uint32_t)v * plane_bytes;
     };
 
-    // vertical index with the wall/periodic rule; sets flip for mirrored nodes
-    auto vidx = [&](int v, bool &flip) -> int {
-        flip = false;
-        // the march reaches at most three planes below and four above the
-        // axis (v in [-3, nv + 3]) and nv >= 6, so one wrap suffices
-        if (!walls) return v < 0 ? v + g.nv : (v >= g.nv ? v - g.nv : v);
-        if (v < 0) { flip = true; return -1 - v; }
-        if (v >= g.nv) { flip = true; return 2 * g.nv - 1 - v; }
-        return v;
+    // vertical index with the wall/periodic rule, and the sign the vertical
+    // fluid velocity takes there (-1 at a mirrored node).  The march reaches
+    // at most three planes below and four above the axis (v in [-3, nv + 3])
+    // and nv >= 6, so one reflection or wrap suffices.  Selects on scalars, not
+    // branches: a wave issues one scalar instruction where it issues one
+    // vector instruction, and the march has few vector ones to hide them
+    auto vidx_up = [&](int v, T &sgn) -> int {      // v >= 0
+        const bool over = v >= g.nv;
+        sgn = over && walls ? (T)-1 : (T)1;
+        const int past = walls ? 2 * g.nv - 1 - v : v - g.nv;
+        return over ? past : v;
     };
-    auto load_av = [&](int v, T &a, T &w) {
-        bool flip;
-        const int vv = vidx(v, flip);
+    auto vidx = [&](int v, T &sgn) -> int {
+        const bool under = v < 0;
+        const int up = vidx_up(v, sgn);
+        sgn = under && walls ? (T)-1 : sgn;
+        const int past = walls ? -1 - v : v + g.nv;
+        return under ? past : up;
+    };
+    auto load_at = [&](int vv, T sgn, T &a, T &w) {
         a = at<T>(plane(ain, vv), colb);
         const T u = at<T>(plane(uv, vv), colb);
-        w = (flip ? -u : u) - vs_at(vv);
+        w = sgn * u - vs_at(vv);
+    };
+    auto load_av = [&](int v, T &a, T &w) {
+        T sgn;
+        const int vv = vidx(v, sgn);
+        load_at(vv, sgn, a, w);
     };
 
     // lateral halo slots of this thread (fixed over the march), as byte
-    // offsets within a plane and LDS indices (-1: no slot)
+    // offsets within a plane and LDS indices; a spare slot (its array filled)
+    // reads column 0 and writes to a place of its lane's past the arrays, so
+    // publication needs no lane masks
     // a-plane cross: rows ty in [0,TY) x cols [0,AX), plus (3D) y-halo rows
     constexpr int NA = (D == 3) ? AX * TY + TX * 6 : AX;
     constexpr int NUX = AX * TY;
@@ -175,42 +200,53 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
     int ldsX[SUX];
     uint32_t offY[(SUY > 0) ? SUY : 1];
     int ldsY[(SUY > 0) ? SUY : 1];
-    auto wrapx = [&](int x) { x %= g.nx; return x < 0 ? x + g.nx : x; };
-    auto wrapy = [&](int y) { y %= g.ny; return y < 0 ? y + g.ny : y; };
+    // lateral wrap of a position from three cells below the axis on.  Positions
+    // past its third cell beyond are read by no cell of the grid and are
+    // clamped there, so one wrap does unless the axis has fewer than three
+    // cells (the general remainder, twelve of which cost as much as two planes
+    // of the march)
+    auto wrap = [](int j, int n) {
+        j = min(j, n + 2);
+        if (n < 3) j %= n;
+        j += j < 0 ? n : 0;
+        return j - (j >= n ? n : 0);
+    };
+    auto wrapx = [&](int x) { return wrap(x, g.nx); };
+    auto wrapy = [&](int y) { return wrap(y, g.ny); };
     auto lat = [&](int x, int y) { return (uint32_t)(x + g.nx * y) * (uint32_t)sizeof(T); };
 #pragma unroll
     for (int s = 0; s < SA; ++s) {
         const int i = tid + s * NT;
-        ldsA[s] = -1;
+        ldsA[s] = O_END + (tid & 63);
         offA[s] = 0;
         if (i < NA) {
             int lx, ly;  // plane-local coords, halo origin at (-3, -3)
             if (i < AX * TY) { lx = i % AX; ly = (D == 3) ? (i / AX) + 3 : 0; }
             else { const int j = i - AX * TY; lx = (j % TX) + 3; ly = (j / TX) < 3 ? (j / TX) : (j / TX) + TY; }
             offA[s] = lat(wrapx(x0 + lx - 3), (D == 3) ? wrapy(y0 + ly - 3) : 0);
-            ldsA[s] = ly * AX + lx;
+            ldsA[s] = O_A + ly * AX + lx;
         }
     }
 #pragma unroll
     for (int s = 0; s < SUX; ++s) {
         const int i = tid + s * NT;
-        ldsX[s] = -1;
+        ldsX[s] = O_END + (tid & 63);
         offX[s] = 0;
         if (i < NUX) {
             const int lx = i % AX, ly = i / AX;
             offX[s] = lat(wrapx(x0 + lx - 3), (D == 3) ? wrapy(y0 + ly) : 0);
-            ldsX[s] = ly * AX + lx;
+            ldsX[s] = O_UX + ly * AX + lx;
         }
     }
 #pragma unroll
     for (int s = 0; s < SUY; ++s) {
         const int i = tid + s * NT;
-        ldsY[s] = -1;
+        ldsY[s] = O_END + (tid & 63);
         offY[s] = 0;
         if (i < NUY) {
             const int lx = i % TX, ly = i / TX;
             offY[s] = lat(wrapx(x0 + lx), wrapy(y0 + ly - 3));
-            ldsY[s] = ly * TX + lx;
+            ldsY[s] = O_UY + ly * TX + lx;
         }
     }
 
@@ -223,12 +259,12 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
 #pragma unroll
     for (int s = 0; s < SSS; ++s) {
         const int i = tid + s * NT;
-        ldsS[s] = -1;
+        ldsS[s] = O_END + (tid & 63);
         offS[s] = 0;
         if (i < NSS) {
             const int lx = i % SXL, ly = i / SXL;
             offS[s] = lat(wrapx(x0 + lx - 1), (D == 3) ? wrapy(y0 + ly - 1) : 0);
-            ldsS[s] = i;
+            ldsS[s] = O_S + i;
         }
     }
     const T *__restrict__ sin = (const T *)(FS && s_entry ? r.s : r.c);
@@ -309,8 +345,8 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
         s_c = at<T>(plane(sin, v0), colb);
         us_c = at<T>(plane(uv, v0), colb);
         if (!(walls && v0 == 0)) {
-            bool flip;
-            const int vb = vidx(v0 - 1, flip);
+            T sgn;
+            const int vb = vidx(v0 - 1, sgn);
             gbelow = sface(at<T>(plane(sin, vb), colb), s_c, at<T>(plane(uv, vb), colb), us_c);
         }
     }
@@ -327,14 +363,12 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
     // prefetch registers for the lateral planes
     T pA[SA], pX[SUX], pY[(SUY > 0) ? SUY : 1], pS[(SSS > 0) ? SSS : 1];
     auto prefetch = [&](int v) {
-        bool flip;
-        const int vv = vidx(v, flip);
+        T sgn;
+        const int vv = vidx_up(v, sgn);
         const void *pa = plane(ain, vv), *px = plane(ux, vv), *py = plane(uy, vv);
 #pragma unroll
         for (int s = 0; s < SSS; ++s) pS[s] = at<T>(plane(sin, vv), offS[s]);
-        // unconditional: slots without an LDS target read column 0 (in
-        // bounds) and are dropped at publication, so no load sits behind a
-        // branch
+        // unconditional, so no load sits behind a branch
 #pragma unroll
         for (int s = 0; s < SA; ++s) pA[s] = at<T>(pa, offA[s]);
 #pragma unroll
@@ -372,13 +406,13 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
             for (int s = 0; s < SSS; ++s) asm volatile("" : "+v"(offS[s]));
             // publish plane v
 #pragma unroll
-            for (int s = 0; s < SA; ++s) if (ldsA[s] >= 0) sA[ldsA[s]] = pA[s];
+            for (int s = 0; s < SA; ++s) smem[ldsA[s]] = pA[s];
 #pragma unroll
-            for (int s = 0; s < SUX; ++s) if (ldsX[s] >= 0) sUx[ldsX[s]] = pX[s];
+            for (int s = 0; s < SUX; ++s) smem[ldsX[s]] = pX[s];
 #pragma unroll
-            for (int s = 0; s < SUY; ++s) if (ldsY[s] >= 0) sUy[ldsY[s]] = pY[s];
+            for (int s = 0; s < SUY; ++s) smem[ldsY[s]] = pY[s];
 #pragma unroll
-            for (int s = 0; s < SSS; ++s) if (ldsS[s] >= 0) sS[ldsS[s]] = pS[s];
+            for (int s = 0; s < SSS; ++s) smem[ldsS[s]] = pS[s];
             __syncthreads();
             // loads, in the order they are consumed (the load counter drains in
             // issue order, so waiting for one waits for all issued before it):
@@ -389,12 +423,13 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
             // it inside)
             T cown = (T)0;
             if (STAGE != 1) cown = at<T>(plane(r.c, v), colb);
-            T anext, wnext;
-            load_av(v + 4, anext, wnext);
+            T anext, wnext, snext;
+            const int vnext = vidx_up(v + 4, snext);
+            load_at(vnext, snext, anext, wnext);
             T s_n = (T)0, us_n = (T)0;
             if constexpr (FS) {
-                bool flip;
-                const int vn = vidx(v + 1, flip);
+                T sgn;
+                const int vn = vidx_up(v + 1, sgn);
                 s_n = at<T>(plane(sin, vn), colb);
                 us_n = at<T>(plane(uv, vn), colb);
             }
@@ -464,9 +499,7 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
             }
             // vertical face above this cell
             T fabove;
-            if (walls && v == g.nv - 1) {
-                fabove = (T)0;
-            } else if constexpr (NV) {
+            if constexpr (NV) {
                 auto S6 = [&](int m) { return (ph + m) % 6; };
                 fabove = weno5_flux_nodes<T>(vP[S6(2)], vH[S6(0)], vH[S6(1)], vH[S6(2)],
                                              vH[S6(3)], vH[S6(4)], vH[S6(5)], EL(S6(1)), EL(S6(2)),
@@ -475,6 +508,7 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
                 fabove = face6<T, SCHEME>(A(0), A(1), A(2), A(3), A(4), A(5), W(0), W(1), W(2), W(3),
                                           W(4), W(5), kap, eps);
             }
+            fabove = walls && v == g.nv - 1 ? (T)0 : fabove;
             T gabove = (T)0;
             if constexpr (FS) gabove = (walls && v == g.nv - 1) ? (T)0 : sface(s_c, s_n, us_c, us_n);
             __syncthreads();
