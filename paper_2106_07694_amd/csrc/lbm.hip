@@ -77,7 +77,8 @@ __global__ void __launch_bounds__(1024) k_collide_stream_batched(const RunDev *_
                                                                  const int *__restrict__ blk_start,
                                                                  int nbatch, int sflip) {
     const int total = blk_start[nbatch];
-    int b = 0;
+    if ((int)blockIdx.x >= total) return;
+    int b = entry_of(blk_start, nbatch, 0, blockIdx.x);
     for (int w = blockIdx.x; w < total; w += gridDim.x) {
         while (blk_start[b + 1] <= w) ++b;   // w only grows, so b only grows
         RunDev r = runs[b];

@@ -86,6 +86,20 @@ struct BatchArgs {
                                // S-dependent settling speed (each form in its own kernels)
 };
 
+// Entry of a work list that holds item w, at or after entry b: start[i] is the
+// first item of entry i (n entries, start[n] the total, which exceeds w).
+// Called by whole waves; each lane looks at one entry, so 64 of them cost one
+// load.  Entry by entry it was a chain of dependent scalar loads before a block
+// could start on its tile, five times over in a step.
+__device__ __forceinline__ int entry_of(const int *__restrict__ start, int n, int b, int w) {
+    const int lane = (int)(threadIdx.x & 63);
+    for (;;) {
+        const int at_or_before = __popcll(__ballot(start[min(b + lane + 1, n)] <= w));
+        b += at_or_before;
+        if (at_or_before < 64) return b;
+    }
+}
+
 // Launchers (return the launch error, if any).  `odd` selects the second
 // kernel of the in-place streaming pair.
 hipError_t launch_collide_stream(int q, int precision, const RunDev &r, bool odd,

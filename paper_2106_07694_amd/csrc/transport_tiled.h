@@ -605,9 +605,9 @@ __global__ void __launch_bounds__(TX *TY) k_stage_batched(const RunDev *__restri
         hi = (int)((int64_t)total * (xcd + 1) / 8);
         stride = per_xcd;
     }
+    int b = 0;
     for (int w = first; w < hi; w += stride) {
-        int b = 0;
-        while (tile_start[b + 1] <= w) ++b;                // runs are few; linear scan
+        b = entry_of(tile_start, nbatch, b, w);            // w only grows, so b only grows
         RunDev r = runs[b];
         if (form >= 0 && (r.vs_s != 0.0) != (form == 1)) continue;   // the other form's entry
         if (sflip) { void *t = r.s; r.s = r.s2; r.s2 = t; }
