@@ -139,6 +139,17 @@ lbw::RunDev class_view(const lbw_handle *h, const lbw::RunDev &r, int b, int i) 
     return v;
 }
 
+// The size classes of run b, for a launch that advances them together.
+lbw::ClassSet class_set(const lbw_handle *h, int b) {
+    lbw::ClassSet cs;
+    cs.of = cs.n = h->run[b].ncls;
+    for (int i = 0; i < LBW_MAX_CLASSES; ++i) {
+        cs.vs[i] = h->cfg[b].vs_class[i];
+        cs.kappa[i] = h->cfg[b].kappa_class[i];
+    }
+    return cs;
+}
+
 void release_graph(lbw_handle *h) {
     if (h->gexec) (void)hipGraphExecDestroy(h->gexec);
     if (h->graph) (void)hipGraphDestroy(h->graph);
@@ -511,25 +522,22 @@ int enqueue_step(lbw_handle *h, const FusedStep *fused = nullptr) {
         hipError_t e = lbw::launch_transport_batched(h->dim, h->precision, a, h->stream);
         if (e != hipSuccess) return hip_fail(e, "batched transport launch");
     } else if (fused) {
-        const lbw::RunDev r = current(h, 0);
-        const size_t es = elem_size(h->precision);
-        for (int i = 0; i < r.ncls; ++i) {
-            const size_t off = (size_t)i * r.N * es;
-            auto at = [&](void *p) -> void * { return p ? (char *)p + off : nullptr; };
-            lbw::RunDev v = class_view(h, r, 0, i);
-            v.c = at(fused->c_in);
-            hipError_t e = lbw::launch_rk3_fused2d(h->precision, v, at(fused->c_out), at(fused->a1),
-                                                   at(fused->a2), h->stream);
-            if (e != hipSuccess) return hip_fail(e, "fused transport launch");
-        }
+        lbw::RunDev r = current(h, 0);
+        r.c = fused->c_in;
+        hipError_t e = lbw::launch_rk3_fused2d(h->precision, r, class_set(h, 0), fused->c_out, fused->a1,
+                                               fused->a2, h->stream);
+        if (e != hipSuccess) return hip_fail(e, "fused transport launch");
     } else {
         for (int b = 0; b < h->nbatch; ++b) {
             const lbw::RunDev r = current(h, b);
-            for (int i = 0; i < r.ncls; ++i) {
-                hipError_t e = lbw::launch_transport(h->dim, h->precision, class_view(h, r, b, i),
-                                                     h->launch, h->stream);
-                if (e != hipSuccess) return hip_fail(e, "transport launch");
+            hipError_t e = hipSuccess;
+            if (h->launch.variant == 1) {
+                for (int i = 0; i < r.ncls && e == hipSuccess; ++i)
+                    e = lbw::launch_transport_plain(h->dim, h->precision, class_view(h, r, b, i), h->stream);
+            } else {
+                e = lbw::launch_transport_tiled(h->dim, h->precision, r, class_set(h, b), h->launch, h->stream);
             }
+            if (e != hipSuccess) return hip_fail(e, "transport launch");
         }
     }
     if ((rc = span_close(h, sp, h->stream))) return rc;

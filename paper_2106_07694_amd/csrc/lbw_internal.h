@@ -64,6 +64,30 @@ struct RunDev {
     double phi_c;        // volume fraction per unit C in the (1 - phi) of eq. 10
 };
 
+// The size classes a transport launch advances together: classes first ..
+// first + n - 1 of a run with `of` of them (of = 1: the run as it stands).
+// Each has its own C, stage buffers and deposit counters (class after class in
+// the run's arrays), settling speed and diffusivity; the S update rides with
+// class 0.
+struct ClassSet {
+    int32_t first = 0, n = 1, of = 1;
+    double vs[LBW_MAX_CLASSES], kappa[LBW_MAX_CLASSES];
+};
+
+// Make r the run as class i sees it; true if the class carries the S update.
+template <typename T>
+__device__ __forceinline__ bool select_class(RunDev &r, const ClassSet &cs, int i) {
+    if (cs.of <= 1) return true;
+    const int64_t off = i * r.N;
+    r.c = (T *)r.c + off;
+    r.c1 = (T *)r.c1 + off;
+    r.c2 = (T *)r.c2 + off;
+    r.dep += i * r.ncol;
+    r.vs = cs.vs[i];
+    r.kappa_c = cs.kappa[i];
+    return i == 0;
+}
+
 // Tile shape of the tiled transport kernels: tx x ty columns marching `chunk`
 // vertical planes.
 struct TileShape {
@@ -110,34 +134,35 @@ hipError_t launch_import_f(int q, int precision, const RunDev &r, bool odd, cons
                            hipStream_t st);
 hipError_t launch_export_f(int q, int precision, const RunDev &r, bool odd, void *dst,
                            hipStream_t st);
-hipError_t launch_transport(int dim, int precision, const RunDev &r, const lbw_launch &l,
-                            hipStream_t st);
-hipError_t launch_transport_tiled(int dim, int precision, const RunDev &r, const lbw_launch &l,
-                                  hipStream_t st);
+hipError_t launch_transport_plain(int dim, int precision, const RunDev &r, hipStream_t st);
+hipError_t launch_transport_tiled(int dim, int precision, const RunDev &r, const ClassSet &cs,
+                                  const lbw_launch &l, hipStream_t st);
 hipError_t launch_s_update(int dim, int precision, const RunDev &r, hipStream_t st);
 // One RK stage (1, 2 or 3) of the tiled transport over the whole grid (runs
 // with a constant settling speed).
 hipError_t launch_one_stage(int dim, int precision, const RunDev &r, const lbw_launch &l,
                             int stage, hipStream_t st);
-// The launch's tile shape for n runs advanced together; fields the caller left
-// at 0 are chosen for those runs' sizes.
 // Whether a run takes the fused transport: 2D, no launch shape set, and a grid
 // small enough.
 bool rk3_fused2d_applies(int dim, const RunDev &r, const lbw_launch &l);
-// The whole transport of a 2D step in one launch: reads C from r.c, writes the
-// result to cout (another buffer) and, where given, the stages to a1 and a2.
-hipError_t launch_rk3_fused2d(int precision, const RunDev &r, void *cout, void *a1, void *a2,
-                              hipStream_t st);
-TileShape resolve_tile_shape(int dim, int precision, const lbw_launch &l, const RunDev *runs, int n);
+// The whole transport of a 2D step in one launch: reads C (of every class) from
+// r.c, writes the result to cout (another buffer) and, where given, the stages
+// to a1 and a2.
+hipError_t launch_rk3_fused2d(int precision, const RunDev &r, const ClassSet &cs, void *cout, void *a1,
+                              void *a2, hipStream_t st);
+// The launch's tile shape for n runs advanced together, or for `classes` size
+// classes of one; fields the caller left at 0 are chosen for their sizes.
+TileShape resolve_tile_shape(int dim, int precision, const lbw_launch &l, const RunDev *runs, int n,
+                             int classes = 1);
 // Tiles (blocks) of one run in that shape, over all vertical chunks.
 int64_t transport_tiles(int dim, const RunDev &r, const TileShape &s);
 hipError_t launch_transport_batched(int dim, int precision, const BatchArgs &b, hipStream_t st);
 // The tiled stages in one unit per dimension, element type and settling form
-// (VSS: a settling speed that depends on S), of the single run r or, when b is
-// not NULL, of the batched entries.  stage 0: all three; 1-3: that one only
-// (single runs).
+// (VSS: a settling speed that depends on S), of the classes cs of the single run
+// r or, when b is not NULL, of the batched entries.  stage 0: all three; 1-3:
+// that one only (single runs).
 template <typename T, int D, bool VSS>
-hipError_t tiled_unit(const RunDev &r, const TileShape &sh, int stage, hipStream_t st,
+hipError_t tiled_unit(const RunDev &r, const ClassSet &cs, const TileShape &sh, int stage, hipStream_t st,
                       const BatchArgs *b);
 // nodes: total nodes of the batch (chooses the cache policy of the
 // population accesses)

@@ -202,9 +202,7 @@ hipError_t launch_s_update(int dim, int precision, const RunDev &r, hipStream_t 
     return hipGetLastError();
 }
 
-hipError_t launch_transport(int dim, int precision, const RunDev &r, const lbw_launch &l,
-                            hipStream_t st) {
-    if (l.variant != 1) return launch_transport_tiled(dim, precision, r, l, st);
+hipError_t launch_transport_plain(int dim, int precision, const RunDev &r, hipStream_t st) {
     if (precision == LBW_FP32_SHIFTED)
         return dim == 2 ? transport_d<float, 2>(r, st) : transport_d<float, 3>(r, st);
     return dim == 2 ? transport_d<double, 2>(r, st) : transport_d<double, 3>(r, st);

@@ -31,14 +31,20 @@ __device__ __forceinline__ int wrap_index(int j, int n) {
 }
 
 template <typename T, int SCHEME, bool VSS, bool FS, int TX, int TY, int NT>
-__global__ void __launch_bounds__(NT) k_rk3_2d(RunDev r, T *__restrict__ cout, T *__restrict__ a1out,
-                                               T *__restrict__ a2out) {
+__global__ void __launch_bounds__(NT) k_rk3_2d(RunDev r, ClassSet cs, T *__restrict__ cout,
+                                               T *__restrict__ a1out, T *__restrict__ a2out) {
     // C on the tile with nine halo cells, stage 1 with six, stage 2 with three;
     // the x velocity on stage 1's rows, the vertical transport velocity on
     // stage 1's columns
     constexpr int RX = TX + 18, RY = TY + 18, PX = TX + 12, PY = TY + 12, QX = TX + 6, QY = TY + 6;
     __shared__ T sC[RY * RX], sU[PY * RX], sW[RY * PX], sA1[PY * PX], sA2[QY * QX];
     __shared__ T sFx[PY * (PX + 1)], sFy[(PY + 1) * PX];
+
+    const int64_t off = (int64_t)blockIdx.z * r.N;      // block z: size class z
+    cout += off;
+    if (a1out) a1out += off;
+    if (a2out) a2out += off;
+    const bool s_entry = select_class<T>(r, cs, (int)blockIdx.z);
 
     const int tid = threadIdx.x;
     const int nx = r.nx, ny = r.ny;
@@ -106,7 +112,7 @@ __global__ void __launch_bounds__(NT) k_rk3_2d(RunDev r, T *__restrict__ cout, T
     // S: forward Euler on the tile's own cells, straight from memory
     if constexpr (FS) {
         const T kaps = (T)r.kappa_s;
-        for (int i = tid; i < TX * TY; i += NT) {
+        for (int i = tid; i < (s_entry ? TX * TY : 0); i += NT) {
             const int x = x0 + i % TX, y = y0 + i / TX;
             if (x >= nx || y >= ny) continue;
             const int k = x + nx * y;
@@ -183,13 +189,13 @@ __global__ void __launch_bounds__(NT) k_rk3_2d(RunDev r, T *__restrict__ cout, T
 }
 
 template <typename T, int SCHEME, int TX, int TY, int NT>
-hipError_t fused_tile(const RunDev &r, void *cout, void *a1, void *a2, hipStream_t st) {
-    const dim3 grid((unsigned)((r.nx + TX - 1) / TX), (unsigned)((r.ny + TY - 1) / TY));
+hipError_t fused_tile(const RunDev &r, const ClassSet &cs, void *cout, void *a1, void *a2, hipStream_t st) {
+    const dim3 grid((unsigned)((r.nx + TX - 1) / TX), (unsigned)((r.ny + TY - 1) / TY), (unsigned)cs.n);
     T *o = (T *)cout, *p = (T *)a1, *q = (T *)a2;
-    if (r.vs_s != 0.0 && r.has_s) k_rk3_2d<T, SCHEME, true, true, TX, TY, NT><<<grid, NT, 0, st>>>(r, o, p, q);
-    else if (r.vs_s != 0.0) k_rk3_2d<T, SCHEME, true, false, TX, TY, NT><<<grid, NT, 0, st>>>(r, o, p, q);
-    else if (r.has_s) k_rk3_2d<T, SCHEME, false, true, TX, TY, NT><<<grid, NT, 0, st>>>(r, o, p, q);
-    else k_rk3_2d<T, SCHEME, false, false, TX, TY, NT><<<grid, NT, 0, st>>>(r, o, p, q);
+    if (r.vs_s != 0.0 && r.has_s) k_rk3_2d<T, SCHEME, true, true, TX, TY, NT><<<grid, NT, 0, st>>>(r, cs, o, p, q);
+    else if (r.vs_s != 0.0) k_rk3_2d<T, SCHEME, true, false, TX, TY, NT><<<grid, NT, 0, st>>>(r, cs, o, p, q);
+    else if (r.has_s) k_rk3_2d<T, SCHEME, false, true, TX, TY, NT><<<grid, NT, 0, st>>>(r, cs, o, p, q);
+    else k_rk3_2d<T, SCHEME, false, false, TX, TY, NT><<<grid, NT, 0, st>>>(r, cs, o, p, q);
     return hipGetLastError();
 }
 
@@ -200,21 +206,21 @@ hipError_t fused_tile(const RunDev &r, void *cout, void *a1, void *a2, hipStream
 // 15.6, 19.6; 256x512 20.9, 19.6, 23.4; 700x1100 78.8, 66.7, 74.5 (32x32 holds
 // 114 KB of LDS there, one block per CU).
 template <typename T, int SCHEME>
-hipError_t fused_scheme(const RunDev &r, void *cout, void *a1, void *a2, hipStream_t st) {
-    auto fits = [&](int tx, int ty) { return (int64_t)((r.nx + tx - 1) / tx) * ((r.ny + ty - 1) / ty) <= 256; };
-    if (fits(16, 16)) return fused_tile<T, SCHEME, 16, 16, 1024>(r, cout, a1, a2, st);
+hipError_t fused_scheme(const RunDev &r, const ClassSet &cs, void *cout, void *a1, void *a2, hipStream_t st) {
+    auto fits = [&](int tx, int ty) { return (int64_t)((r.nx + tx - 1) / tx) * ((r.ny + ty - 1) / ty) * cs.n <= 256; };
+    if (fits(16, 16)) return fused_tile<T, SCHEME, 16, 16, 1024>(r, cs, cout, a1, a2, st);
     if constexpr (sizeof(T) == 4) {
-        if (!fits(32, 16)) return fused_tile<T, SCHEME, 32, 32, 1024>(r, cout, a1, a2, st);
+        if (!fits(32, 16)) return fused_tile<T, SCHEME, 32, 32, 1024>(r, cs, cout, a1, a2, st);
     }
-    return fused_tile<T, SCHEME, 32, 16, 1024>(r, cout, a1, a2, st);
+    return fused_tile<T, SCHEME, 32, 16, 1024>(r, cs, cout, a1, a2, st);
 }
 
 template <typename T>
-hipError_t fused_t(const RunDev &r, void *cout, void *a1, void *a2, hipStream_t st) {
+hipError_t fused_t(const RunDev &r, const ClassSet &cs, void *cout, void *a1, void *a2, hipStream_t st) {
     switch (r.scheme) {
-        case LBW_WENO5: return fused_scheme<T, LBW_WENO5>(r, cout, a1, a2, st);
-        case LBW_WENO3: return fused_scheme<T, LBW_WENO3>(r, cout, a1, a2, st);
-        case LBW_UPWIND1: return fused_scheme<T, LBW_UPWIND1>(r, cout, a1, a2, st);
+        case LBW_WENO5: return fused_scheme<T, LBW_WENO5>(r, cs, cout, a1, a2, st);
+        case LBW_WENO3: return fused_scheme<T, LBW_WENO3>(r, cs, cout, a1, a2, st);
+        case LBW_UPWIND1: return fused_scheme<T, LBW_UPWIND1>(r, cs, cout, a1, a2, st);
     }
     return hipErrorInvalidValue;
 }
@@ -229,13 +235,13 @@ hipError_t fused_t(const RunDev &r, void *cout, void *a1, void *a2, hipStream_t 
 // block row per tile row: 65535 at most.
 bool rk3_fused2d_applies(int dim, const RunDev &r, const lbw_launch &l) {
     return dim == 2 && l.variant == 0 && !l.tile_x && !l.tile_y && !l.tile_rows &&
-           r.N <= (3 << 18) && r.ny <= 65535 * 16;
+           r.N * r.ncls <= (3 << 18) && r.ny <= 65535 * 16;
 }
 
-hipError_t launch_rk3_fused2d(int precision, const RunDev &r, void *cout, void *a1, void *a2,
-                              hipStream_t st) {
-    return precision == LBW_FP32_SHIFTED ? fused_t<float>(r, cout, a1, a2, st)
-                                         : fused_t<double>(r, cout, a1, a2, st);
+hipError_t launch_rk3_fused2d(int precision, const RunDev &r, const ClassSet &cs, void *cout, void *a1,
+                              void *a2, hipStream_t st) {
+    return precision == LBW_FP32_SHIFTED ? fused_t<float>(r, cs, cout, a1, a2, st)
+                                         : fused_t<double>(r, cs, cout, a1, a2, st);
 }
 
 }  // namespace lbw

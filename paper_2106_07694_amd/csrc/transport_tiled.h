@@ -47,14 +47,20 @@ struct TileGeom {
 
 // Position of the block: blocks are dealt round-robin to the 8 XCDs, so the
 // flat index is remapped to give each XCD a contiguous range of tiles whose
-// halos then meet in that XCD's L2.
-__device__ __forceinline__ void block_tile(const TileGeom &g, int &bx, int &by, int &bz) {
-    const int nb = g.gx * g.gy * g.gz;
+// halos then meet in that XCD's L2, the size classes of one tile next to each
+// other (they read the same velocity).
+__device__ __forceinline__ void block_tile(const TileGeom &g, int ncls, int &bx, int &by, int &bz, int &cls) {
+    const int nb = g.gx * g.gy * g.gz * ncls;
     const int b = blockIdx.x;
     int logical = b;
     if ((nb & 7) == 0) {
         const int per = nb >> 3;
         logical = (b & 7) * per + (b >> 3);
+    }
+    cls = 0;
+    if (ncls > 1) {
+        cls = logical % ncls;
+        logical /= ncls;
     }
     bx = logical % g.gx;
     const int t = logical / g.gx;
@@ -560,10 +566,11 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
 }
 
 template <typename T, int D, int SCHEME, int STAGE, int TX, int TY, bool FULL, bool VSS, bool FS = false>
-__global__ void __launch_bounds__(TX *TY) k_stage_tiled(RunDev r, TileGeom g) {
-    int bx, by, bz;
-    block_tile(g, bx, by, bz);
-    stage_tile<T, D, SCHEME, STAGE, TX, TY, FULL, VSS, FS>(r, g, bx, by, bz, true);
+__global__ void __launch_bounds__(TX *TY) k_stage_tiled(RunDev r, ClassSet cs, TileGeom g) {
+    int bx, by, bz, cls;
+    block_tile(g, cs.n, bx, by, bz, cls);
+    const bool s_entry = select_class<T>(r, cs, cs.first + cls);
+    stage_tile<T, D, SCHEME, STAGE, TX, TY, FULL, VSS, FS>(r, g, bx, by, bz, s_entry);
 }
 
 template <int D>
@@ -623,32 +630,44 @@ __global__ void __launch_bounds__(TX *TY) k_stage_batched(const RunDev *__restri
 // (runs with a variable settling speed always take the masked form, which
 // halves the kernels built for them).
 template <typename T, int D, int SCHEME, int STAGE, int TX, int TY, bool VSS, bool FS = false>
-void launch_stage(const RunDev &r, const TileGeom &g, unsigned nb, hipStream_t st) {
+void launch_stage(const RunDev &r, const ClassSet &cs, const TileGeom &g, unsigned nb, hipStream_t st) {
     if constexpr (!VSS) {
         if (g.nx % TX == 0 && (D == 2 || g.ny % TY == 0)) {
-            k_stage_tiled<T, D, SCHEME, STAGE, TX, TY, true, false, FS><<<nb, TX * TY, 0, st>>>(r, g);
+            k_stage_tiled<T, D, SCHEME, STAGE, TX, TY, true, false, FS><<<nb, TX * TY, 0, st>>>(r, cs, g);
             return;
         }
     }
-    k_stage_tiled<T, D, SCHEME, STAGE, TX, TY, false, VSS, FS><<<nb, TX * TY, 0, st>>>(r, g);
+    k_stage_tiled<T, D, SCHEME, STAGE, TX, TY, false, VSS, FS><<<nb, TX * TY, 0, st>>>(r, cs, g);
 }
 
 // Stage 1, carrying the S update when the run has S.
 template <typename T, int D, int SCHEME, int TX, int TY, bool VSS>
-void launch_stage1(const RunDev &r, const TileGeom &g, unsigned nb, hipStream_t st) {
-    if (r.has_s) launch_stage<T, D, SCHEME, 1, TX, TY, VSS, true>(r, g, nb, st);
-    else launch_stage<T, D, SCHEME, 1, TX, TY, VSS, false>(r, g, nb, st);
+void launch_stage1(const RunDev &r, const ClassSet &cs, const TileGeom &g, unsigned nb, hipStream_t st) {
+    if (r.has_s) launch_stage<T, D, SCHEME, 1, TX, TY, VSS, true>(r, cs, g, nb, st);
+    else launch_stage<T, D, SCHEME, 1, TX, TY, VSS, false>(r, cs, g, nb, st);
 }
 
-// The three stages (stage 0) or one of them of a single run.
+// The three stages (stage 0) or one of them of a single run's classes: one
+// launch per stage for all of them, so that they fill the chip together, class
+// by class only where one launch would need 2^32 work-items.
 template <typename T, int D, int SCHEME, int TX, int TY, bool VSS>
-hipError_t stages(const RunDev &r, int chunk, int stage, hipStream_t st) {
+hipError_t stages(const RunDev &r, const ClassSet &cs, int chunk, int stage, hipStream_t st) {
     const TileGeom g = make_geom<D>(r, chunk, TX, TY);
-    const int64_t nb = (int64_t)g.gx * g.gy * g.gz;
+    const int64_t tiles = (int64_t)g.gx * g.gy * g.gz, nb = tiles * cs.n;
+    if (cs.n > 1 && (nb > 0x7fffffff || nb * TX * TY >= ((int64_t)1 << 32))) {
+        hipError_t e = hipSuccess;
+        ClassSet one = cs;
+        one.n = 1;
+        for (int i = 0; i < cs.n && e == hipSuccess; ++i) {
+            one.first = cs.first + i;
+            e = stages<T, D, SCHEME, TX, TY, VSS>(r, one, chunk, stage, st);
+        }
+        return e;
+    }
     if (nb > 0x7fffffff) return hipErrorInvalidValue;
-    if (stage == 0 || stage == 1) launch_stage1<T, D, SCHEME, TX, TY, VSS>(r, g, (unsigned)nb, st);
-    if (stage == 0 || stage == 2) launch_stage<T, D, SCHEME, 2, TX, TY, VSS>(r, g, (unsigned)nb, st);
-    if (stage == 0 || stage == 3) launch_stage<T, D, SCHEME, 3, TX, TY, VSS>(r, g, (unsigned)nb, st);
+    if (stage == 0 || stage == 1) launch_stage1<T, D, SCHEME, TX, TY, VSS>(r, cs, g, (unsigned)nb, st);
+    if (stage == 0 || stage == 2) launch_stage<T, D, SCHEME, 2, TX, TY, VSS>(r, cs, g, (unsigned)nb, st);
+    if (stage == 0 || stage == 3) launch_stage<T, D, SCHEME, 3, TX, TY, VSS>(r, cs, g, (unsigned)nb, st);
     return hipGetLastError();
 }
 
@@ -699,24 +718,24 @@ hipError_t stages_batched(const BatchArgs &a, hipStream_t st) {
 }
 
 template <typename T, int D, int SCHEME, bool VSS>
-hipError_t stages_shape(const RunDev &r, const TileShape &sh, int stage, hipStream_t st,
+hipError_t stages_shape(const RunDev &r, const ClassSet &cs, const TileShape &sh, int stage, hipStream_t st,
                         const BatchArgs *batch) {
     return with_tile<D>(sh, [&](auto tx, auto ty) {
         constexpr int TX = decltype(tx)::value, TY = decltype(ty)::value;
         return batch ? stages_batched<T, D, SCHEME, TX, TY, VSS>(*batch, st)
-                     : stages<T, D, SCHEME, TX, TY, VSS>(r, sh.chunk, stage, st);
+                     : stages<T, D, SCHEME, TX, TY, VSS>(r, cs, sh.chunk, stage, st);
     });
 }
 
 }  // namespace
 
 template <typename T, int D, bool VSS>
-hipError_t tiled_unit(const RunDev &r, const TileShape &sh, int stage, hipStream_t st,
+hipError_t tiled_unit(const RunDev &r, const ClassSet &cs, const TileShape &sh, int stage, hipStream_t st,
                       const BatchArgs *b) {
     switch (r.scheme) {
-        case LBW_WENO5: return stages_shape<T, D, LBW_WENO5, VSS>(r, sh, stage, st, b);
-        case LBW_WENO3: return stages_shape<T, D, LBW_WENO3, VSS>(r, sh, stage, st, b);
-        case LBW_UPWIND1: return stages_shape<T, D, LBW_UPWIND1, VSS>(r, sh, stage, st, b);
+        case LBW_WENO5: return stages_shape<T, D, LBW_WENO5, VSS>(r, cs, sh, stage, st, b);
+        case LBW_WENO3: return stages_shape<T, D, LBW_WENO3, VSS>(r, cs, sh, stage, st, b);
+        case LBW_UPWIND1: return stages_shape<T, D, LBW_UPWIND1, VSS>(r, cs, sh, stage, st, b);
     }
     return hipErrorInvalidValue;
 }

@@ -59,10 +59,11 @@ TileShape default_tile(int dim, int precision, const RunDev *runs, int n) {
 // 64, 528 at 24, 572 at eight.  Full means 16 waves a CU in 2D and the blocks
 // that fit beside each other in 3D (registers: three of 64x8 in single
 // precision, two in double).
-int default_chunk(int dim, int precision, const TileShape &s, const RunDev *runs, int n) {
+int default_chunk(int dim, int precision, const TileShape &s, const RunDev *runs, int n, int classes) {
     int64_t blocks = 0;                 // at one plane per block
     for (int i = 0; i < n; ++i)
         blocks += padded_columns(dim, runs[i], s.tx, s.ty) / (s.tx * s.ty) * planes(dim, runs[i]);
+    blocks *= classes;
     constexpr int64_t cus = 256;
     int64_t full, lo, hi;
     if (dim == 2) {
@@ -85,7 +86,8 @@ int default_chunk(int dim, int precision, const TileShape &s, const RunDev *runs
 // work-items for a run that could launch with 32x8 columns and 64 planes (256
 // and 32 in 2D) in place of the fields left at 0: those are what creation and
 // lbw_set_launch check.
-TileShape resolve_tile_shape(int dim, int precision, const lbw_launch &l, const RunDev *runs, int n) {
+TileShape resolve_tile_shape(int dim, int precision, const lbw_launch &l, const RunDev *runs, int n,
+                             int classes) {
     TileShape s;
     if (l.tile_x || l.tile_rows) {
         s.tx = l.tile_x ? l.tile_x : (dim == 3 ? 32 : 256);
@@ -93,7 +95,7 @@ TileShape resolve_tile_shape(int dim, int precision, const lbw_launch &l, const 
     } else {
         s = default_tile(dim, precision, runs, n);
     }
-    s.chunk = l.tile_y > 0 ? l.tile_y : default_chunk(dim, precision, s, runs, n);
+    s.chunk = l.tile_y > 0 ? l.tile_y : default_chunk(dim, precision, s, runs, n, classes);
     if (n == 1) {
         auto too_many = [&] { return transport_tiles(dim, runs[0], s) * s.tx * s.ty >= ((int64_t)1 << 32); };
         if (!l.tile_x && !l.tile_rows && l.tile_y > 0 && dim == 3 && too_many()) s.tx = 32;
@@ -109,22 +111,22 @@ int64_t transport_tiles(int dim, const RunDev &r, const TileShape &s) {
 
 namespace {
 
-hipError_t tiled_any(int dim, int precision, bool vss, const RunDev &r, const TileShape &sh, int stage,
-                     hipStream_t st, const BatchArgs *b) {
+hipError_t tiled_any(int dim, int precision, bool vss, const RunDev &r, const ClassSet &cs,
+                     const TileShape &sh, int stage, hipStream_t st, const BatchArgs *b) {
     if (precision == LBW_FP32_SHIFTED) {
-        if (dim == 2) return vss ? tiled_unit<float, 2, true>(r, sh, stage, st, b) : tiled_unit<float, 2, false>(r, sh, stage, st, b);
-        return vss ? tiled_unit<float, 3, true>(r, sh, stage, st, b) : tiled_unit<float, 3, false>(r, sh, stage, st, b);
+        if (dim == 2) return vss ? tiled_unit<float, 2, true>(r, cs, sh, stage, st, b) : tiled_unit<float, 2, false>(r, cs, sh, stage, st, b);
+        return vss ? tiled_unit<float, 3, true>(r, cs, sh, stage, st, b) : tiled_unit<float, 3, false>(r, cs, sh, stage, st, b);
     }
-    if (dim == 2) return vss ? tiled_unit<double, 2, true>(r, sh, stage, st, b) : tiled_unit<double, 2, false>(r, sh, stage, st, b);
-    return vss ? tiled_unit<double, 3, true>(r, sh, stage, st, b) : tiled_unit<double, 3, false>(r, sh, stage, st, b);
+    if (dim == 2) return vss ? tiled_unit<double, 2, true>(r, cs, sh, stage, st, b) : tiled_unit<double, 2, false>(r, cs, sh, stage, st, b);
+    return vss ? tiled_unit<double, 3, true>(r, cs, sh, stage, st, b) : tiled_unit<double, 3, false>(r, cs, sh, stage, st, b);
 }
 
 }  // namespace
 
-hipError_t launch_transport_tiled(int dim, int precision, const RunDev &r, const lbw_launch &l,
-                                  hipStream_t st) {
-    const TileShape sh = resolve_tile_shape(dim, precision, l, &r, 1);
-    return tiled_any(dim, precision, r.vs_s != 0.0, r, sh, 0, st, nullptr);
+hipError_t launch_transport_tiled(int dim, int precision, const RunDev &r, const ClassSet &cs,
+                                  const lbw_launch &l, hipStream_t st) {
+    const TileShape sh = resolve_tile_shape(dim, precision, l, &r, 1, cs.n);
+    return tiled_any(dim, precision, r.vs_s != 0.0, r, cs, sh, 0, st, nullptr);
 }
 
 hipError_t launch_one_stage(int dim, int precision, const RunDev &r, const lbw_launch &l,
@@ -133,14 +135,14 @@ hipError_t launch_one_stage(int dim, int precision, const RunDev &r, const lbw_l
     const TileShape sh = resolve_tile_shape(dim, precision, l, &r, 1);
     // one block per tile and chunk, fewer than 2^32 work-items a launch
     if (transport_tiles(dim, r, sh) * sh.tx * sh.ty >= ((int64_t)1 << 32)) return hipErrorInvalidConfiguration;
-    return tiled_any(dim, precision, false, r, sh, stage, st, nullptr);
+    return tiled_any(dim, precision, false, r, ClassSet(), sh, stage, st, nullptr);
 }
 
 hipError_t launch_transport_batched(int dim, int precision, const BatchArgs &b, hipStream_t st) {
     const RunDev &r = b.host_runs[0];
     bool any_var = false, any_const = false;
     for (int i = 0; i < b.nbatch; ++i) (b.host_runs[i].vs_s != 0.0 ? any_var : any_const) = true;
-    if (!any_var || !any_const) return tiled_any(dim, precision, any_var, r, b.shape, 0, st, &b);
+    if (!any_var || !any_const) return tiled_any(dim, precision, any_var, r, ClassSet(), b.shape, 0, st, &b);
     // both settling forms: each stage runs once per form, each kernel over
     // its own entries, so every run takes the kernels it takes alone
     BatchArgs x = b;
@@ -148,7 +150,7 @@ hipError_t launch_transport_batched(int dim, int precision, const BatchArgs &b, 
         x.stage = k;
         for (int form = 0; form < 2; ++form) {
             x.form = form;
-            const hipError_t e = tiled_any(dim, precision, form == 1, r, b.shape, 0, st, &x);
+            const hipError_t e = tiled_any(dim, precision, form == 1, r, ClassSet(), b.shape, 0, st, &x);
             if (e != hipSuccess) return e;
         }
     }

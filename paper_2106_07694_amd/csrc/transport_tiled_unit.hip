@@ -5,6 +5,7 @@
 #include "transport_tiled.h"
 
 namespace lbw {
-template hipError_t tiled_unit<LBW_T, LBW_D, LBW_VSS != 0>(const RunDev &, const TileShape &, int,
-                                                           hipStream_t, const BatchArgs *);
+template hipError_t tiled_unit<LBW_T, LBW_D, LBW_VSS != 0>(const RunDev &, const ClassSet &,
+                                                           const TileShape &, int, hipStream_t,
+                                                           const BatchArgs *);
 }  // namespace lbw
