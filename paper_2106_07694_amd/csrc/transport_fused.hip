@@ -13,7 +13,10 @@
 //
 // The step reads C from r.c and writes the result to another buffer (a
 // neighbouring block still reads the old values for its halo), so the caller
-// alternates two buffers over consecutive steps.  Faces and combinations are
+// alternates two buffers over consecutive steps.  On the smallest grids the
+// block's chain of loads and six barriers bounds it (8 us at 64x128 in double
+// precision); near the upper limit vector issue does (512x1024: 15.7 us, of
+// which 13.5 are its 928 vector instructions per cell).  Faces and combinations are
 // those of the tiled stages, in the same order: the same bits.
 #include "transport_face.h"
 
@@ -62,51 +65,59 @@ __global__ void __launch_bounds__(NT) k_rk3_2d(RunDev r, ClassSet cs, T *__restr
     // stored row of position p (mirrored beyond a wall; rows further out than
     // the three that any cell of the grid reads are clamped into range)
     auto row = [&](int p, bool &ghost) -> int {
-        ghost = false;
+        ghost = walls && (p < 0 || p >= ny);
         if (!walls) return wrap_index(p, ny);
-        if (p < 0) { p = -1 - p; ghost = true; }
-        else if (p >= ny) { p = 2 * ny - 1 - p; ghost = true; }
+        p = p < 0 ? -1 - p : (p >= ny ? 2 * ny - 1 - p : p);
         return min(max(p, 0), ny - 1);
     };
 
-    // stage the inputs, every load issued before the first store to LDS
-    constexpr int NC = RY * RX, NU = PY * RX, NW = RY * PX;
-    constexpr int LC = (NC + NT - 1) / NT, LU = (NU + NT - 1) / NT, LW = (NW + NT - 1) / NT;
-    T pc[LC], pu[LU], pw[LW], ps[VSS ? LW : 1];
-    bool gw[LW];
+    // stage the inputs, every load issued before the first store to LDS; one
+    // position serves C and both velocities (whose regions lie inside C's).
+    // Wide tiles give a wave whole rows and a lane one of their columns, so the
+    // row's address is scalar and the column's is found once: element by
+    // element, the index arithmetic was a quarter of their vector
+    // instructions.  The narrow tile's rows would leave half of the lanes idle
+    // (64x128 in double precision 13.3 against 12.7 us per step)
+    constexpr bool ROWS = RX >= 48;
+    static_assert(!ROWS || RX <= 64, "one lane per staged column");
+    constexpr int WAVES = NT / 64, LOADS = ROWS ? (RY + WAVES - 1) / WAVES : (RY * RX + NT - 1) / NT;
+    auto place = [&](int q, int &ry, int &cx) -> bool {
+        if constexpr (ROWS) {
+            ry = __builtin_amdgcn_readfirstlane(tid >> 6) + q * WAVES;
+            cx = tid & 63;
+            return ry < RY && cx < RX;
+        } else {
+            const int i = tid + q * NT;
+            ry = i / RX;
+            cx = i % RX;
+            return i < RY * RX;
+        }
+    };
+    T pc[LOADS], pu[LOADS], pw[LOADS], ps[VSS ? LOADS : 1], sg[LOADS];
 #pragma unroll
-    for (int q = 0; q < LC; ++q) {
-        const int i = min(tid + q * NT, NC - 1), ry = i / RX, cx = i % RX;
+    for (int q = 0; q < LOADS; ++q) {
+        int ry, cx;
         bool g;
-        pc[q] = c[wrap_index(x0 - 9 + cx, nx) + nx * row(y0 - 9 + ry, g)];
+        place(q, ry, cx);
+        const int64_t at = (int64_t)row(y0 - 9 + min(ry, RY - 1), g) * nx;
+        const uint32_t xoff = (uint32_t)wrap_index(x0 - 9 + min(cx, RX - 1), nx) * (uint32_t)sizeof(T);
+        auto load = [&](const T *p) { return *(const T *)((const char *)(p + at) + xoff); };
+        sg[q] = g ? (T)-1 : (T)1;
+        pc[q] = load(c);
+        pu[q] = load(ux);
+        pw[q] = load(uy);
+        if constexpr (VSS) ps[q] = load(s);
     }
 #pragma unroll
-    for (int q = 0; q < LU; ++q) {
-        const int i = min(tid + q * NT, NU - 1), ry = i / RX, cx = i % RX;
-        bool g;
-        pu[q] = ux[wrap_index(x0 - 9 + cx, nx) + nx * row(y0 - 6 + ry, g)];
-    }
-#pragma unroll
-    for (int q = 0; q < LW; ++q) {
-        const int i = min(tid + q * NT, NW - 1), ry = i / PX, cx = i % PX;
-        const int k = wrap_index(x0 - 6 + cx, nx) + nx * row(y0 - 9 + ry, gw[q]);
-        pw[q] = uy[k];
-        if constexpr (VSS) ps[q] = settle(k);
-    }
-#pragma unroll
-    for (int q = 0; q < LC; ++q) {
-        const int i = tid + q * NT;
-        if (i < NC) sC[i] = pc[q];
-    }
-#pragma unroll
-    for (int q = 0; q < LU; ++q) {
-        const int i = tid + q * NT;
-        if (i < NU) sU[i] = pu[q];
-    }
-#pragma unroll
-    for (int q = 0; q < LW; ++q) {
-        const int i = tid + q * NT;
-        if (i < NW) sW[i] = (gw[q] ? -pw[q] : pw[q]) - (VSS ? ps[q] : vs);
+    for (int q = 0; q < LOADS; ++q) {
+        int ry, cx;
+        if (!place(q, ry, cx)) continue;
+        sC[ry * RX + cx] = pc[q];
+        if (ry >= 3 && ry < RY - 3) sU[(ry - 3) * RX + cx] = pu[q];
+        if (cx >= 3 && cx < RX - 3) {
+            const T fall = VSS ? vs * ((T)1 - (T)r.vs_s * ps[q]) : vs;
+            sW[ry * PX + cx - 3] = sg[q] * pw[q] - fall;
+        }
     }
 
     // S: forward Euler on the tile's own cells, straight from memory
