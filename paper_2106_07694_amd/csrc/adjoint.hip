@@ -422,210 +422,267 @@ __global__ void __launch_bounds__(256) k_adj_gather(AdjDev A) {
 }
 
 // ---------------------------------------------------------------------------
-// 2D: one reversed RK stage in one kernel.  A block owns a TX x TY tile of
-// nodes and keeps everything between the stage's inputs and its per-node
-// results in LDS: the stage input a, the transport velocity and the face
-// adjoints lam with the halos the tile's face stencils reach (wall images
-// already mirrored, with the sign of the vertical velocity flipped); the
-// products of every x face the tile's nodes read (five faces beyond the
-// tile), gathered per node; then the same for the y faces.  Faces are
-// evaluated with the same face_vjp on the same values as the two-kernel form
-// and gathered in the same order, so the results are identical bit for bit;
-// the workspace round trip of the face products disappears, at the price of
-// recomputing the five faces per row and column that neighbouring tiles also
-// need.
+// One reversed RK stage in one kernel.  A block owns a TX x TY x TZ tile of
+// nodes (2D: TZ = 1) and takes the axes one after the other: it stages the
+// stage input, the axis' transport velocity and the face adjoints lam of the
+// tile's lines with the halo the line's face stencils reach (wall images
+// already mirrored, with the sign of the vertical velocity flipped), evaluates
+// every face the tile's nodes read (five beyond the tile on each line) and
+// gathers the products per node.  Faces are evaluated with the same face_vjp
+// on the same values as the two-kernel form and gathered in the same order, so
+// the results are identical bit for bit; the workspace round trip of the face
+// products (6 D values of A and of W per node, written and read) disappears,
+// at the price of the faces neighbouring tiles also evaluate.
+//
+// Vector issue bounds it (2D 512x1024 in single precision: 790 vector
+// instructions per node, 11.7 of a stage's 15 us), so tiles are as large as
+// occupancy allows (2D 64x8 evaluates 2.7 faces per node, 3D 16x4x4 5.8), one
+// node index serves three loads, and positions wrap without remainders.  All the
+// tile's loads are in flight before the first is stored to LDS; LDS holds one
+// axis at a time, and of its products first A, then W (kept in registers
+// meanwhile), so that a CU holds 16 to 32 waves.  us per reverse step: 2D
+// 512x1024 61.5 -> 52 (against the whole set of products in LDS and remainders
+// in the index arithmetic); 3D 64x48x96 81 -> 63 (against the two-kernel form).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int wrap_any(int j, int n) {
-    j %= n;
-    return j < 0 ? j + n : j;
+
+// Stored position of j on a periodic axis, for the at most five cells a line's
+// halo reaches below it and any number above; positions past its fifth cell
+// beyond, which no node of the grid reads, are clamped there.
+__device__ __forceinline__ int wrap_halo(int j, int n) {
+    j = min(j, n + 4);
+    if (n < 5) j %= n;
+    j += j < 0 ? n : 0;
+    return j - (j >= n ? n : 0);
 }
 
-template <typename T, bool SH, int STAGE, int TX, int TY>
-__global__ void __launch_bounds__(256) k_adj_stage2d(AdjDev A, const T *__restrict__ a,
-                                                     const T *__restrict__ lam, T scale) {
-    constexpr int NT = 256, PER = TX * TY / NT;
-    static_assert(TX * TY % NT == 0, "tile must be a multiple of the block");
-    constexpr int HX = TX + 10, LX = TX + 6, NFX = TX + 5;   // x: a/w row, lam row, faces per row
-    constexpr int HY = TY + 10, LY = TY + 6, NFY = TY + 5;   // y: the same per column
-    constexpr int NP = (NFX * TY > NFY * TX) ? NFX * TY : NFY * TX;
-    __shared__ T sAx[TY * HX], sWx[TY * HX], sLx[TY * LX];
-    __shared__ T sAy[HY * TX], sWy[HY * TX], sLy[LY * TX];
-    __shared__ T sPA[6 * NP], sPW[6 * NP];
+template <int TX, int TY, int TZ, int D> struct AdjTile {
+    static constexpr int NODES = TX * TY * TZ;
+    static constexpr int extent(int ax) { return ax == 0 ? TX : (ax == 1 ? TY : TZ); }
+    static constexpr int lines(int ax) { return NODES / extent(ax); }
+    static constexpr int most(int a, int b) { return a > b ? a : b; }
+    // faces of an axis, and values staged for it: a, w and lam on extent + 10
+    // positions of every line
+    static constexpr int faces(int ax) { return (extent(ax) + 5) * lines(ax); }
+    static constexpr int staged(int ax) { return 3 * (extent(ax) + 10) * lines(ax); }
+    static constexpr int max_faces = most(faces(0), most(faces(1), D == 3 ? faces(2) : 0));
+    static constexpr int max_staged = most(staged(0), most(staged(1), D == 3 ? staged(2) : 0));
+};
+
+template <int Q, typename T, bool SH, int STAGE, int TX, int TY, int TZ, int NT, int BLOCKS>
+__global__ void __launch_bounds__(NT, BLOCKS) k_adj_stage(AdjDev A, const T *__restrict__ a,
+                                                          const T *__restrict__ lam, T scale) {
+    constexpr int D = Lattice<Q>::D;
+    using G = AdjTile<TX, TY, TZ, D>;
+    constexpr int PER = G::NODES / NT, NP = G::max_faces;
+    static_assert(G::NODES % NT == 0, "tile must be a multiple of the block");
+    __shared__ T sS[G::max_staged], sP[6 * NP];
 
     const RunDev &r = A.r;
-    const int nx = r.nx, ny = r.ny;
-    const int x0 = blockIdx.x * TX, y0 = blockIdx.y * TY;
+    const int nx = r.nx, ny = r.ny, nz = D == 3 ? r.nz : 1;
+    const int gx = (nx + TX - 1) / TX, gy = (ny + TY - 1) / TY;
+    // blocks are dealt round-robin to the 8 XCDs: each takes a contiguous
+    // range of tiles, whose halos then meet in its L2
+    const int nb = (int)gridDim.x;
+    int tile = (int)blockIdx.x;
+    if ((nb & 7) == 0) tile = (tile & 7) * (nb >> 3) + (tile >> 3);
+    const int x0 = tile % gx * TX, y0 = tile / gx % gy * TY, z0 = D == 3 ? tile / gx / gy * TZ : 0;
     const int tid = threadIdx.x;
     const bool walls = !r.vper;
     const T *u = (const T *)(A.frozen ? r.u : A.u);
-    const T *ux = u, *uy = u + r.N;
     const T vs = (T)r.vs, kap = (T)r.kappa_c, eps = (T)r.eps;
-    // vertical position p of a stencil or lam row -> stored row (mirrored
-    // beyond walls; rows no face of the tile reads are clamped into range)
-    auto vrow = [&](int p, bool &ghost) {
+    const int64_t plane = (int64_t)nx * ny;
+
+    auto vertical = [](auto ax) { return decltype(ax)::value == D - 1; };
+    auto origin = [&](auto ax) { return decltype(ax)::value == 0 ? x0 : (decltype(ax)::value == 1 ? y0 : z0); };
+    auto length = [&](auto ax) { return decltype(ax)::value == 0 ? nx : (decltype(ax)::value == 1 ? ny : nz); };
+    // node at position p of line `line` of an axis (mirrored beyond a wall;
+    // rows no face of the tile reads are clamped into range)
+    auto node_at = [&](auto ax, int line, int p, bool &ghost) -> int64_t {
+        constexpr int AX = decltype(ax)::value;
+        const int n = length(ax);
         ghost = false;
-        if (!walls) return wrap_any(p, ny);
-        if (p < 0) { p = -1 - p; ghost = true; }
-        else if (p >= ny) { p = 2 * ny - 1 - p; ghost = true; }
-        return p < 0 ? 0 : (p >= ny ? ny - 1 : p);
+        if (vertical(ax) && walls) {
+            if (p < 0) { p = -1 - p; ghost = true; }
+            else if (p >= n) { p = 2 * n - 1 - p; ghost = true; }
+            p = min(max(p, 0), n - 1);
+        } else {
+            p = wrap_halo(p, n);
+        }
+        const int l0 = line % (AX == 0 ? TY : TX), l1 = line / (AX == 0 ? TY : TX);
+        const int x = AX == 0 ? p : min(x0 + l0, nx - 1);
+        const int y = AX == 1 ? p : min(y0 + (AX == 0 ? l0 : l1), ny - 1);
+        if constexpr (D == 2) return (int64_t)x + (int64_t)nx * y;
+        const int z = AX == 2 ? p : min(z0 + l1, nz - 1);
+        return (int64_t)(x + nx * y) + plane * z;
+    };
+    // element i of an array of `len` positions per line: x lines are contiguous,
+    // the others interleaved (lanes run along x)
+    auto split = [](auto ax, int i, int len, int &line, int &c) {
+        constexpr int AX = decltype(ax)::value;
+        if constexpr (AX == 0) { line = i / len; c = i % len; }
+        else { line = i % G::lines(AX); c = i / G::lines(AX); }
     };
 
-    // stage the inputs.  Every slot is loaded into registers first,
-    // unconditionally (a spare slot repeats the last entry of its array), so
-    // all of the tile's loads are in flight together; a loop that stored
-    // each load to LDS before issuing the next waited for every load in turn
-    constexpr int N1 = TY * HX, N2 = TY * LX, N3 = HY * TX, N4 = LY * TX;
-    constexpr int S1 = (N1 + NT - 1) / NT, S2 = (N2 + NT - 1) / NT, S3 = (N3 + NT - 1) / NT,
-                  S4 = (N4 + NT - 1) / NT;
-    T pA1[S1], pW1[S1], pL2[S2], pA3[S3], pW3[S3], pL4[S4];
-    bool g3[S3];
+    // load every axis' values into registers, unconditionally (a spare slot
+    // repeats the last entry of its array).  One node index serves a, w and lam
+    // (whose line starts two positions in)
+    auto load = [&](auto ax, T *pa, T *pw, T *pl) {
+        constexpr int AX = decltype(ax)::value, NL = G::lines(AX), HL = G::extent(AX) + 10;
+        const int o = origin(ax);
+        const T *ud = u + (int64_t)AX * r.N;
 #pragma unroll
-    for (int q = 0; q < S1; ++q) {
-        const int i = min(tid + q * NT, N1 - 1);
-        const int ly = i / HX, c = i % HX;
-        const int gy = min(y0 + ly, ny - 1);
-        const int64_t k = (int64_t)wrap_any(x0 - 5 + c, nx) + (int64_t)nx * gy;
-        pA1[q] = a[k];
-        pW1[q] = ux[k];
-    }
+        for (int q = 0; q < (HL * NL + NT - 1) / NT; ++q) {
+            int line, c;
+            bool g;
+            split(ax, min(tid + q * NT, HL * NL - 1), HL, line, c);
+            const int64_t k = node_at(ax, line, o - 5 + c, g);
+            pa[q] = a[k];
+            const T w = ud[k];
+            pw[q] = vertical(ax) ? (g ? -w : w) - vs : w;
+            pl[q] = lam[k];
+        }
+    };
+    auto publish = [&](auto ax, const T *pa, const T *pw, const T *pl) {
+        constexpr int AX = decltype(ax)::value, NL = G::lines(AX), HL = G::extent(AX) + 10, NH = HL * NL;
 #pragma unroll
-    for (int q = 0; q < S2; ++q) {
-        const int i = min(tid + q * NT, N2 - 1);
-        const int ly = i / LX, c = i % LX;
-        const int gy = min(y0 + ly, ny - 1);
-        pL2[q] = lam[(int64_t)wrap_any(x0 - 3 + c, nx) + (int64_t)nx * gy];
-    }
-#pragma unroll
-    for (int q = 0; q < S3; ++q) {
-        const int i = min(tid + q * NT, N3 - 1);
-        const int ry = i / TX, lx = i % TX;
-        const int gy = vrow(y0 - 5 + ry, g3[q]);
-        const int64_t k = (int64_t)wrap_any(x0 + lx, nx) + (int64_t)nx * gy;
-        pA3[q] = a[k];
-        pW3[q] = uy[k];
-    }
-#pragma unroll
-    for (int q = 0; q < S4; ++q) {
-        const int i = min(tid + q * NT, N4 - 1);
-        const int ry = i / TX, lx = i % TX;
-        bool ghost;
-        const int gy = vrow(y0 - 3 + ry, ghost);
-        pL4[q] = lam[(int64_t)wrap_any(x0 + lx, nx) + (int64_t)nx * gy];
-    }
-#pragma unroll
-    for (int q = 0; q < S1; ++q) {
-        const int i = tid + q * NT;
-        if (i < N1) { sAx[i] = pA1[q]; sWx[i] = pW1[q]; }
-    }
-#pragma unroll
-    for (int q = 0; q < S2; ++q) {
-        const int i = tid + q * NT;
-        if (i < N2) sLx[i] = pL2[q];
-    }
-#pragma unroll
-    for (int q = 0; q < S3; ++q) {
-        const int i = tid + q * NT;
-        if (i < N3) { sAy[i] = pA3[q]; sWy[i] = (g3[q] ? -pW3[q] : pW3[q]) - vs; }
-    }
-#pragma unroll
-    for (int q = 0; q < S4; ++q) {
-        const int i = tid + q * NT;
-        if (i < N4) sLy[i] = pL4[q];
-    }
-    __syncthreads();
+        for (int q = 0; q < (NH + NT - 1) / NT; ++q) {
+            const int i = tid + q * NT;
+            if (i < NH) {
+                sS[i] = pa[q];
+                sS[NH + i] = pw[q];
+                sS[2 * NH + i] = pl[q];
+            }
+        }
+    };
 
-    // x faces j = x0 - 3 + i of every tile row (the x axis is periodic)
-    for (int f = tid; f < NFX * TY; f += NT) {
-        const int ly = f / NFX, i = f % NFX;
-        T av[6], wv[6];
-#pragma unroll
-        for (int q = 0; q < 6; ++q) {
-            av[q] = sAx[ly * HX + i + q];
-            wv[q] = sWx[ly * HX + i + q];
-        }
-        const T pb = scale * (sLx[ly * LX + i + 1] - sLx[ly * LX + i]);
-        T fa6[6], fw6[6];
-        face_vjp<T>(av, wv, pb, kap, eps, fa6, fw6);
-#pragma unroll
-        for (int q = 0; q < 6; ++q) {
-            sPA[q * NP + f] = fa6[q];
-            sPW[q * NP + f] = fw6[q];
-        }
-    }
-    __syncthreads();
-    T abar[PER], ubx[PER], uby[PER];
+    T abar[PER], ubs[PER][3];
     double vsp[PER];
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
-        const int node = tid + e * NT, lx = node % TX, ly = node / TX;
         abar[e] = 0;
-        ubx[e] = 0;
-        uby[e] = 0;
+        ubs[e][0] = ubs[e][1] = ubs[e][2] = 0;
         vsp[e] = 0.0;
-#pragma unroll
-        for (int q = 0; q < 6; ++q) {            // face x - q + 2 reads this node at slot q
-            const int f = ly * NFX + lx + 5 - q;
-            abar[e] += sPA[q * NP + f];
-            ubx[e] += sPW[q * NP + f];
-        }
     }
-    __syncthreads();
+    auto coords_of = [&](int e, int &lx, int &ly, int &lz) {
+        const int node = tid + e * NT;
+        lx = node % TX;
+        ly = node / TX % TY;
+        lz = node / (TX * TY);
+    };
+    // nodes of the grid only: for a row beyond the top of a ragged tile the
+    // image above the wall could name a face outside the tile's range.  For a
+    // grid node every face it reads lies in [o - 3, o + extent + 1]: its own
+    // faces m - 3 .. m + 2, the bottom images (faces 0, 1, read only when
+    // m <= 1, so o = 0) and the top images (faces >= n - 3 >= m - 2, read only
+    // when m >= n - 3)
+    auto in_grid = [&](int lx, int ly, int lz) { return x0 + lx < nx && y0 + ly < ny && z0 + lz < nz; };
 
-    // y faces j = y0 - 3 + i of every tile column (faces exist for
-    // 0 <= j <= ny - 2 with walls; periodic positions wrap)
-    for (int f = tid; f < NFY * TX; f += NT) {
-        const int iy = f / TX, lx = f % TX;
-        const int j = y0 - 3 + iy;
-        if (walls && (j < 0 || j > ny - 2)) continue;   // never gathered
-        T av[6], wv[6];
+    // the faces of one axis and their gather; `then` runs once the staged
+    // values are used up (the next axis' values take their place)
+    auto sweep = [&](auto ax, auto &&then) {
+        constexpr int AX = decltype(ax)::value, TD = G::extent(AX), NL = G::lines(AX), HL = TD + 10,
+                      NF = TD + 5, NH = HL * NL, ROUNDS = (NF * NL + NT - 1) / NT;
+        constexpr int SI = AX == 0 ? 1 : NL;                  // stride between positions of a line
+        const int o = origin(ax), n = length(ax);
+        const bool wall_ax = vertical(ax) && walls;
+        T fw[ROUNDS][6];
 #pragma unroll
-        for (int q = 0; q < 6; ++q) {
-            av[q] = sAy[(iy + q) * TX + lx];
-            wv[q] = sWy[(iy + q) * TX + lx];
-        }
-        const T pb = scale * (sLy[(iy + 1) * TX + lx] - sLy[iy * TX + lx]);
-        T fa6[6], fw6[6];
-        face_vjp<T>(av, wv, pb, kap, eps, fa6, fw6);
+        for (int q = 0; q < ROUNDS; ++q) {
+            const int f = tid + q * NT;
+            int line, i;
+            split(ax, f, NF, line, i);
+            const int j = o - 3 + i;                          // with walls faces exist for 0 <= j <= n - 2
+            if (f >= NF * NL || (wall_ax && (j < 0 || j > n - 2))) continue;   // else never gathered
+            const T *pa = sS + (AX == 0 ? line * HL + i : i * NL + line), *pw = pa + NH, *pl = pw + NH;
+            T av[6], wv[6], fa[6];
 #pragma unroll
-        for (int q = 0; q < 6; ++q) {
-            sPA[q * NP + f] = fa6[q];
-            sPW[q * NP + f] = fw6[q];
+            for (int s = 0; s < 6; ++s) {
+                av[s] = pa[s * SI];
+                wv[s] = pw[s * SI];
+            }
+            const T pb = scale * (pl[3 * SI] - pl[2 * SI]);
+            face_vjp<T>(av, wv, pb, kap, eps, fa, fw[q]);
+#pragma unroll
+            for (int s = 0; s < 6; ++s) sP[s * NP + f] = fa[s];
         }
-    }
+        __syncthreads();
+        // wall images reach only rows m <= 1 (the image -1 - m feeds faces 0
+        // and 1) and m >= n - 2 (the image 2 n - 1 - m feeds faces n - 3 and
+        // n - 2); tiles clear of both take the node itself only (the same sum:
+        // the skipped images add nothing)
+        const int nimg = (wall_ax && (o < 2 || o + TD > n - 2)) ? 3 : 1;
+        auto gather = [&](auto &&add) {
+#pragma unroll
+            for (int e = 0; e < PER; ++e) {
+                int lx, ly, lz;
+                coords_of(e, lx, ly, lz);
+                if (!in_grid(lx, ly, lz)) continue;
+                const int l = AX == 0 ? lx : (AX == 1 ? ly : lz), m = o + l;
+                const int line = AX == 0 ? ly + TY * lz : (AX == 1 ? lx + TX * lz : lx + TX * ly);
+                for (int im = 0; im < nimg; ++im) {
+                    const int p = im == 0 ? m : (im == 1 ? -1 - m : 2 * n - 1 - m);
+#pragma unroll
+                    for (int s = 0; s < 6; ++s) {
+                        const int jf = p - s + 2;             // face whose slot s reads position p
+                        if (wall_ax && (jf < 0 || jf > n - 2)) continue;
+                        const int i = jf - (o - 3);
+                        add(e, im != 0, sP[s * NP + (AX == 0 ? line * NF + i : i * NL + line)]);
+                    }
+                }
+            }
+        };
+        gather([&](int e, bool, T p) { abar[e] += p; });
+        then();
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < ROUNDS; ++q) {
+            const int f = tid + q * NT;
+            if (f >= NF * NL) continue;
+#pragma unroll
+            for (int s = 0; s < 6; ++s) sP[s * NP + f] = fw[q][s];
+        }
+        __syncthreads();
+        gather([&](int e, bool ghost, T p) {
+            if constexpr (AX == D - 1) {
+                ubs[e][AX] += ghost ? -p : p;
+                vsp[e] -= (double)p;
+            } else {
+                ubs[e][AX] += p;
+            }
+        });
+    };
+
+    using std::integral_constant;
+    constexpr integral_constant<int, 0> X{};
+    constexpr integral_constant<int, 1> Y{};
+    constexpr integral_constant<int, 2> Z{};
+    auto count = [](int v) constexpr { return (v + NT - 1) / NT; };
+    T ax_a[count((TX + 10) * G::lines(0))], ax_w[count((TX + 10) * G::lines(0))], ax_l[count((TX + 10) * G::lines(0))];
+    T ay_a[count((TY + 10) * G::lines(1))], ay_w[count((TY + 10) * G::lines(1))], ay_l[count((TY + 10) * G::lines(1))];
+    constexpr int LZ = D == 3 ? G::lines(2) : 1;
+    T az_a[count((TZ + 10) * LZ)], az_w[count((TZ + 10) * LZ)], az_l[count((TZ + 10) * LZ)];
+    load(X, ax_a, ax_w, ax_l);
+    load(Y, ay_a, ay_w, ay_l);
+    if constexpr (D == 3) load(Z, az_a, az_w, az_l);
+    publish(X, ax_a, ax_w, ax_l);
     __syncthreads();
+    sweep(X, [&] { publish(Y, ay_a, ay_w, ay_l); });
+    __syncthreads();
+    if constexpr (D == 3) {
+        sweep(Y, [&] { publish(Z, az_a, az_w, az_l); });
+        __syncthreads();
+        sweep(Z, [] {});
+    } else {
+        sweep(Y, [] {});
+    }
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
-        const int node = tid + e * NT, lx = node % TX, ly = node / TX;
-        const int m = y0 + ly;
-        // only nodes of the grid gather: for a row beyond the top of a ragged
-        // tile the image above the wall could name a face outside the tile's
-        // range.  For a grid node every face it reads lies in [y0 - 3, y0 + TY + 1]:
-        // its own faces m - 3 .. m + 2, the bottom images (faces 0, 1, read only
-        // when m <= 1, so y0 = 0) and the top images (faces >= ny - 3 >= m - 2,
-        // read only when m >= ny - 3).
-        if (x0 + lx >= nx || m >= ny) continue;
-        // wall images reach only rows m <= 1 (the image -1 - m feeds faces 0
-        // and 1) and m >= ny - 2 (the image 2 ny - 1 - m feeds faces ny - 3
-        // and ny - 2); tiles clear of both take the node itself only (the
-        // same sum: the skipped images add nothing)
-        const int nimg = (walls && (y0 < 2 || y0 + TY > ny - 2)) ? 3 : 1;
-        for (int im = 0; im < nimg; ++im) {
-            const int p = im == 0 ? m : (im == 1 ? -1 - m : 2 * ny - 1 - m);
-            const bool ghost = im != 0;
-#pragma unroll
-            for (int q = 0; q < 6; ++q) {
-                const int jf = p - q + 2;        // face whose slot q reads position p
-                if (walls && (jf < 0 || jf > ny - 2)) continue;
-                const int f = (jf - (y0 - 3)) * TX + lx;
-                abar[e] += sPA[q * NP + f];
-                const T wb = sPW[q * NP + f];
-                uby[e] += ghost ? -wb : wb;
-                vsp[e] -= (double)wb;
-            }
-        }
-        const int64_t k = (int64_t)(x0 + lx) + (int64_t)nx * m;
-        const T ubs[3] = {ubx[e], uby[e], (T)0};
-        gather_finish<9, T, SH, STAGE>(A, k, x0 + lx, m, 0, abar[e], ubs, vsp[e]);
+        int lx, ly, lz;
+        coords_of(e, lx, ly, lz);
+        if (!in_grid(lx, ly, lz)) continue;
+        const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
+        const int64_t k = D == 2 ? (int64_t)x + (int64_t)nx * y : (int64_t)(x + nx * y) + plane * z;
+        gather_finish<Q, T, SH, STAGE>(A, k, x, y, z, abar[e], ubs[e], vsp[e]);
     }
 }
 
@@ -686,17 +743,19 @@ hipError_t adjoint_t(const AdjDev &A, const lbw_launch &l, hipStream_t st) {
         if (e == hipSuccess) e = launch_one_stage(D, prec, fr, lt, 2, st);
         if (e != hipSuccess) return e;
     }
-    // the fused 2D form launches one block row per TY grid rows; a launch
-    // takes at most 65535 block rows, so taller runs take the two-kernel form
-    // (the same sums in the same order: the same bits)
-    constexpr int TX = sizeof(T) == 4 ? 32 : 16, TY = sizeof(T) == 4 ? 8 : 16;
-    const int64_t block_rows = ((int64_t)A.r.ny + TY - 1) / TY;
-    if (D == 2 && l.variant != 1 && block_rows <= 65535) {
-        // one kernel per reversed stage, face products kept in LDS
-        const dim3 tg((unsigned)((A.r.nx + TX - 1) / TX), (unsigned)block_rows);
-        k_adj_stage2d<T, SH, 3, TX, TY><<<tg, 256, 0, st>>>(A, (const T *)A.a2, (const T *)A.cbar_next, (T)(2.0 / 3.0));
-        k_adj_stage2d<T, SH, 2, TX, TY><<<tg, 256, 0, st>>>(A, (const T *)A.a1, (const T *)A.abar2, (T)0.25);
-        k_adj_stage2d<T, SH, 1, TX, TY><<<tg, 256, 0, st>>>(A, (const T *)A.c_n, (const T *)A.abar1, (T)1);
+    // one kernel per reversed stage, unless its launch would need 2^32
+    // work-items (then, and with variant 1, the two-kernel form: the same sums
+    // in the same order, the same bits)
+    constexpr bool f32 = sizeof(T) == 4;
+    constexpr int TX = D == 2 ? (f32 ? 64 : 32) : 16, TY = D == 2 ? 8 : 4, TZ = D == 2 ? 1 : 4;
+    constexpr int NT = D == 2 && f32 ? 512 : 256, BLOCKS = D == 2 ? 4 : (f32 ? 5 : 3);
+    const int64_t tiles = (int64_t)((A.r.nx + TX - 1) / TX) * ((A.r.ny + TY - 1) / TY) *
+                          (D == 3 ? (A.r.nz + TZ - 1) / TZ : 1);
+    if (l.variant != 1 && tiles * NT < ((int64_t)1 << 32)) {
+        const dim3 tg((unsigned)tiles);
+        k_adj_stage<Q, T, SH, 3, TX, TY, TZ, NT, BLOCKS><<<tg, NT, 0, st>>>(A, (const T *)A.a2, (const T *)A.cbar_next, (T)(2.0 / 3.0));
+        k_adj_stage<Q, T, SH, 2, TX, TY, TZ, NT, BLOCKS><<<tg, NT, 0, st>>>(A, (const T *)A.a1, (const T *)A.abar2, (T)0.25);
+        k_adj_stage<Q, T, SH, 1, TX, TY, TZ, NT, BLOCKS><<<tg, NT, 0, st>>>(A, (const T *)A.c_n, (const T *)A.abar1, (T)1);
     } else {
         k_adj_face<T, D><<<grid, block, 0, st>>>(A, (const T *)A.a2, (const T *)A.cbar_next, (T)(2.0 / 3.0));
         k_adj_gather<Q, T, SH, 3><<<grid, block, 0, st>>>(A);
