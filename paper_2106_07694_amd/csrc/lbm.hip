@@ -62,12 +62,118 @@ __device__ __forceinline__ void collide_stream_node(const RunDev &r, int64_t k) 
     }
 }
 
+// The same for populations that stay in the caches (at most kStreamingBytes,
+// so 2^32 bytes are never reached): a lane's addresses are 32-bit byte offsets
+// from scalar bases, and the odd half finds its neighbours from one step per
+// axis (the lateral wrap and the walls resolved once per node) instead of a
+// 64-bit index per direction and side.  Vector issue bounds the odd half there
+// (3D: 927 vector instructions a node, here 582; even half 435 and 417).  Mean
+// of the pair, plain and this, us: 64x48x96 14.3, 11.1; 97x63x130 30.1, 26.1;
+// 1024x2048 33.9, 33.1; 64x128 in double precision 7.3, 6.7.  Streamed from HBM
+// the plain form's accesses are the faster ones (256x256x512 971 against 1040,
+// a sweep of 30 runs 132 against 145), so such runs keep it.
+template <int Q, typename T, bool SH, bool ODD>
+__device__ __forceinline__ void collide_stream_node32(const RunDev &r, uint32_t k) {
+    using L = Lattice<Q>;
+    constexpr int D = L::D;
+    constexpr uint32_t ES = sizeof(T);
+    const uint32_t N = (uint32_t)r.N, kb = k * ES;
+    // value at byte offset `off` of slot i (scalar base), or of the whole array
+    auto slot = [&](int i) { return (char *)r.f + (uint64_t)i * ((uint64_t)N * ES); };
+    auto ref = [](char *base, uint32_t off) -> T * { return (T *)(base + off); };
+
+    // offsets of the nodes one step down (0) and up (1) each axis, in bytes
+    // relative to this node (modulo 2^32), and which walls they lie beyond
+    uint32_t step[3][2] = {};
+    bool low = false, high = false;
+    if constexpr (ODD) {
+        const uint32_t nx = r.nx, ny = r.ny;
+        const uint32_t row = k / nx, x = k - row * nx;
+        const uint32_t z = D == 3 ? row / ny : 0, y = D == 3 ? row - z * ny : row;
+        step[0][0] = (x == 0 ? nx - 1 : (uint32_t)-1) * ES;
+        step[0][1] = (x == nx - 1 ? 1 - nx : 1u) * ES;
+        const uint32_t rb = nx * ES;
+        step[1][0] = y == 0 ? (ny - 1) * rb : 0u - rb;
+        step[1][1] = y == ny - 1 ? (1 - ny) * rb : rb;
+        if constexpr (D == 3) {
+            const uint32_t nz = r.nz, pb = rb * ny;
+            step[2][0] = z == 0 ? (nz - 1) * pb : 0u - pb;
+            step[2][1] = z == nz - 1 ? (1 - nz) * pb : pb;
+        }
+        const uint32_t v = D == 2 ? y : z, nv = D == 2 ? ny : (uint32_t)r.nz;
+        low = !r.vper && v == 0;
+        high = !r.vper && v == nv - 1;
+    }
+    // byte offset of the node at k + s c_i (s = +1 or -1)
+    auto moved = [&](int i, int s) -> uint32_t {
+        uint32_t o = kb;
+        if (L::cx[i]) o += step[0][s * L::cx[i] > 0];
+        if (L::cy[i]) o += step[1][s * L::cy[i] > 0];
+        if (D == 3 && L::cz[i]) o += step[2][s * L::cz[i] > 0];
+        return o;
+    };
+    // whether k + s c_i lies beyond a wall
+    auto beyond = [&](int i, int s) -> bool {
+        const int cv = s * (D == 2 ? L::cy[i] : L::cz[i]);
+        return cv < 0 ? low : (cv > 0 ? high : false);
+    };
+    const bool lid = ODD && (r.utop[0] != 0.0 || r.utop[1] != 0.0 || r.utop[2] != 0.0);
+
+    T fi[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        const int cv = D == 2 ? L::cy[i] : L::cz[i];
+        if (!ODD) {
+            fi[i] = *ref(slot(i), kb);
+        } else if (cv == 0) {
+            fi[i] = *ref(slot(L::opp[i]), moved(i, -1));
+        } else {
+            const uint32_t off = beyond(i, -1) ? (uint32_t)i * (N * ES) + kb
+                                               : (uint32_t)L::opp[i] * (N * ES) + moved(i, -1);
+            fi[i] = *ref((char *)r.f, off);
+            // reflected at the moving top wall
+            if (cv < 0 && lid) fi[i] = high ? fi[i] + (T)lid_term<Q>(r, i) : fi[i];
+        }
+    }
+
+    T F[3], uu[3], rho;
+    lbm_force<D, T>(r, (const T *)r.c, (const T *)r.s, k, F);
+    lbm_collide<Q, T, SH>(r, fi, F, rho, uu);
+    char *uo = (char *)r.u;
+    *ref(uo, kb) = uu[0];
+    *ref(uo + (uint64_t)N * ES, kb) = uu[1];
+    if (D == 3) *ref(uo + 2 * ((uint64_t)N * ES), kb) = uu[2];
+    if (r.rho) *ref((char *)r.rho, kb) = rho;
+
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        const int cv = D == 2 ? L::cy[i] : L::cz[i];
+        if (!ODD) {
+            *ref(slot(L::opp[i]), kb) = fi[i];
+        } else if (cv == 0) {
+            *ref(slot(i), moved(i, 1)) = fi[i];
+        } else {
+            T v = fi[i];
+            if (cv > 0 && lid) v = high ? v - (T)lid_term<Q>(r, i) : v;
+            const uint32_t off = beyond(i, 1) ? (uint32_t)L::opp[i] * (N * ES) + kb
+                                              : (uint32_t)i * (N * ES) + moved(i, 1);
+            *ref((char *)r.f, off) = v;
+        }
+    }
+}
+
+template <int Q, typename T, bool SH, bool ODD, bool NT>
+__device__ __forceinline__ void collide_stream_at(const RunDev &r, int64_t k) {
+    if constexpr (NT) collide_stream_node<Q, T, SH, ODD, true>(r, k);
+    else collide_stream_node32<Q, T, SH, ODD>(r, (uint32_t)k);
+}
+
 // Every node of one run, one per thread.
 template <int Q, typename T, bool SH, bool ODD, bool NT>
 __global__ void __launch_bounds__(1024) k_collide_stream(RunDev r) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= r.N) return;
-    collide_stream_node<Q, T, SH, ODD, NT>(r, k);
+    collide_stream_at<Q, T, SH, ODD, NT>(r, k);
 }
 
 // Batched form: a persistent grid walks the thread blocks of every run;
@@ -84,7 +190,7 @@ __global__ void __launch_bounds__(1024) k_collide_stream_batched(const RunDev *_
         RunDev r = runs[b];
         if (sflip) { void *t = r.s; r.s = r.s2; r.s2 = t; }
         const int64_t k = (int64_t)(w - blk_start[b]) * blockDim.x + threadIdx.x;
-        if (k < r.N) collide_stream_node<Q, T, SH, ODD, NT>(r, k);
+        if (k < r.N) collide_stream_at<Q, T, SH, ODD, NT>(r, k);
     }
 }
 
