@@ -16,6 +16,8 @@
 // move exactly 2Q values per node: the traffic of a two-lattice scheme at
 // half the footprint.  The node velocity u^n is written for the transport
 // kernels, which use it frozen over the three RK stages.
+#include <algorithm>
+
 #include "lbm_device.h"
 
 namespace lbw {
@@ -255,16 +257,29 @@ inline unsigned blocks_for(int64_t n, int block) { return (unsigned)((n + block 
 constexpr size_t kStreamingBytes = (size_t)192 << 20;
 inline bool streaming_populations(size_t bytes) { return bytes > kStreamingBytes; }
 
+// LDS the even half reserves (and does not use) when it streams: all its
+// accesses are aligned, and HBM serves them fastest from 16 to 20 waves a CU;
+// with more, the 2Q streams of the waves in flight interleave more finely
+// (256x256x512, blocks of 256, mean of the pair: 987 us at 24 waves a CU, 966
+// at 20, 965 at 16, 1430 at 12).  The odd half wants its waves (957 us at 28,
+// 1002 at 20), and so do runs that stay in the caches.
+inline size_t occupancy_lds(bool odd, bool nt, int block) {
+    if (odd || !nt) return 0;
+    const size_t blocks = std::max(1, 20 * 64 / block);
+    return std::min((size_t)64 << 10, ((size_t)160 << 10) / blocks & ~(size_t)511);
+}
+
 template <int Q, typename T, bool SH>
 hipError_t collide_stream_t(const RunDev &r, bool odd, int block, hipStream_t st) {
     const bool nt = streaming_populations((size_t)Q * sizeof(T) * (size_t)r.N);
     const dim3 grid(blocks_for(r.N, block));
+    const size_t lds = occupancy_lds(odd, nt, block);
     if (odd) {
-        if (nt) k_collide_stream<Q, T, SH, true, true><<<grid, block, 0, st>>>(r);
-        else k_collide_stream<Q, T, SH, true, false><<<grid, block, 0, st>>>(r);
+        if (nt) k_collide_stream<Q, T, SH, true, true><<<grid, block, lds, st>>>(r);
+        else k_collide_stream<Q, T, SH, true, false><<<grid, block, lds, st>>>(r);
     } else {
-        if (nt) k_collide_stream<Q, T, SH, false, true><<<grid, block, 0, st>>>(r);
-        else k_collide_stream<Q, T, SH, false, false><<<grid, block, 0, st>>>(r);
+        if (nt) k_collide_stream<Q, T, SH, false, true><<<grid, block, lds, st>>>(r);
+        else k_collide_stream<Q, T, SH, false, false><<<grid, block, lds, st>>>(r);
     }
     return hipGetLastError();
 }
