@@ -176,12 +176,17 @@ hipError_t launch_adjoint(int q, int precision, const RunDev &r, bool frozen, co
                           const void *fbar_next, const void *cbar_next,
                           double dep_bar, void *fbar, void *cbar, double *vs_bar, void *work,
                           const lbw_launch &l, hipStream_t st);
+// Per-block partials of each run into part (kReduceBlocks per run) and, when
+// out is not NULL, each run's sum into out[run]; both writable by the device.
 // plane >= 0: MASS_C / MASS_S sum only the cells below that horizontal plane
 // (the first plane * ncol nodes of each run); -1: all nodes.  cls >= 0:
 // MASS_C and DEPOSIT of that particle size class only; -1: every class.
 hipError_t launch_reduce(int q, int precision, const RunDev *runs, int nbatch, int what,
-                         bool odd, double *scratch, hipStream_t st, int plane = -1,
+                         bool odd, double *part, double *out, hipStream_t st, int plane = -1,
                          int cls = -1);
+// The sum of one run's kReduceBlocks partials, bit for bit as the reduction's
+// last pass forms it.
+double final_sum(const double *part);
 // Power spectral density of a front height (device, ncol values) along
 // lateral axis `axis` for slice `index` (-1: mean over slices); out[len/2+1].
 hipError_t launch_front_psd(const RunDev &r, int dim, const double *h, int axis, int index,

@@ -81,6 +81,25 @@ __global__ void __launch_bounds__(1024) k_partial(RunDev r, int what, bool odd, 
     if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
+// Sum of one run's partials in the order of k_final, on the host: the tree of
+// its wavefront shuffles over each 64 partials, then the four wave sums.
+}  // namespace
+
+double final_sum(const double *part) {
+    static_assert(kReduceBlocks == 256, "four waves of partials");
+    double t = 0.0;
+    for (int w = 0; w < 4; ++w) {
+        double v[64];
+        for (int i = 0; i < 64; ++i) v[i] = part[64 * w + i];
+        for (int off = 32; off > 0; off >>= 1)
+            for (int i = 0; i < off; ++i) v[i] += v[i + off];
+        t += v[0];
+    }
+    return t;
+}
+
+namespace {
+
 __global__ void __launch_bounds__(256) k_final(const double *__restrict__ part, int nblocks,
                                                double *__restrict__ out) {
     const double *p = part + (int64_t)blockIdx.x * nblocks;
@@ -92,11 +111,11 @@ __global__ void __launch_bounds__(256) k_final(const double *__restrict__ part, 
 
 template <int Q, typename T>
 hipError_t reduce_t(const RunDev *runs, int nbatch, int what, bool odd, bool shifted,
-                    double *scratch, hipStream_t st, int plane, int cls) {
+                    double *part, double *out, hipStream_t st, int plane, int cls) {
     for (int b = 0; b < nbatch; ++b)
         k_partial<Q, T><<<kReduceBlocks, 1024, 0, st>>>(runs[b], what, odd, shifted, plane, cls,
-                                                        scratch + (int64_t)b * kReduceBlocks);
-    k_final<<<nbatch, 256, 0, st>>>(scratch, kReduceBlocks, scratch + (int64_t)nbatch * kReduceBlocks);
+                                                        part + (int64_t)b * kReduceBlocks);
+    if (out) k_final<<<nbatch, 256, 0, st>>>(part, kReduceBlocks, out);
     return hipGetLastError();
 }
 
@@ -176,13 +195,13 @@ __global__ void __launch_bounds__(64 * W) k_front_height(const T *__restrict__ c
 }  // namespace
 
 hipError_t launch_reduce(int q, int precision, const RunDev *runs, int nbatch, int what, bool odd,
-                         double *scratch, hipStream_t st, int plane, int cls) {
+                         double *part, double *out, hipStream_t st, int plane, int cls) {
     const bool sh = precision != LBW_FP64;
     if (precision == LBW_FP32_SHIFTED)
-        return q == 9 ? reduce_t<9, float>(runs, nbatch, what, odd, sh, scratch, st, plane, cls)
-                      : reduce_t<19, float>(runs, nbatch, what, odd, sh, scratch, st, plane, cls);
-    return q == 9 ? reduce_t<9, double>(runs, nbatch, what, odd, sh, scratch, st, plane, cls)
-                  : reduce_t<19, double>(runs, nbatch, what, odd, sh, scratch, st, plane, cls);
+        return q == 9 ? reduce_t<9, float>(runs, nbatch, what, odd, sh, part, out, st, plane, cls)
+                      : reduce_t<19, float>(runs, nbatch, what, odd, sh, part, out, st, plane, cls);
+    return q == 9 ? reduce_t<9, double>(runs, nbatch, what, odd, sh, part, out, st, plane, cls)
+                  : reduce_t<19, double>(runs, nbatch, what, odd, sh, part, out, st, plane, cls);
 }
 
 template <typename T, bool MULTI>
