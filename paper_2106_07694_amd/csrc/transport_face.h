@@ -87,6 +87,33 @@ __device__ __forceinline__ T face6(T a0, T a1, T a2, T a3, T a4, T a5, T w0, T w
     return hh - kappa * (a3 - a2);
 }
 
+// face6 of six nodes in LDS, S elements apart, a at byte offset base + CA and w
+// at base + CW: the upwind side is chosen by the address the stencil is read
+// from (node j-2 upwards or j+3 downwards), which costs one select and an add
+// per node where selecting among loaded values costs two selects (four in
+// double precision); a and w of a node share the address.
+template <typename T, int SCHEME, int S, int CA, int CW>
+__device__ __forceinline__ T face6_lds(const T *smem, uint32_t base, T kappa, T eps) {
+    constexpr int E = (int)sizeof(T);
+    auto at = [&](uint32_t off, int c) { return *(const T *)((const char *)smem + off + c); };
+    const bool pos = (at(base, CW + 2 * S * E) + at(base, CW + 3 * S * E)) >= (T)0;
+    const uint32_t n0 = base + (pos ? 0u : (uint32_t)(5 * S * E)), step = pos ? (uint32_t)(S * E) : (uint32_t)(-S * E);
+    const uint32_t n1 = n0 + step, n2 = n1 + step, n3 = n2 + step, n4 = n3 + step;
+    const T a2 = at(n2, CA), a3 = at(n3, CA), kd = pos ? kappa : -kappa;
+    T hh;
+    if constexpr (SCHEME == LBW_WENO5) {
+        const T a0 = at(n0, CA), a1 = at(n1, CA), a4 = at(n4, CA);
+        hh = weno5_rcp<T>(at(n0, CW) * a0, at(n1, CW) * a1, at(n2, CW) * a2, at(n3, CW) * a3, at(n4, CW) * a4,
+                          a0, a1, a2, a3, a4, (T)(12.0 / 13.0) * eps);
+    } else if constexpr (SCHEME == LBW_WENO3) {
+        const T a1 = at(n1, CA);
+        hh = weno3_rcp<T>(at(n1, CW) * a1, at(n2, CW) * a2, at(n3, CW) * a3, a1, a2, a3, eps);
+    } else {
+        hh = at(n2, CW) * a2;
+    }
+    return hh - kd * (a3 - a2);
+}
+
 // WENO5 with the work of each node done once (the arithmetic of weno5_rcp
 // regrouped by node).  Node m is the centre of three sub-stencils that faces
 // read: with t = a_{m+1} - 2 a_m + a_{m-1} and c = a_{m+1} - a_{m-1}, their

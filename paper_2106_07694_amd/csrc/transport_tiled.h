@@ -115,7 +115,7 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
     // accesses which share a lane-dependent index can share one address
     // register and differ only in the instruction's constant offset.
     constexpr int O_A = 0, O_UX = AY * AX, O_UY = O_UX + TY * AX,
-                  O_FX = O_UY + ((D == 3) ? (TY + 6) * TX : 1), O_FY = O_FX + TY * (TX + 1),
+                  O_FX = O_UY + ((D == 3) ? (TY + 6) * AX : 1), O_FY = O_FX + TY * (TX + 1),
                   O_S = O_FY + ((D == 3) ? (TY + 1) * TX : 1), O_GX = O_S + (FS ? SXL * SYL : 1),
                   O_GY = O_GX + (FS ? TY * (TX + 1) : 1),
                   O_END = O_GY + ((FS && D == 3) ? (TY + 1) * TX : 1);
@@ -252,7 +252,7 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
         if (i < NUY) {
             const int lx = i % TX, ly = i / TX;
             offY[s] = lat(wrapx(x0 + lx), wrapy(y0 + ly - 3));
-            ldsY[s] = O_UY + ly * TX + lx;
+            ldsY[s] = O_UY + ly * AX + lx + 3;
         }
     }
 
@@ -444,20 +444,20 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
             // each thread the x face on the left of its cell and (3D) the y
             // face below it; the stage input at the cell is the x stencil's
             // fourth node
+            // byte offsets of the faces' first nodes from cell (tx, ty)'s place in a
+            // row of AX: x nodes tx-3 .. tx+2 of the row, y rows ty-3 .. ty+2 of the
+            // column
+            constexpr int XA = (O_A + ((D == 3) ? 3 * AX : 0)) * (int)sizeof(T), XW = O_UX * (int)sizeof(T);
+            constexpr int YA = (O_A + 3) * (int)sizeof(T), YW = (O_UY + 3) * (int)sizeof(T);
+            const uint32_t cell = (uint32_t)((ty * AX + tx) * (int)sizeof(T));
             T a_own;
             {
                 const T *ar = sA + ((D == 3) ? (ty + 3) : 0) * AX + tx;   // nodes tx-3 .. tx+2
-                const T *ur = sUx + ty * AX + tx;
-                sFx[ty * (TX + 1) + tx] = face6<T, SCHEME>(ar[0], ar[1], ar[2], ar[3], ar[4], ar[5], ur[0],
-                                                            ur[1], ur[2], ur[3], ur[4], ur[5], kap, eps);
+                sFx[ty * (TX + 1) + tx] = face6_lds<T, SCHEME, 1, XA, XW>(smem, cell, kap, eps);
                 a_own = ar[3];
             }
             if constexpr (D == 3) {
-                const T *ac = sA + ty * AX + tx + 3;      // rows ty-3+3 .. ty+2+3 of column tx
-                const T *uc = sUy + ty * TX + tx;
-                sFy[ty * TX + tx] = face6<T, SCHEME>(ac[0], ac[AX], ac[2 * AX], ac[3 * AX], ac[4 * AX],
-                                                     ac[5 * AX], uc[0], uc[TX], uc[2 * TX], uc[3 * TX],
-                                                     uc[4 * TX], uc[5 * TX], kap, eps);
+                sFy[ty * TX + tx] = face6_lds<T, SCHEME, AX, YA, YW>(smem, cell, kap, eps);
             }
             if constexpr (FS) {
                 // S faces on the left of the cell and (3D) below it
@@ -466,8 +466,8 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
                 sGx[ty * (TX + 1) + tx] = sface(sr[0], sr[1], ur[0], ur[1]);
                 if constexpr (D == 3) {
                     const T *sc = sS + ty * SXL + tx + 1;                  // y - 1, y
-                    const T *uc = sUy + (ty + 2) * TX + tx;
-                    sGy[ty * TX + tx] = sface(sc[0], sc[SXL], uc[0], uc[TX]);
+                    const T *uc = sUy + (ty + 2) * AX + tx + 3;
+                    sGy[ty * TX + tx] = sface(sc[0], sc[SXL], uc[0], uc[AX]);
                 }
             }
             // faces on the far edges of the tile, taken by the first lanes in
@@ -479,24 +479,17 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
             static_assert(NEX <= NT, "one pass of edge faces");
             if (D == 3 && tid < TX) {
                 if constexpr (D == 3) {
-                    const T *ac = sA + (ty + TY) * AX + tx + 3;
-                    const T *uc = sUy + (ty + TY) * TX + tx;
-                    sFy[(ty + TY) * TX + tx] = face6<T, SCHEME>(ac[0], ac[AX], ac[2 * AX], ac[3 * AX],
-                                                                ac[4 * AX], ac[5 * AX], uc[0], uc[TX],
-                                                                uc[2 * TX], uc[3 * TX], uc[4 * TX],
-                                                                uc[5 * TX], kap, eps);
+                    sFy[(ty + TY) * TX + tx] = face6_lds<T, SCHEME, AX, YA, YW>(smem, cell + TY * AX * (int)sizeof(T), kap, eps);
                     if constexpr (FS) {
                         const T *sc = sS + (ty + TY) * SXL + tx + 1;
-                        const T *uc2 = sUy + (ty + TY + 2) * TX + tx;
-                        sGy[(ty + TY) * TX + tx] = sface(sc[0], sc[SXL], uc2[0], uc2[TX]);
+                        const T *uc2 = sUy + (ty + TY + 2) * AX + tx + 3;
+                        sGy[(ty + TY) * TX + tx] = sface(sc[0], sc[SXL], uc2[0], uc2[AX]);
                     }
                 }
             } else if (tid < NEX) {
                 const int fy = tid - ((D == 3) ? TX : 0);
-                const T *ar = sA + ((D == 3) ? (fy + 3) : 0) * AX + TX;
-                const T *ur = sUx + fy * AX + TX;
-                sFx[fy * (TX + 1) + TX] = face6<T, SCHEME>(ar[0], ar[1], ar[2], ar[3], ar[4], ar[5], ur[0],
-                                                           ur[1], ur[2], ur[3], ur[4], ur[5], kap, eps);
+                sFx[fy * (TX + 1) + TX] =
+                    face6_lds<T, SCHEME, 1, XA, XW>(smem, (uint32_t)((fy * AX + TX) * (int)sizeof(T)), kap, eps);
                 if constexpr (FS) {
                     const T *sr = sS + ((D == 3) ? fy + 1 : 0) * SXL + TX;
                     const T *ur2 = sUx + fy * AX + TX + 2;
