@@ -146,23 +146,27 @@ __global__ void __launch_bounds__(NT) k_rk3_2d(RunDev r, ClassSet cs, T *__restr
         constexpr int STAGE = decltype(stage_id)::value, H = decltype(halo)::value;
         constexpr int OX = TX + 2 * H, OY = TY + 2 * H, IX = OX + 6;
         constexpr int FX = OY * (OX + 1), FY = (OY + 1) * OX;
-        for (int i = tid; i < FX; i += NT) {             // face on the left of cell (cx, ry)
-            const int ry = i / (OX + 1), cx = i % (OX + 1);
-            const T *a = in + (ry + 3) * IX + cx, *w = sU + (ry + 6 - H) * RX + cx + 6 - H;
-            sFx[i] = face6<T, SCHEME>(a[0], a[1], a[2], a[3], a[4], a[5], w[0], w[1], w[2], w[3], w[4],
+        // a thread takes an x face and a y face at once, without branches, so
+        // that the two chains of dependent arithmetic overlap
+        for (int i = tid; i < (FX > FY ? FX : FY); i += NT) {
+            const int fx = min(i, FX - 1), fy = min(i, FY - 1);
+            T fl, fb;
+            {                                            // face on the left of cell (cx, ry)
+                const int ry = fx / (OX + 1), cx = fx % (OX + 1);
+                const T *a = in + (ry + 3) * IX + cx, *w = sU + (ry + 6 - H) * RX + cx + 6 - H;
+                fl = face6<T, SCHEME>(a[0], a[1], a[2], a[3], a[4], a[5], w[0], w[1], w[2], w[3], w[4],
                                       w[5], kap, eps);
-        }
-        for (int i = tid; i < FY; i += NT) {             // face below cell (cx, ry)
-            const int ry = i / OX, cx = i % OX, y = y0 - H + ry;
-            if (walls && (y < 0 || y > ny)) continue;    // no cell of the grid reads it
-            const T *a = in + ry * IX + cx + 3, *w = sW + (ry + 6 - H) * PX + cx + 6 - H;
-            T f;
-            if (walls && y == 0) f = -settle(wrap_index(x0 - H + cx, nx)) * a[3 * IX];   // absorbing bottom
-            else if (walls && y == ny) f = (T)0;
-            else
-                f = face6<T, SCHEME>(a[0], a[IX], a[2 * IX], a[3 * IX], a[4 * IX], a[5 * IX], w[0], w[PX],
-                                     w[2 * PX], w[3 * PX], w[4 * PX], w[5 * PX], kap, eps);
-            sFy[i] = f;
+            }
+            {                                            // face below cell (cx, ry)
+                const int ry = fy / OX, cx = fy % OX, y = y0 - H + ry;
+                const T *a = in + ry * IX + cx + 3, *w = sW + (ry + 6 - H) * PX + cx + 6 - H;
+                fb = face6<T, SCHEME>(a[0], a[IX], a[2 * IX], a[3 * IX], a[4 * IX], a[5 * IX], w[0], w[PX],
+                                      w[2 * PX], w[3 * PX], w[4 * PX], w[5 * PX], kap, eps);
+                if (walls && y == ny) fb = (T)0;         // closed top; rows further out are not read
+                if (walls && y == 0) fb = -settle(wrap_index(x0 - H + cx, nx)) * a[3 * IX];   // absorbing bottom
+            }
+            sFx[fx] = fl;
+            sFy[fy] = fb;
         }
         __syncthreads();
         for (int i = tid; i < OX * OY; i += NT) {
