@@ -19,12 +19,13 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
 # (source, object name, preprocessor definitions); the tiled transport builds one unit per
-# element type, dimension and settling form, all in parallel
+# element type, dimension and settling form, the fused one per element type, all in parallel
 TILED = [("transport_tiled_unit.hip", f"transport_tiled_{d}d_{t}{'_vs' if v else ''}",
           [f"-DLBW_T={t}", f"-DLBW_D={d}", f"-DLBW_VSS={v}"])
          for t in ("double", "float") for d in (3, 2) for v in (0, 1)]
-SOURCES = TILED + [(src, os.path.splitext(src)[0], []) for src in (
-    "adjoint.hip", "lbm.hip", "transport.hip", "transport_tiled.hip", "transport_fused.hip", "reduce.hip", "api.cpp")]
+FUSED = [("transport_fused.hip", f"transport_fused_{t}", [f"-DLBW_T={t}"]) for t in ("double", "float")]
+SOURCES = TILED + FUSED + [(src, os.path.splitext(src)[0], []) for src in (
+    "adjoint.hip", "lbm.hip", "transport.hip", "transport_tiled.hip", "reduce.hip", "api.cpp")]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

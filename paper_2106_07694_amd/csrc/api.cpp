@@ -117,7 +117,7 @@ struct FusedStep {
 };
 
 bool fused_applies(const lbw_handle *h) {
-    return h->nbatch == 1 && lbw::rk3_fused2d_applies(h->dim, h->run[0], h->launch);
+    return h->nbatch == 1 && lbw::rk3_fused2d_applies(h->dim, h->precision, h->run[0], h->launch);
 }
 
 // Size class i of a run as the transport kernels see it: its C field and

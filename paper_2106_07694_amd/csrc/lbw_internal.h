@@ -144,7 +144,10 @@ hipError_t launch_one_stage(int dim, int precision, const RunDev &r, const lbw_l
                             int stage, hipStream_t st);
 // Whether a run takes the fused transport: 2D, no launch shape set, and a grid
 // small enough.
-bool rk3_fused2d_applies(int dim, const RunDev &r, const lbw_launch &l);
+bool rk3_fused2d_applies(int dim, int precision, const RunDev &r, const lbw_launch &l);
+// The same per element type (one unit each).
+template <typename T>
+hipError_t fused_unit(const RunDev &r, const ClassSet &cs, void *cout, void *a1, void *a2, hipStream_t st);
 // The whole transport of a 2D step in one launch: reads C (of every class) from
 // r.c, writes the result to cout (another buffer) and, where given, the stages
 // to a1 and a2.

@@ -214,24 +214,57 @@ hipError_t fused_tile(const RunDev &r, const ClassSet &cs, void *cout, void *a1,
     return hipGetLastError();
 }
 
-// The smallest tile whose blocks find a CU each: a smaller tile recomputes
-// more halo per cell, a larger one leaves CUs idle.  us per step, collide
-// included (16x16, 32x16, 32x32): single precision 128x256 11.4, 12.6, 15.1;
-// 256x512 15.8, 14.7, 17.1; 700x1100 50.9, 42.5, 40.4; double 128x256 13.5,
-// 15.6, 19.6; 256x512 20.9, 19.6, 23.4; 700x1100 78.8, 66.7, 74.5 (32x32 holds
-// 114 KB of LDS there, one block per CU).
+// The tile whose launch is estimated to end first.  A CU holds two blocks at a
+// time, and with k = ceil(blocks / 256) of them to work off it takes about
+// start + k * block us (measured on grids from 128x256 to 1024x1536, each tile
+// on all of them; within 1 us up to k = 4): a small tile recomputes more halo
+// per cell, a large one leaves CUs idle, and one block beyond a multiple of 256
+// costs a whole block's time (515x1030 in single precision: 561 blocks of 32x32
+// take 23.2 us, 442 of 32x40 20.1; 512x1024: 512 of 32x32 16.8, 416 of 32x40
+// 19.6).
+struct FusedTile {
+    int tx, ty;
+    float start, block;
+};
+constexpr FusedTile kTilesF32[] = {{16, 16, 6.9f, 2.45f}, {32, 16, 6.2f, 3.55f}, {32, 24, 7.0f, 4.4f},
+                                   {32, 32, 6.5f, 5.25f}, {32, 40, 7.6f, 6.35f}, {32, 48, 8.0f, 7.05f}};
+constexpr FusedTile kTilesF64[] = {{16, 16, 7.5f, 3.85f}, {32, 16, 7.6f, 5.5f}, {32, 24, 5.0f, 10.5f},
+                                   {32, 32, 4.0f, 12.7f}};
+
 template <typename T, int SCHEME>
 hipError_t fused_scheme(const RunDev &r, const ClassSet &cs, void *cout, void *a1, void *a2, hipStream_t st) {
-    auto fits = [&](int tx, int ty) { return (int64_t)((r.nx + tx - 1) / tx) * ((r.ny + ty - 1) / ty) * cs.n <= 256; };
-    if (fits(16, 16)) return fused_tile<T, SCHEME, 16, 16, 1024>(r, cs, cout, a1, a2, st);
+    const FusedTile *best = nullptr;
+    float least = 0.f;
+    auto consider = [&](const FusedTile &t) {
+        const int64_t blocks = (int64_t)((r.nx + t.tx - 1) / t.tx) * ((r.ny + t.ty - 1) / t.ty) * cs.n;
+        const float us = t.start + t.block * (float)((blocks + 255) / 256);
+        if (!best || us < least) {
+            best = &t;
+            least = us;
+        }
+    };
     if constexpr (sizeof(T) == 4) {
-        if (!fits(32, 16)) return fused_tile<T, SCHEME, 32, 32, 1024>(r, cs, cout, a1, a2, st);
+        for (const FusedTile &t : kTilesF32) consider(t);
+    } else {
+        for (const FusedTile &t : kTilesF64) consider(t);
     }
-    return fused_tile<T, SCHEME, 32, 16, 1024>(r, cs, cout, a1, a2, st);
+    if (best->tx == 16) return fused_tile<T, SCHEME, 16, 16, 1024>(r, cs, cout, a1, a2, st);
+    switch (best->ty) {
+        case 16: return fused_tile<T, SCHEME, 32, 16, 1024>(r, cs, cout, a1, a2, st);
+        case 24: return fused_tile<T, SCHEME, 32, 24, 1024>(r, cs, cout, a1, a2, st);
+        case 32: return fused_tile<T, SCHEME, 32, 32, 1024>(r, cs, cout, a1, a2, st);
+    }
+    if constexpr (sizeof(T) == 4) {
+        if (best->ty == 40) return fused_tile<T, SCHEME, 32, 40, 1024>(r, cs, cout, a1, a2, st);
+        if (best->ty == 48) return fused_tile<T, SCHEME, 32, 48, 1024>(r, cs, cout, a1, a2, st);
+    }
+    return hipErrorInvalidValue;
 }
 
+}  // namespace
+
 template <typename T>
-hipError_t fused_t(const RunDev &r, const ClassSet &cs, void *cout, void *a1, void *a2, hipStream_t st) {
+hipError_t fused_unit(const RunDev &r, const ClassSet &cs, void *cout, void *a1, void *a2, hipStream_t st) {
     switch (r.scheme) {
         case LBW_WENO5: return fused_scheme<T, LBW_WENO5>(r, cs, cout, a1, a2, st);
         case LBW_WENO3: return fused_scheme<T, LBW_WENO3>(r, cs, cout, a1, a2, st);
@@ -240,23 +273,7 @@ hipError_t fused_t(const RunDev &r, const ClassSet &cs, void *cout, void *a1, vo
     return hipErrorInvalidValue;
 }
 
-}  // namespace
-
-// Grids up to 3/4 of 2^20 cells: beyond, three launches of the march fill the
-// chip and the recomputed halo decides.  us per step, fused against march,
-// collide included: 64x128 11.3 against 19.6 (double 13.3, 20.5); 515x1030
-// 34.0, 36.9 (53.2, 58.3); 700x1100 40.4, 44.7 (66.7, 73.8); 1024x1024 47.9,
-// 47.0 (87.2, 79.2).  A launch shape set by the caller asks for the march.  One
-// block row per tile row: 65535 at most.
-bool rk3_fused2d_applies(int dim, const RunDev &r, const lbw_launch &l) {
-    return dim == 2 && l.variant == 0 && !l.tile_x && !l.tile_y && !l.tile_rows &&
-           r.N * r.ncls <= (3 << 18) && r.ny <= 65535 * 16;
-}
-
-hipError_t launch_rk3_fused2d(int precision, const RunDev &r, const ClassSet &cs, void *cout, void *a1,
-                              void *a2, hipStream_t st) {
-    return precision == LBW_FP32_SHIFTED ? fused_t<float>(r, cs, cout, a1, a2, st)
-                                         : fused_t<double>(r, cs, cout, a1, a2, st);
-}
+// built once per element type (LBW_T)
+template hipError_t fused_unit<LBW_T>(const RunDev &, const ClassSet &, void *, void *, void *, hipStream_t);
 
 }  // namespace lbw

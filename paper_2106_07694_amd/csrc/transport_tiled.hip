@@ -1,5 +1,6 @@
 // transport_tiled.hip -- launch shapes and launchers of the tiled RK3 stage
-// kernels (transport_tiled.h, built in transport_tiled_unit.hip).
+// kernels (transport_tiled.h, built in transport_tiled_unit.hip) and of the
+// fused 2D transport (transport_fused.hip).
 #include <algorithm>
 
 #include "lbw_internal.h"
@@ -155,6 +156,25 @@ hipError_t launch_transport_batched(int dim, int precision, const BatchArgs &b, 
         }
     }
     return hipSuccess;
+}
+
+// Grids up to 9 * 2^17 cells (6 * 2^17 in double precision): beyond, three
+// launches of the march fill the chip and the recomputed halo decides.  us per
+// step of transport, fused against march, single precision: 515x1030 20.1, 25.0;
+// 1024x1024 27.7, 29.1; 900x1300 32.9, 36.4; 1024x1280 32.8, 32.1; 1024x1536
+// 36.4, 35.3; double: 256x512 13.5, 18.5; 512x1024 29.7, 30.1; 700x1100 44.3,
+// 47.5; 1024x1024 52.7, 45.0.  A launch shape set by the caller asks for the
+// march.  One block row per 16 or more grid rows, 65535 at most.
+bool rk3_fused2d_applies(int dim, int precision, const RunDev &r, const lbw_launch &l) {
+    const int64_t most = (int64_t)(precision == LBW_FP32_SHIFTED ? 9 : 6) << 17;
+    return dim == 2 && l.variant == 0 && !l.tile_x && !l.tile_y && !l.tile_rows && r.N * r.ncls <= most &&
+           r.ny <= 65535 * 16;
+}
+
+hipError_t launch_rk3_fused2d(int precision, const RunDev &r, const ClassSet &cs, void *cout, void *a1,
+                              void *a2, hipStream_t st) {
+    return precision == LBW_FP32_SHIFTED ? fused_unit<float>(r, cs, cout, a1, a2, st)
+                                         : fused_unit<double>(r, cs, cout, a1, a2, st);
 }
 
 }  // namespace lbw

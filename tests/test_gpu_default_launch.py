@@ -58,6 +58,8 @@ def test_default_shape_gives_the_bits_of_an_explicit_one(dim, size, precision):
 # grids that take the fused 2D transport: each of its tiles, whole and ragged,
 # axes shorter than its nine-cell reach, the minimal height
 FUSED = [(3, 6), (7, 20), (16, 16), (33, 47), (65, 130), (200, 290), (258, 300), (512, 640)]
+# one more grid per taller tile of single precision (32x24, 32x40, 32x48) and of double (32x24, 32x32)
+FUSED += [(300, 560), (400, 700), (700, 1100), (480, 530)]
 
 
 SCHEMES = ("weno5", "weno3", "upwind1")
