@@ -28,6 +28,12 @@
 #include "lbm_device.h"
 #include "transport_device.h"
 
+// The one-kernel and the two-kernel form of a reversed stage give the same
+// bits, so multiply-adds are fused only within one source expression (the
+// default fast contraction may also fuse across statements, differently in
+// each kernel).
+#pragma clang fp contract(on)
+
 namespace lbw {
 namespace {
 
@@ -86,88 +92,74 @@ __global__ void __launch_bounds__(256) k_adj_moments(AdjDev a) {
 template <typename T> __device__ __forceinline__ T rcp(T x) { return (T)1 / x; }
 template <> __device__ __forceinline__ float rcp<float>(float x) { return __builtin_amdgcn_rcpf(x); }
 
-// Reverse of the WENO5-JS face value for stencil values (upwind -> downwind)
-// h (fluxes) and a (smoothness input): gb = dJ/d(face value); returns dJ/dh
-// and the smoothness part of dJ/da.  Four reciprocals, no divisions.
-template <typename T>
-__device__ __forceinline__ void weno5_vjp(const T h[5], const T a[5], T eps, T gb, T hb[5], T ab[5]) {
-    constexpr T i6 = (T)(1.0 / 6.0);
-    const T q0 = ((T)2 * h[0] - (T)7 * h[1] + (T)11 * h[2]) * i6;
-    const T q1 = (-h[1] + (T)5 * h[2] + (T)2 * h[3]) * i6;
-    const T q2 = ((T)2 * h[2] + (T)5 * h[3] - h[4]) * i6;
-    const T t0 = a[0] - (T)2 * a[1] + a[2], s0 = a[0] - (T)4 * a[1] + (T)3 * a[2];
-    const T t1 = a[1] - (T)2 * a[2] + a[3], s1 = a[1] - a[3];
-    const T t2 = a[2] - (T)2 * a[3] + a[4], s2 = (T)3 * a[2] - (T)4 * a[3] + a[4];
-    const T e0 = eps + ((T)(13.0 / 12.0) * t0 * t0 + (T)0.25 * s0 * s0);
-    const T e1 = eps + ((T)(13.0 / 12.0) * t1 * t1 + (T)0.25 * s1 * s1);
-    const T e2 = eps + ((T)(13.0 / 12.0) * t2 * t2 + (T)0.25 * s2 * s2);
-    const T ie0 = rcp<T>(e0), ie1 = rcp<T>(e1), ie2 = rcp<T>(e2);
-    const T al0 = (T)0.1 * ie0 * ie0, al1 = (T)0.6 * ie1 * ie1, al2 = (T)0.3 * ie2 * ie2;
-    const T iS = rcp<T>(al0 + al1 + al2);
-    const T g = (al0 * q0 + al1 * q1 + al2 * q2) * iS;
-    // g = sum al_k q_k / S: dg/dq_k = al_k / S, dg/dal_k = (q_k - g) / S,
-    // dal_k/de_k = -2 al_k / e_k (e_k = eps + smoothness indicator k)
-    const T gS = gb * iS;
-    const T qb0 = gS * al0, qb1 = gS * al1, qb2 = gS * al2;
-    const T bb0 = (q0 - g) * qb0 * ((T)-2 * ie0);
-    const T bb1 = (q1 - g) * qb1 * ((T)-2 * ie1);
-    const T bb2 = (q2 - g) * qb2 * ((T)-2 * ie2);
-    hb[0] = (T)(2.0 / 6.0) * qb0;
-    hb[1] = (T)(-7.0 / 6.0) * qb0 - i6 * qb1;
-    hb[2] = (T)(11.0 / 6.0) * qb0 + (T)(5.0 / 6.0) * qb1 + (T)(2.0 / 6.0) * qb2;
-    hb[3] = (T)(2.0 / 6.0) * qb1 + (T)(5.0 / 6.0) * qb2;
-    hb[4] = -i6 * qb2;
-    // indicator = 13/12 t^2 + 1/4 s^2
-    T tb = (T)(13.0 / 6.0) * t0 * bb0, sb = (T)0.5 * s0 * bb0;
-    ab[0] = tb + sb;
-    ab[1] = (T)-2 * tb - (T)4 * sb;
-    ab[2] = tb + (T)3 * sb;
-    tb = (T)(13.0 / 6.0) * t1 * bb1;
-    sb = (T)0.5 * s1 * bb1;
-    ab[1] += tb + sb;
-    ab[2] += (T)-2 * tb;
-    ab[3] = tb - sb;
-    tb = (T)(13.0 / 6.0) * t2 * bb2;
-    sb = (T)0.5 * s2 * bb2;
-    ab[2] += tb + (T)3 * sb;
-    ab[3] += (T)-2 * tb - (T)4 * sb;
-    ab[4] = tb + sb;
+// Reciprocals of three indicators: one division for all of them in double
+// precision (a division is some ten instructions there), the hardware
+// reciprocal of each in single.
+__device__ __forceinline__ void rcp3(float e0, float e1, float e2, float &i0, float &i1, float &i2) {
+    i0 = rcp<float>(e0);
+    i1 = rcp<float>(e1);
+    i2 = rcp<float>(e2);
+}
+__device__ __forceinline__ void rcp3(double e0, double e1, double e2, double &i0, double &i1, double &i2) {
+    const double e12 = e1 * e2, i = 1.0 / (e0 * e12);
+    i0 = i * e12;
+    i1 = i * (e0 * e2);
+    i2 = i * (e0 * e1);
 }
 
-// Products of one face's local Jacobian with its adjoint pb, for the six
-// stencil nodes j-2..j+3 (values av, transport velocities wv):
-//   A[s] = pb * dPhi/da_s (WENO5 through h = w a and the indicators, plus the
-//          central diffusion), W[s] = pb * dPhi/dw_s.
-// The upwind side is taken with selects (the stencil is read mirrored when
-// the face velocity is negative), so lanes of a wave do not diverge.
+// Products of one face's local Jacobian with its adjoint pb, for the five
+// nodes its WENO5-JS reconstruction reads, ordered upwind -> downwind (values
+// a, transport velocities w; the sixth node of the stencil enters nothing):
+//   A[s] = pb * dPhi/da_s (through the fluxes h = w a, the indicators and the
+//          central diffusion -kd (a_3 - a_2)),  W[s] = pb * dPhi/dw_s.
+// Indicators are scaled by 12/13 as in the forward faces (weights are ratios):
+// e_k = t_k^2 + (3/13) s_k^2 + eps12 with t_k, s_k built from the four first
+// differences g, and the reverse runs through g as well: 130 vector
+// instructions a face in single precision, 200 with the differences of a
+// written out and the upwind side selected among the results.
 template <typename T>
-__device__ __forceinline__ void face_vjp(const T av[6], const T wv[6], T pb, T kap, T eps, T A[6],
-                                         T W[6]) {
-    const bool pos = (wv[2] + wv[3]) >= (T)0;
-    T h5[5], a5[5], hb5[5], ab5[5];
+__device__ __forceinline__ void face_vjp(const T a[5], const T w[5], T pb, T kd, T eps12, T A[5], T W[5]) {
+    T h[5];
 #pragma unroll
-    for (int s = 0; s < 5; ++s) {
-        const T aa = pos ? av[s] : av[5 - s];
-        const T ww = pos ? wv[s] : wv[5 - s];
-        a5[s] = aa;
-        h5[s] = ww * aa;
-    }
-    weno5_vjp<T>(h5, a5, eps, pb, hb5, ab5);
-    T hb[6], ab[6];
+    for (int s = 0; s < 5; ++s) h[s] = w[s] * a[s];
+    const T g0 = a[1] - a[0], g1 = a[2] - a[1], g2 = a[3] - a[2], g3 = a[4] - a[3];
+    const T t0 = g1 - g0, t1 = g2 - g1, t2 = g3 - g2;
+    const T s0 = t0 + (T)2 * g1;          // a0 - 4 a1 + 3 a2
+    const T s1 = g1 + g2;                 // a3 - a1
+    const T s2 = t2 - (T)2 * g2;          // 3 a2 - 4 a3 + a4
+    constexpr T k = (T)(3.0 / 13.0);
+    const T r0 = k * s0, r1 = k * s1, r2 = k * s2;
+    T i0, i1, i2;
+    rcp3(t0 * t0 + (r0 * s0 + eps12), t1 * t1 + (r1 * s1 + eps12), t2 * t2 + (r2 * s2 + eps12), i0, i1, i2);
+    const T al0 = i0 * i0, al1 = (T)6 * i1 * i1, al2 = (T)3 * i2 * i2;
+    const T iS = rcp<T>(al0 + al1 + al2);
+    const T q0 = (T)(1.0 / 3.0) * h[0] - (T)(7.0 / 6.0) * h[1] + (T)(11.0 / 6.0) * h[2];
+    const T q1 = (T)(5.0 / 6.0) * h[2] - (T)(1.0 / 6.0) * h[1] + (T)(1.0 / 3.0) * h[3];
+    const T q2 = (T)(1.0 / 3.0) * h[2] + (T)(5.0 / 6.0) * h[3] - (T)(1.0 / 6.0) * h[4];
+    const T f = (al0 * q0 + al1 * q1 + al2 * q2) * iS;
+    // f = sum al_k q_k / S: df/dq_k = al_k / S, df/dal_k = (q_k - f) / S,
+    // dal_k/de_k = -2 al_k / e_k, de_k/dt_k = 2 t_k, de_k/ds_k = 2 (3/13) s_k
+    const T p = pb * iS;
+    const T b0 = al0 * p, b1 = al1 * p, b2 = al2 * p;
+    const T m0 = (q0 - f) * b0 * ((T)-4 * i0);
+    const T m1 = (q1 - f) * b1 * ((T)-4 * i1);
+    const T m2 = (q2 - f) * b2 * ((T)-4 * i2);
+    const T v0 = r0 * m0, v1 = r1 * m1, v2 = r2 * m2;        // of s_k
+    const T d0 = t0 * m0 + v0, u1 = t1 * m1, d2 = t2 * m2 + v2;   // of t_0, t_1, t_2 (s_0, s_2 hold t_0, t_2)
+    const T c1 = (d0 + (T)2 * v0) + (v1 - u1);               // of g_1; of g_0 -d0, of g_3 d2
+    const T c2 = ((v1 + u1) - (d2 + (T)2 * v2)) - kd * pb;   // of g_2
+    W[0] = (T)(1.0 / 3.0) * b0;
+    W[1] = (T)(-7.0 / 6.0) * b0 - (T)(1.0 / 6.0) * b1;
+    W[2] = (T)(11.0 / 6.0) * b0 + ((T)(5.0 / 6.0) * b1 + (T)(1.0 / 3.0) * b2);
+    W[3] = (T)(1.0 / 3.0) * b1 + (T)(5.0 / 6.0) * b2;
+    W[4] = (T)(-1.0 / 6.0) * b2;
+    A[0] = d0 + W[0] * w[0];
+    A[1] = (-d0 - c1) + W[1] * w[1];
+    A[2] = (c1 - c2) + W[2] * w[2];
+    A[3] = (c2 - d2) + W[3] * w[3];
+    A[4] = d2 + W[4] * w[4];
 #pragma unroll
-    for (int s = 0; s < 6; ++s) {
-        const T hp = s < 5 ? hb5[s] : (T)0, hn = s > 0 ? hb5[5 - s] : (T)0;
-        const T ap = s < 5 ? ab5[s] : (T)0, an = s > 0 ? ab5[5 - s] : (T)0;
-        hb[s] = pos ? hp : hn;
-        ab[s] = pos ? ap : an;
-    }
-    ab[3] += -kap * pb;   // diffusion -kappa (a_{j+1} - a_j)
-    ab[2] += kap * pb;
-#pragma unroll
-    for (int s = 0; s < 6; ++s) {
-        A[s] = ab[s] + hb[s] * wv[s];   // through a directly and through h = w a
-        W[s] = hb[s] * av[s];
-    }
+    for (int s = 0; s < 5; ++s) W[s] = W[s] * a[s];
 }
 
 // For every interior face j+1/2 (stored at its lower node j) and axis d:
@@ -183,7 +175,7 @@ __global__ void __launch_bounds__(256) k_adj_face(AdjDev A, const T *__restrict_
     xyz<D>(r, k, x, y, z);
     const T *u = (const T *)(A.frozen ? r.u : A.u);
     T *fa = (T *)A.faceA, *fw = (T *)A.faceW;
-    const T vs = (T)r.vs, kap = (T)r.kappa_c, eps = (T)r.eps;
+    const T vs = (T)r.vs, kap = (T)r.kappa_c, eps12 = (T)(12.0 / 13.0) * (T)r.eps;
 #pragma unroll
     for (int d = 0; d < D; ++d) {
         const bool vert = (d == D - 1);
@@ -214,12 +206,22 @@ __global__ void __launch_bounds__(256) k_adj_face(AdjDev A, const T *__restrict_
         int jn = j + 1;
         if (jn >= n) jn -= n;   // periodic neighbour (walls never reach here at the top)
         const T pb = scale * (lam[k + (int64_t)(jn - j) * stride] - lam[k]);
-        T fa6[6], fw6[6];
-        face_vjp<T>(av, wv, pb, kap, eps, fa6, fw6);
+        // the stencil read from its upwind end (selects, so that lanes of a
+        // wave do not diverge); the node beyond the downwind end gets zeros
+        const bool pos = (wv[2] + wv[3]) >= (T)0;
+        T a5[5], w5[5], fa5[5], fw5[5];
+#pragma unroll
+        for (int s = 0; s < 5; ++s) {
+            a5[s] = pos ? av[s] : av[5 - s];
+            w5[s] = pos ? wv[s] : wv[5 - s];
+        }
+        face_vjp<T>(a5, w5, pb, pos ? kap : -kap, eps12, fa5, fw5);
 #pragma unroll
         for (int s = 0; s < 6; ++s) {
-            fa[base + s * r.N] = fa6[s];
-            fw[base + s * r.N] = fw6[s];
+            const T ap = s < 5 ? fa5[s] : (T)0, an = s > 0 ? fa5[5 - s] : (T)0;
+            const T wp = s < 5 ? fw5[s] : (T)0, wn = s > 0 ? fw5[5 - s] : (T)0;
+            fa[base + s * r.N] = pos ? ap : an;
+            fw[base + s * r.N] = pos ? wp : wn;
         }
     }
 }
@@ -434,15 +436,18 @@ __global__ void __launch_bounds__(256) k_adj_gather(AdjDev A) {
 // products (6 D values of A and of W per node, written and read) disappears,
 // at the price of the faces neighbouring tiles also evaluate.
 //
-// Vector issue bounds it (2D 512x1024 in single precision: 790 vector
-// instructions per node, 11.7 of a stage's 15 us), so tiles are as large as
-// occupancy allows (2D 64x8 evaluates 2.7 faces per node, 3D 16x4x4 5.8), one
-// node index serves three loads, and positions wrap without remainders.  All the
+// Vector issue bounds it (2D 512x1024 in single precision: 516 vector
+// instructions per node, 6.9 of a stage's 12.3 us; 790 and 15.5 with the upwind
+// side chosen by selects and per-lane positions), so tiles are as large as
+// occupancy allows (2D 64x8 evaluates 2.7 faces per node, 3D 16x4x4 5.8), a
+// stencil's upwind side is an address, a wave stages one position of 64 lines
+// (its place on the axis, wrap and mirror are scalar work), and faces beyond a
+// wall hold zeros so that a node adds its six products unchecked.  All the
 // tile's loads are in flight before the first is stored to LDS; LDS holds one
 // axis at a time, and of its products first A, then W (kept in registers
 // meanwhile), so that a CU holds 16 to 32 waves.  us per reverse step: 2D
-// 512x1024 61.5 -> 52 (against the whole set of products in LDS and remainders
-// in the index arithmetic); 3D 64x48x96 81 -> 63 (against the two-kernel form).
+// 512x1024 61.5 -> 45 (against the whole set of products in LDS); 3D 64x48x96
+// 81 -> 54 (against the two-kernel form).
 // ---------------------------------------------------------------------------
 
 // Stored position of j on a periodic axis, for the at most five cells a line's
@@ -486,68 +491,95 @@ __global__ void __launch_bounds__(NT, BLOCKS) k_adj_stage(AdjDev A, const T *__r
     int tile = (int)blockIdx.x;
     if ((nb & 7) == 0) tile = (tile & 7) * (nb >> 3) + (tile >> 3);
     const int x0 = tile % gx * TX, y0 = tile / gx % gy * TY, z0 = D == 3 ? tile / gx / gy * TZ : 0;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int WAVES = NT / 64, E = (int)sizeof(T);
     const bool walls = !r.vper;
     const T *u = (const T *)(A.frozen ? r.u : A.u);
-    const T vs = (T)r.vs, kap = (T)r.kappa_c, eps = (T)r.eps;
+    const T vs = (T)r.vs, kap = (T)r.kappa_c, eps12 = (T)(12.0 / 13.0) * (T)r.eps;
     const int64_t plane = (int64_t)nx * ny;
 
     auto vertical = [](auto ax) { return decltype(ax)::value == D - 1; };
     auto origin = [&](auto ax) { return decltype(ax)::value == 0 ? x0 : (decltype(ax)::value == 1 ? y0 : z0); };
     auto length = [&](auto ax) { return decltype(ax)::value == 0 ? nx : (decltype(ax)::value == 1 ? ny : nz); };
-    // node at position p of line `line` of an axis (mirrored beyond a wall;
-    // rows no face of the tile reads are clamped into range)
-    auto node_at = [&](auto ax, int line, int p, bool &ghost) -> int64_t {
-        constexpr int AX = decltype(ax)::value;
-        const int n = length(ax);
-        ghost = false;
-        if (vertical(ax) && walls) {
-            if (p < 0) { p = -1 - p; ghost = true; }
-            else if (p >= n) { p = 2 * n - 1 - p; ghost = true; }
-            p = min(max(p, 0), n - 1);
-        } else {
-            p = wrap_halo(p, n);
-        }
-        const int l0 = line % (AX == 0 ? TY : TX), l1 = line / (AX == 0 ? TY : TX);
-        const int x = AX == 0 ? p : min(x0 + l0, nx - 1);
-        const int y = AX == 1 ? p : min(y0 + (AX == 0 ? l0 : l1), ny - 1);
-        if constexpr (D == 2) return (int64_t)x + (int64_t)nx * y;
-        const int z = AX == 2 ? p : min(z0 + l1, nz - 1);
-        return (int64_t)(x + nx * y) + plane * z;
-    };
-    // element i of an array of `len` positions per line: x lines are contiguous,
-    // the others interleaved (lanes run along x)
-    auto split = [](auto ax, int i, int len, int &line, int &c) {
-        constexpr int AX = decltype(ax)::value;
-        if constexpr (AX == 0) { line = i / len; c = i % len; }
-        else { line = i % G::lines(AX); c = i / G::lines(AX); }
-    };
 
-    // load every axis' values into registers, unconditionally (a spare slot
-    // repeats the last entry of its array).  One node index serves a, w and lam
-    // (whose line starts two positions in)
+    // Position c of line `line` that this thread stages in round q.  Lines of y
+    // and z are 64, one per lane, so a wave stages one position of each and
+    // its place on the axis is uniform; a line of x is a row, taken by a wave
+    // where it is as wide as one, else the rows are dealt flat.
+    static_assert(G::lines(1) == 64 && (D == 2 || G::lines(2) == 64), "a lane per line of y and z");
+    constexpr bool ROWS = TX == 64 && TY * TZ == WAVES;
+    auto place = [&](auto ax, int q, int &line, int &c) {
+        constexpr int AX = decltype(ax)::value, HL = G::extent(AX) + 10;
+        if constexpr (AX > 0) { line = lane; c = wave + q * WAVES; }
+        else if constexpr (ROWS) { line = wave; c = lane + q * 64; }
+        else { line = (tid + q * NT) / HL; c = (tid + q * NT) % HL; }
+    };
+    constexpr int XR = ROWS ? (TX + 10 + 63) / 64 : ((TX + 10) * G::lines(0) + NT - 1) / NT;
+    constexpr int YR = (TY + 10 + WAVES - 1) / WAVES, ZR = D == 3 ? (TZ + 10 + WAVES - 1) / WAVES : 1;
+    // load an axis' values into registers, unconditionally (a spare slot
+    // repeats the last position).  One address serves a, w and lam; positions
+    // beyond a wall are mirrored (rows no face of the tile reads are clamped
+    // into range), those of a periodic axis wrap
+    const int lx = min(x0 + (D == 2 ? lane : lane % TX), nx - 1);
     auto load = [&](auto ax, T *pa, T *pw, T *pl) {
-        constexpr int AX = decltype(ax)::value, NL = G::lines(AX), HL = G::extent(AX) + 10;
-        const int o = origin(ax);
+        constexpr int AX = decltype(ax)::value, HL = G::extent(AX) + 10;
+        constexpr int R = AX == 0 ? XR : (AX == 1 ? YR : ZR);
+        const int o = origin(ax), n = length(ax);
         const T *ud = u + (int64_t)AX * r.N;
+        // lane's part of the node index, for lines of y and z
+        const int64_t across = D == 2 || AX == 0 ? lx
+                               : AX == 1 ? lx + plane * min(lane / TX, nz - 1 - z0)
+                                         : lx + (int64_t)nx * min(y0 + lane / TX, ny - 1);
 #pragma unroll
-        for (int q = 0; q < (HL * NL + NT - 1) / NT; ++q) {
+        for (int q = 0; q < R; ++q) {
             int line, c;
-            bool g;
-            split(ax, min(tid + q * NT, HL * NL - 1), HL, line, c);
-            const int64_t k = node_at(ax, line, o - 5 + c, g);
-            pa[q] = a[k];
-            const T w = ud[k];
-            pw[q] = vertical(ax) ? (g ? -w : w) - vs : w;
-            pl[q] = lam[k];
+            place(ax, q, line, c);
+            int p = o - 5 + min(c, HL - 1);
+            bool ghost = false;
+            if (vertical(ax) && walls) {
+                if (p < 0) { p = -1 - p; ghost = true; }
+                else if (p >= n) { p = 2 * n - 1 - p; ghost = true; }
+                p = min(max(p, 0), n - 1);
+            } else {
+                p = wrap_halo(p, n);
+            }
+            int64_t row, in;                               // uniform part, lane's part
+            if constexpr (AX == 0 && ROWS) {
+                row = (int64_t)nx * min(y0 + line, ny - 1);
+                in = p;
+            } else if constexpr (AX == 0) {
+                row = 0;
+                in = p + (int64_t)nx * min(y0 + line % TY, ny - 1) + plane * min(z0 + line / TY, nz - 1);
+            } else if constexpr (AX == 1) {
+                row = (int64_t)nx * p + (D == 3 ? plane * z0 : 0);
+                in = across;
+            } else {
+                row = plane * p;
+                in = across;
+            }
+            T w;
+            if constexpr (D == 2 || AX == 2) {             // within a row or plane: 32-bit byte offsets
+                const uint32_t off = (uint32_t)in * E;
+                pa[q] = *(const T *)((const char *)(a + row) + off);
+                w = *(const T *)((const char *)(ud + row) + off);
+                pl[q] = *(const T *)((const char *)(lam + row) + off);
+            } else {
+                pa[q] = a[row + in];
+                w = ud[row + in];
+                pl[q] = lam[row + in];
+            }
+            pw[q] = vertical(ax) ? (ghost ? -w : w) - vs : w;
         }
     };
     auto publish = [&](auto ax, const T *pa, const T *pw, const T *pl) {
         constexpr int AX = decltype(ax)::value, NL = G::lines(AX), HL = G::extent(AX) + 10, NH = HL * NL;
+        constexpr int R = AX == 0 ? XR : (AX == 1 ? YR : ZR);
 #pragma unroll
-        for (int q = 0; q < (NH + NT - 1) / NT; ++q) {
-            const int i = tid + q * NT;
-            if (i < NH) {
+        for (int q = 0; q < R; ++q) {
+            int line, c;
+            place(ax, q, line, c);
+            if (AX == 0 ? (c < HL && line < NL) : c < HL) {
+                const int i = AX == 0 ? line * HL + c : c * NL + line;
                 sS[i] = pa[q];
                 sS[NH + i] = pw[q];
                 sS[2 * NH + i] = pl[q];
@@ -585,32 +617,52 @@ __global__ void __launch_bounds__(NT, BLOCKS) k_adj_stage(AdjDev A, const T *__r
         constexpr int SI = AX == 0 ? 1 : NL;                  // stride between positions of a line
         const int o = origin(ax), n = length(ax);
         const bool wall_ax = vertical(ax) && walls;
-        T fw[ROUNDS][6];
+        // each face reads its stencil from the upwind end and stores its
+        // products in that order by address: slot s of face f at byte
+        // at0 + s at1 (slot 5, the node beyond the downwind end, is zero)
+        T fw[ROUNDS][5];
+        uint32_t at0[ROUNDS], at1[ROUNDS];
+        bool live[ROUNDS];
+        auto S = [&](uint32_t off, int c) { return *(const T *)((const char *)sS + off + c * E); };
+        auto P = [&](uint32_t off) -> T & { return *(T *)((char *)sP + off); };
 #pragma unroll
         for (int q = 0; q < ROUNDS; ++q) {
             const int f = tid + q * NT;
-            int line, i;
-            split(ax, f, NF, line, i);
-            const int j = o - 3 + i;                          // with walls faces exist for 0 <= j <= n - 2
-            if (f >= NF * NL || (wall_ax && (j < 0 || j > n - 2))) continue;   // else never gathered
-            const T *pa = sS + (AX == 0 ? line * HL + i : i * NL + line), *pw = pa + NH, *pl = pw + NH;
-            T av[6], wv[6], fa[6];
+            const int line = AX == 0 ? f / NF : lane, i = AX == 0 ? f % NF : wave + q * WAVES;
+            const int j = o - 3 + i;
+            live[q] = false;
+            if (AX == 0 ? f >= NF * NL : i >= NF) continue;
+            if (wall_ax && (j < 0 || j > n - 2)) {            // no such face: adds nothing to a node
 #pragma unroll
-            for (int s = 0; s < 6; ++s) {
-                av[s] = pa[s * SI];
-                wv[s] = pw[s * SI];
+                for (int s = 0; s < 6; ++s) sP[s * NP + f] = (T)0;
+                continue;
             }
-            const T pb = scale * (pl[3 * SI] - pl[2 * SI]);
-            face_vjp<T>(av, wv, pb, kap, eps, fa, fw[q]);
+            live[q] = true;
+            const uint32_t base = (uint32_t)(AX == 0 ? line * HL + i : i * NL + line) * E;
+            const bool pos = (S(base, NH + 2 * SI) + S(base, NH + 3 * SI)) >= (T)0;
+            const T pb = scale * (S(base, 2 * NH + 3 * SI) - S(base, 2 * NH + 2 * SI));
+            const uint32_t step = pos ? (uint32_t)(SI * E) : (uint32_t)(-SI * E);
+            uint32_t nd = pos ? base : base + 5 * SI * E;
+            T a5[5], w5[5], fa[5];
 #pragma unroll
-            for (int s = 0; s < 6; ++s) sP[s * NP + f] = fa[s];
+            for (int s = 0; s < 5; ++s, nd += step) {
+                a5[s] = S(nd, 0);
+                w5[s] = S(nd, NH);
+            }
+            face_vjp<T>(a5, w5, pb, pos ? kap : -kap, eps12, fa, fw[q]);
+            at0[q] = (uint32_t)f * E + (pos ? 0u : (uint32_t)(5 * NP * E));
+            at1[q] = pos ? (uint32_t)(NP * E) : (uint32_t)(-NP * E);
+            uint32_t to = at0[q];
+#pragma unroll
+            for (int s = 0; s < 5; ++s, to += at1[q]) P(to) = fa[s];
+            P(to) = (T)0;
         }
         __syncthreads();
         // wall images reach only rows m <= 1 (the image -1 - m feeds faces 0
         // and 1) and m >= n - 2 (the image 2 n - 1 - m feeds faces n - 3 and
         // n - 2); tiles clear of both take the node itself only (the same sum:
         // the skipped images add nothing)
-        const int nimg = (wall_ax && (o < 2 || o + TD > n - 2)) ? 3 : 1;
+        const bool images = wall_ax && (o < 2 || o + TD > n - 2);
         auto gather = [&](auto &&add) {
 #pragma unroll
             for (int e = 0; e < PER; ++e) {
@@ -619,14 +671,20 @@ __global__ void __launch_bounds__(NT, BLOCKS) k_adj_stage(AdjDev A, const T *__r
                 if (!in_grid(lx, ly, lz)) continue;
                 const int l = AX == 0 ? lx : (AX == 1 ? ly : lz), m = o + l;
                 const int line = AX == 0 ? ly + TY * lz : (AX == 1 ? lx + TX * lz : lx + TX * ly);
-                for (int im = 0; im < nimg; ++im) {
-                    const int p = im == 0 ? m : (im == 1 ? -1 - m : 2 * n - 1 - m);
+#pragma unroll
+                for (int s = 0; s < 6; ++s) {                 // face m - s + 2 reads the node in slot s
+                    const int i = l - s + 5;
+                    add(e, false, sP[s * NP + (AX == 0 ? line * NF + i : i * NL + line)]);
+                }
+                if (!images) continue;
+                for (int im = 1; im < 3; ++im) {
+                    const int p = im == 1 ? -1 - m : 2 * n - 1 - m;
 #pragma unroll
                     for (int s = 0; s < 6; ++s) {
                         const int jf = p - s + 2;             // face whose slot s reads position p
-                        if (wall_ax && (jf < 0 || jf > n - 2)) continue;
+                        if (jf < 0 || jf > n - 2) continue;
                         const int i = jf - (o - 3);
-                        add(e, im != 0, sP[s * NP + (AX == 0 ? line * NF + i : i * NL + line)]);
+                        add(e, true, sP[s * NP + (AX == 0 ? line * NF + i : i * NL + line)]);
                     }
                 }
             }
@@ -636,10 +694,10 @@ __global__ void __launch_bounds__(NT, BLOCKS) k_adj_stage(AdjDev A, const T *__r
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < ROUNDS; ++q) {
-            const int f = tid + q * NT;
-            if (f >= NF * NL) continue;
+            if (!live[q]) continue;
+            uint32_t to = at0[q];
 #pragma unroll
-            for (int s = 0; s < 6; ++s) sP[s * NP + f] = fw[q][s];
+            for (int s = 0; s < 5; ++s, to += at1[q]) P(to) = fw[q][s];
         }
         __syncthreads();
         gather([&](int e, bool ghost, T p) {
@@ -656,11 +714,7 @@ __global__ void __launch_bounds__(NT, BLOCKS) k_adj_stage(AdjDev A, const T *__r
     constexpr integral_constant<int, 0> X{};
     constexpr integral_constant<int, 1> Y{};
     constexpr integral_constant<int, 2> Z{};
-    auto count = [](int v) constexpr { return (v + NT - 1) / NT; };
-    T ax_a[count((TX + 10) * G::lines(0))], ax_w[count((TX + 10) * G::lines(0))], ax_l[count((TX + 10) * G::lines(0))];
-    T ay_a[count((TY + 10) * G::lines(1))], ay_w[count((TY + 10) * G::lines(1))], ay_l[count((TY + 10) * G::lines(1))];
-    constexpr int LZ = D == 3 ? G::lines(2) : 1;
-    T az_a[count((TZ + 10) * LZ)], az_w[count((TZ + 10) * LZ)], az_l[count((TZ + 10) * LZ)];
+    T ax_a[XR], ax_w[XR], ax_l[XR], ay_a[YR], ay_w[YR], ay_l[YR], az_a[ZR], az_w[ZR], az_l[ZR];
     load(X, ax_a, ax_w, ax_l);
     load(Y, ay_a, ay_w, ay_l);
     if constexpr (D == 3) load(Z, az_a, az_w, az_l);
@@ -747,8 +801,8 @@ hipError_t adjoint_t(const AdjDev &A, const lbw_launch &l, hipStream_t st) {
     // work-items (then, and with variant 1, the two-kernel form: the same sums
     // in the same order, the same bits)
     constexpr bool f32 = sizeof(T) == 4;
-    constexpr int TX = D == 2 ? (f32 ? 64 : 32) : 16, TY = D == 2 ? 8 : 4, TZ = D == 2 ? 1 : 4;
-    constexpr int NT = D == 2 && f32 ? 512 : 256, BLOCKS = D == 2 ? 4 : (f32 ? 5 : 3);
+    constexpr int TX = D == 2 ? 64 : 16, TY = D == 2 ? 8 : 4, TZ = D == 2 ? 1 : 4;
+    constexpr int NT = D == 2 ? 512 : 256, BLOCKS = D == 2 ? 4 : (f32 ? 5 : 3);
     const int64_t tiles = (int64_t)((A.r.nx + TX - 1) / TX) * ((A.r.ny + TY - 1) / TY) *
                           (D == 3 ? (A.r.nz + TZ - 1) / TZ : 1);
     if (l.variant != 1 && tiles * NT < ((int64_t)1 << 32)) {
