@@ -232,6 +232,15 @@ __global__ void __launch_bounds__(256) k_adj_face(AdjDev A, const T *__restrict_
 // Reverse of streaming, collision and moments at node k given the node's
 // total velocity adjoint ub (transport part included); writes fbar and
 // returns the node's contribution to cbar through the force.
+//
+// With f* = f - omega (f - feq(rho, u)) + G(u, F), g_i = w_i fsb_i (fsb the
+// adjoint of f*) and its moments M0 = sum g, M1 = sum g c, M2 = sum g c c,
+//   sum_i dfeq_i/drho fsb_i = M0 + 3 M1.u + 9/2 u.M2 u - 3/2 u.u M0,
+//   sum_i dfeq_i/du   fsb_i = rho V,  V = 3 M1 + 9 M2 u - 3 u M0,
+//   sum_i dG_i/dF     fsb_i = guo V,  sum_i dG_i/du fsb_i = guo (9 M2 F - 3 F M0),
+// the sums taken over pairs of opposite directions: vector issue bounded the
+// stage this ends (2D 536 of its 1072 instructions a node with the terms
+// written out per direction).
 template <int Q, typename T, bool SH>
 __device__ __forceinline__ T collide_reverse_node(const AdjDev &A, int64_t k, int x, int y, int z,
                                                   const T ubt[3]) {
@@ -239,13 +248,32 @@ __device__ __forceinline__ T collide_reverse_node(const AdjDev &A, int64_t k, in
     constexpr int D = L::D;
     const RunDev &r = A.r;
     const T *fbn = (const T *)A.fbar_next;
+    // the node's neighbours one step down (0) and up (1) each axis, and the
+    // walls they lie beyond
+    const int64_t nx = r.nx, plane = nx * r.ny;
+    const int64_t sx[2] = {x == 0 ? nx - 1 : -1, x == r.nx - 1 ? 1 - nx : 1};
+    const int64_t sy[2] = {y == 0 ? plane - nx : -nx, y == r.ny - 1 ? nx - plane : nx};
+    const int64_t sz[2] = {z == 0 ? r.N - plane : -plane, z == r.nz - 1 ? plane - r.N : plane};
+    const int v = D == 2 ? y : z, nv = D == 2 ? r.ny : r.nz;
+    const bool low = !r.vper && v == 0, high = !r.vper && v == nv - 1;
     T fi[Q], fsb[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         // forward streaming sent f*_i(x) to slot i of x + c_i, or to slot
-        // opp(i) of x across a wall: pull the adjoint from there
-        const int64_t dst = displaced<D>(r, x, y, z, L::cx[i], L::cy[i], L::cz[i]);
-        fsb[i] = dst >= 0 ? fbn[(int64_t)i * r.N + dst] : fbn[(int64_t)L::opp[i] * r.N + k];
+        // opp(i) of x across a wall: pull the adjoint from there (a load of
+        // the wrapped node stands in until the wall's own below)
+        int64_t n = k;
+        if (L::cx[i]) n += sx[L::cx[i] > 0];
+        if (L::cy[i]) n += sy[L::cy[i] > 0];
+        if (D == 3 && L::cz[i]) n += sz[L::cz[i] > 0];
+        fsb[i] = (fbn + (int64_t)i * r.N)[n];
+    }
+    if (low || high) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const int cv = D == 2 ? L::cy[i] : L::cz[i];
+            if (cv && (cv < 0 ? low : high)) fsb[i] = (fbn + (int64_t)L::opp[i] * r.N)[k];
+        }
     }
     T F[3], u[3] = {0, 0, 0}, rho;
     lbm_force<D, T>(r, (const T *)A.c_n, nullptr, k, F);
@@ -263,42 +291,52 @@ __device__ __forceinline__ T collide_reverse_node(const AdjDev &A, int64_t k, in
         T drho;
         lbm_rho_u<Q, T, SH>(fi, F, rho, drho, u);
     }
-    const T usq = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
     const T omega = (T)r.omega, guo = (T)r.guo;
-    T ub[3] = {ubt[0], ubt[1], ubt[2]}, Fb[3] = {0, 0, 0}, rb = 0;
-    T *fb = (T *)A.fbar;
+    T m0 = (T)L::w[0] * fsb[0], m1[3] = {0, 0, 0}, m2[3][3] = {};
 #pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        const T w = (T)L::w[i];
-        const T c[3] = {(T)L::cx[i], (T)L::cy[i], (T)L::cz[i]};
-        const T cu = c[0] * u[0] + c[1] * u[1] + c[2] * u[2];
-        const T cF = c[0] * F[0] + c[1] * F[1] + c[2] * F[2];
-        const T poly = (T)3 * cu + (T)4.5 * cu * cu - (T)1.5 * usq;
-        // f* = f - omega (f - feq(rho, u)) + G(u, F)
-        const T eb = omega * fsb[i];      // adjoint of feq_i
-        const T gb = fsb[i];              // adjoint of G_i
-        rb += eb * w * ((T)1 + poly);
+    for (int i = 1; i < Q; ++i) {
+        const int o = L::opp[i];
+        if (o < i) continue;
+        const int c[3] = {L::cx[i], L::cy[i], L::cz[i]};
+        const T w = (T)L::w[i], sum = w * (fsb[i] + fsb[o]), dif = w * (fsb[i] - fsb[o]);
+        m0 += sum;
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            ub[d] += eb * w * rho * ((T)3 * c[d] + (T)9 * cu * c[d] - (T)3 * u[d]) +
-                     gb * guo * w * ((T)-3 * F[d] + (T)9 * c[d] * cF);
-            Fb[d] += gb * guo * w * ((T)3 * (c[d] - u[d]) + (T)9 * cu * c[d]);
+        for (int d = 0; d < D; ++d) {
+            if (c[d]) m1[d] += c[d] > 0 ? dif : -dif;
+#pragma unroll
+            for (int e = d; e < D; ++e)
+                if (c[d] && c[e]) m2[d][e] += c[d] * c[e] > 0 ? sum : -sum;
         }
-        fi[i] = ((T)1 - omega) * fsb[i];
+    }
+    T V[3] = {0, 0, 0}, ub[3] = {0, 0, 0}, Vu = 0, Mu = 0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        T Au = 0, AF = 0;
+#pragma unroll
+        for (int e = 0; e < D; ++e) {
+            const T m = d < e ? m2[d][e] : m2[e][d];
+            Au += m * u[e];
+            AF += m * F[e];
+        }
+        V[d] = (T)3 * (m1[d] - u[d] * m0) + (T)9 * Au;
+        ub[d] = ubt[d] + (omega * rho * V[d] + guo * ((T)9 * AF - (T)3 * F[d] * m0));
+        Vu += V[d] * u[d];
+        Mu += m1[d] * u[d];
     }
     // u = (m + F/2) / rho, m = sum f c, rho = sum f (+1 when shifted)
-    T mb[3];
+    T rb = omega * (m0 + ((T)0.5 * Vu + (T)1.5 * Mu)), mb[3] = {0, 0, 0};
     const T irho = rcp<T>(rho);
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
+    for (int d = 0; d < D; ++d) {
         mb[d] = ub[d] * irho;
-        Fb[d] += (T)0.5 * mb[d];
         rb -= mb[d] * u[d];
     }
+    const T Fbv = guo * V[D - 1] + (T)0.5 * mb[D - 1];
+    T *fb = (T *)A.fbar;
 #pragma unroll
     for (int i = 0; i < Q; ++i)
-        fb[(int64_t)i * r.N + k] = fi[i] + (rb + mb[0] * (T)L::cx[i] + mb[1] * (T)L::cy[i] + mb[2] * (T)L::cz[i]);
-    return -(T)r.gp_c * Fb[D - 1];
+        (fb + (int64_t)i * r.N)[k] = ((T)1 - omega) * fsb[i] + (rb + cdot<Q>(i, mb[0], mb[1], mb[2]));
+    return -(T)r.gp_c * Fbv;
 }
 
 // ---------------------------------------------------------------------------
