@@ -763,9 +763,19 @@ int lbw_replay(lbw_handle *h, int32_t run, int32_t n, void *const *c_out, void *
             return fail(LBW_ERR_INVAL, "NULL buffer for replayed step %d", i);
     // fused: step i reads C from c_out[i] and writes it straight to c_out[i + 1]
     // (the last step to the run's own buffer), so only the first is copied;
-    // needs the C buffers to differ from step to step
+    // needs those two to lie clear of each other and of what the step records
+    const size_t es = elem_size(h->precision), fb = h->run[run].N * es, cb = h->run[run].ncls * fb;
+    auto clear = [](const void *a, size_t na, const void *b, size_t nb) {
+        return (uintptr_t)a + na <= (uintptr_t)b || (uintptr_t)b + nb <= (uintptr_t)a;
+    };
+    auto next = [&](int i) { return i + 1 < n ? c_out[i + 1] : h->run[run].c; };
     bool fused = n > 0 && fused_applies(h);
-    for (int i = 0; i < n && fused; ++i) fused = c_out[i] != (i + 1 < n ? c_out[i + 1] : h->run[run].c);
+    for (int i = 0; i < n && fused; ++i) {
+        fused = clear(c_out[i], cb, next(i), cb);
+        for (const void *c : {(const void *)c_out[i], (const void *)next(i)})
+            fused = fused && clear(c, cb, a1_out[i], cb) && clear(c, cb, a2_out[i], cb) &&
+                    (!lbm || (clear(c, cb, u_out[i], h->dim * fb) && clear(c, cb, rho_out[i], fb)));
+    }
     for (int i = 0; i < n && !rc; ++i) {
         if (!fused || i == 0) rc = lbw_export(h, run, LBW_FIELD_C, c_out[i]);
         if (!rc && lbm) rc = lbw_rebind(h, run, LBW_FIELD_U, u_out[i]);
@@ -773,7 +783,7 @@ int lbw_replay(lbw_handle *h, int32_t run, int32_t n, void *const *c_out, void *
         if (!rc) rc = lbw_rebind(h, run, LBW_FIELD_STAGE1, a1_out[i]);
         if (!rc) rc = lbw_rebind(h, run, LBW_FIELD_STAGE2, a2_out[i]);
         if (rc) break;
-        const FusedStep step{c_out[i], i + 1 < n ? c_out[i + 1] : h->run[run].c, a1_out[i], a2_out[i]};
+        const FusedStep step{c_out[i], next(i), a1_out[i], a2_out[i]};
         rc = fused ? enqueue_step(h, &step) : lbw_step(h, 1);
     }
     // bind the per-step outputs back to the handle's own buffers

@@ -153,3 +153,56 @@ def test_fused_replay_records_what_single_steps_do(precision):
         for k in end:
             assert torch.equal(sol.field(k), end[k]), (shared, k)
         sol.close()
+
+
+@pytest.mark.parametrize("precision", ["fp32_shifted", "fp64"])
+@pytest.mark.parametrize("shape,launch,classes", [((65, 70, 1), {}, 1), ((65, 70, 1), {}, 2), ((70, 41, 1), dict(tile_x=64), 1),
+                                                  ((64, 16, 24), {}, 2)])
+@pytest.mark.parametrize("records", ["apart", "stage1_is_next_c", "stage2_is_c"])
+def test_replay_with_overlapping_records(precision, shape, launch, classes, records):
+    """lbw_replay, where C records coincide with stage records too (the fused
+    transport then gives way to the stages, which copy C): the records written
+    last, the stages and the end state are those of single steps."""
+    nx, ny, nz = shape
+    extra = dict(n_classes=2, vs_class=(1e-3, 4e-3), kappa_class=(1e-3, 2e-3)) if classes == 2 else dict(vs=2e-3, kappa_c=1e-3)
+    cfg = lbw.RunConfig(lattice=9 if nz == 1 else 19, precision=precision, nx=nx, ny=ny, nz=nz, tau=0.6, gp_c=1e-4, **extra)
+    rng = np.random.default_rng(nx)
+    c = rng.uniform(0.2, 1.0, cfg.c_shape)
+    dim = 2 if nz == 1 else 3
+    u = 0.02 * rng.standard_normal((dim,) + cfg.shape)
+    n = 4
+
+    def start():
+        sol = lbw.Solver(cfg)
+        sol.set_launch(**launch)
+        sol.set_field("c", c)
+        sol.init_equilibrium(u=u)
+        return sol
+
+    sol = start()
+    want = []
+    for _ in range(n):
+        before = sol.field("c")
+        sol.step(1)
+        want.append((before, sol.field("stage1"), sol.field("stage2"), sol.field("u")))
+    end = {k: sol.field(k) for k in ("f", "c", "deposit")}
+    sol.close()
+    sol = start()
+    buffers = lambda *s: [torch.empty(s, dtype=sol.dtype, device="cuda") for _ in range(n)]
+    cs, a1, a2, us, rho = (buffers(*cfg.c_shape), buffers(*cfg.c_shape), buffers(*cfg.c_shape), buffers(dim, *cfg.shape),
+                           buffers(*cfg.shape))
+    if records == "stage1_is_next_c":
+        a1[:-1] = cs[1:]
+    elif records == "stage2_is_c":
+        a2 = cs
+    sol.replay(cs, a1, a2, us, rho)
+    torch.cuda.synchronize()
+    for i in range(n):
+        if records != "stage2_is_c":
+            assert torch.equal(cs[i], want[i][0])
+        if records != "stage1_is_next_c" or i == n - 1:
+            assert torch.equal(a1[i], want[i][1])
+        assert torch.equal(a2[i], want[i][2]) and torch.equal(us[i], want[i][3])
+    for k in end:
+        assert torch.equal(sol.field(k), end[k]), k
+    sol.close()
