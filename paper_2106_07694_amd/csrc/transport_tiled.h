@@ -20,7 +20,7 @@
 // instructions a plane in 2D; kept free of branches, masks and 64-bit products
 // it is about 100 (3D 236 -> 130 against 206).  Measured, us per step: 3D
 // 256x256x512 transport 640 -> 610, 97x63x130 45 -> 38, 2D + S 1024x2048 49.6
-// -> 46.3, the 30-run sweep 250 -> 236 in all; double precision unchanged (its
+// -> 46.4, the 30-run sweep 250 -> 236 in all; double precision unchanged (its
 // vector work is twice as long).
 //
 // Arithmetic and wall rules are those of the plain kernels (transport.hip):
@@ -119,16 +119,15 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
                   O_S = O_FY + ((D == 3) ? (TY + 1) * TX : 1), O_GX = O_S + (FS ? SXL * SYL : 1),
                   O_GY = O_GX + (FS ? TY * (TX + 1) : 1),
                   O_END = O_GY + ((FS && D == 3) ? (TY + 1) * TX : 1);
-    __shared__ T smem[O_END + 64];
-    T *const sA = smem + O_A;                   // stage input a, plane with halos
-    T *const sUx = smem + O_UX;                 // x velocity, rows with x halo
-    T *const sUy = smem + O_UY;                 // y velocity, columns with y halo
-    T *const sFx = smem + O_FX;                 // x face fluxes
-    T *const sFy = smem + O_FY;                 // y face fluxes
-    T *const sS = smem + O_S;                   // S plane with a one-cell halo
-    T *const sGx = smem + O_GX;                 // S face fluxes
-    T *const sGy = smem + O_GY;
-
+    // 2D: two sets of them, taken in turn, so that a plane costs one barrier
+    // (DB): the next plane is published into the other set after a plane's
+    // faces, and the barrier between the faces and their use is also the one
+    // between that publication and the next plane's faces.  Transport, us per
+    // step: 1024x2048 with S 46.4 -> 43.9, 2048x2048 68.3 -> 63.6, 1024x1024 in
+    // double precision 44.9 -> 42.2, the 30-run sweep 136 -> 121.
+    constexpr bool DB = D == 2;
+    constexpr int SET = O_END + 64;
+    __shared__ T smem[(DB ? 2 : 1) * SET];
     const int tid = threadIdx.x;
     const int tx = tid % TX, ty = tid / TX;
     const int x0 = bx * TX, y0 = by * TY;
@@ -382,7 +381,22 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
 #pragma unroll
         for (int s = 0; s < SUY; ++s) pY[s] = at<T>(py, offY[s]);
     };
+    auto publish = [&](int set) {
+#pragma unroll
+        for (int s = 0; s < SA; ++s) smem[set * SET + ldsA[s]] = pA[s];
+#pragma unroll
+        for (int s = 0; s < SUX; ++s) smem[set * SET + ldsX[s]] = pX[s];
+#pragma unroll
+        for (int s = 0; s < SUY; ++s) smem[set * SET + ldsY[s]] = pY[s];
+#pragma unroll
+        for (int s = 0; s < SSS; ++s) smem[set * SET + ldsS[s]] = pS[s];
+    };
     prefetch(v0);
+    if constexpr (DB) {
+        publish(0);
+        prefetch(v0 + 1);
+        __syncthreads();
+    }
 
     // The march is unrolled six planes at a time with the window slots
     // rotating: at phase ph, window position m lives in slot (ph + m) % 6,
@@ -410,21 +424,25 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
             for (int s = 0; s < SUY; ++s) asm volatile("" : "+v"(offY[s]));
 #pragma unroll
             for (int s = 0; s < SSS; ++s) asm volatile("" : "+v"(offS[s]));
-            // publish plane v
-#pragma unroll
-            for (int s = 0; s < SA; ++s) smem[ldsA[s]] = pA[s];
-#pragma unroll
-            for (int s = 0; s < SUX; ++s) smem[ldsX[s]] = pX[s];
-#pragma unroll
-            for (int s = 0; s < SUY; ++s) smem[ldsY[s]] = pY[s];
-#pragma unroll
-            for (int s = 0; s < SSS; ++s) smem[ldsS[s]] = pS[s];
-            __syncthreads();
+            const int cur = DB ? ph & 1 : 0;
+            T *const set = smem + cur * SET;
+            T *const sA = set + O_A;                   // stage input a, plane with halos
+            T *const sUx = set + O_UX;                 // x velocity, rows with x halo
+            T *const sUy = set + O_UY;                 // y velocity, columns with y halo
+            T *const sFx = set + O_FX;                 // x face fluxes
+            T *const sFy = set + O_FY;                 // y face fluxes
+            T *const sS = set + O_S;                   // S plane with a one-cell halo
+            T *const sGx = set + O_GX;                 // S face fluxes
+            T *const sGy = set + O_GY;
+            if constexpr (!DB) {
+                publish(0);
+                __syncthreads();
+            }
             // loads, in the order they are consumed (the load counter drains in
             // issue order, so waiting for one waits for all issued before it):
             // this cell's C and the vertical pair at v+4, both used at the end of
-            // this plane, then the next lateral plane, used only after the next
-            // barrier and so in flight across this plane's face computation
+            // this plane, then the next lateral plane (with two sets: after this
+            // plane's faces), used only after the next barrier and so in flight across this plane's face computation
             // (past the chunk it is still a valid plane: the vertical rule maps
             // it inside)
             T cown = (T)0;
@@ -439,7 +457,7 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
                 s_n = at<T>(plane(sin, vn), colb);
                 us_n = at<T>(plane(uv, vn), colb);
             }
-            prefetch(v + 1);
+            if constexpr (!DB) prefetch(v + 1);
 
             // each thread the x face on the left of its cell and (3D) the y
             // face below it; the stage input at the cell is the x stencil's
@@ -449,7 +467,7 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
             // column
             constexpr int XA = (O_A + ((D == 3) ? 3 * AX : 0)) * (int)sizeof(T), XW = O_UX * (int)sizeof(T);
             constexpr int YA = (O_A + 3) * (int)sizeof(T), YW = (O_UY + 3) * (int)sizeof(T);
-            const uint32_t cell = (uint32_t)((ty * AX + tx) * (int)sizeof(T));
+            const uint32_t cell = (uint32_t)((cur * SET + ty * AX + tx) * (int)sizeof(T));
             T a_own;
             {
                 const T *ar = sA + ((D == 3) ? (ty + 3) : 0) * AX + tx;   // nodes tx-3 .. tx+2
@@ -489,7 +507,7 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
             } else if (tid < NEX) {
                 const int fy = tid - ((D == 3) ? TX : 0);
                 sFx[fy * (TX + 1) + TX] =
-                    face6_lds<T, SCHEME, 1, XA, XW>(smem, (uint32_t)((fy * AX + TX) * (int)sizeof(T)), kap, eps);
+                    face6_lds<T, SCHEME, 1, XA, XW>(smem, (uint32_t)((cur * SET + fy * AX + TX) * (int)sizeof(T)), kap, eps);
                 if constexpr (FS) {
                     const T *sr = sS + ((D == 3) ? fy + 1 : 0) * SXL + TX;
                     const T *ur2 = sUx + fy * AX + TX + 2;
@@ -510,6 +528,10 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
             fabove = walls && v == g.nv - 1 ? (T)0 : fabove;
             T gabove = (T)0;
             if constexpr (FS) gabove = (walls && v == g.nv - 1) ? (T)0 : sface(s_c, s_n, us_c, us_n);
+            if constexpr (DB) {
+                publish(1 - cur);       // plane v + 1, its loads in flight since the last plane
+                prefetch(v + 2);
+            }
             __syncthreads();
             T L = -(fabove - fbelow);
             L -= sFx[ty * (TX + 1) + tx + 1] - sFx[ty * (TX + 1) + tx];
@@ -551,9 +573,10 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
                 A(0) = anext;
                 W(0) = wnext;
             }
-            // no barrier here: the next plane's publication writes arrays
-            // last read before the barrier above, and the face arrays read
-            // since are next written after that plane's own first barrier
+            // no barrier here: the next publication writes arrays last read
+            // before the barrier above, and the face arrays read since are next
+            // written after another barrier (the next plane's first one, or
+            // with two sets its only one)
         }
     }
 }
