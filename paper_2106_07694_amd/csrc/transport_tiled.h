@@ -12,8 +12,8 @@
 //     above its cell and carries it down as the face below the next cell
 //     (3D, single precision, WENO5: the stencil's node data instead, each
 //     node's flux and indicators computed once, as the node enters);
-//   * the next plane's global loads are issued before the current plane is
-//     computed (software pipelining).
+//   * the plane after next is loaded while a plane is finished and the next
+//     one is published after its faces (software pipelining, one barrier).
 // What bounds it: instruction issue, vector and scalar alike.  A SIMD issues
 // one of each every four cycles, and the march's scalar work (plane addresses,
 // the vertical rule, masks) once outnumbered its vector work, 200 against 142
@@ -119,15 +119,16 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
                   O_S = O_FY + ((D == 3) ? (TY + 1) * TX : 1), O_GX = O_S + (FS ? SXL * SYL : 1),
                   O_GY = O_GX + (FS ? TY * (TX + 1) : 1),
                   O_END = O_GY + ((FS && D == 3) ? (TY + 1) * TX : 1);
-    // 2D: two sets of them, taken in turn, so that a plane costs one barrier
-    // (DB): the next plane is published into the other set after a plane's
-    // faces, and the barrier between the faces and their use is also the one
-    // between that publication and the next plane's faces.  Transport, us per
-    // step: 1024x2048 with S 46.4 -> 43.9, 2048x2048 68.3 -> 63.6, 1024x1024 in
-    // double precision 44.9 -> 42.2, the 30-run sweep 136 -> 121.
-    constexpr bool DB = D == 2;
+    // Two sets of them, taken in turn, so that a plane costs one barrier: the
+    // next plane is published into the other set after a plane's faces, and the
+    // barrier between the faces and their use is also the one between that
+    // publication and the next plane's faces.  Transport, us per step: 2D
+    // 1024x2048 with S 46.4 -> 43.9, 2048x2048 68.3 -> 63.6, 1024x1024 in double
+    // precision 44.9 -> 42.2, the 30-run sweep 136 -> 121; 3D 256x256x512 615 ->
+    // 598, four classes of 128x128x192 216 -> 212, the smaller grids even.
     constexpr int SET = O_END + 64;
-    __shared__ T smem[(DB ? 2 : 1) * SET];
+    __shared__ T smem[2 * SET];
+
     const int tid = threadIdx.x;
     const int tx = tid % TX, ty = tid / TX;
     const int x0 = bx * TX, y0 = by * TY;
@@ -287,12 +288,13 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
     const T eps12 = (T)(12.0 / 13.0) * eps;
     T aw[6], ww[6];
     T vH[6], vD[6];
-    // the indicators of the window's nodes, per thread in LDS (six-slot rings
-    // that rotate like the window; each thread reads only what it wrote)
-    __shared__ T sE[NV ? 18 * NT : 1];
-    auto EL = [&](int slot) -> T & { return sE[(0 * 6 + slot) * NT + tid]; };
-    auto EC = [&](int slot) -> T & { return sE[(1 * 6 + slot) * NT + tid]; };
-    auto ER = [&](int slot) -> T & { return sE[(2 * 6 + slot) * NT + tid]; };
+    // the indicators of the window's nodes, per thread in LDS (each thread reads
+    // only what it wrote), in rings as long as their nodes wait: a node enters
+    // at position 5, its e_l is last read at position 1, e_c at 2, e_r at 3
+    __shared__ T sE[NV ? 11 * NT : 1];
+    auto EL = [&](int slot) -> T & { return sE[slot * NT + tid]; };
+    auto EC = [&](int slot) -> T & { return sE[(6 + slot % 3) * NT + tid]; };
+    auto ER = [&](int slot) -> T & { return sE[(9 + slot % 2) * NT + tid]; };
     bool vP[6];
     T a_last = (T)0, w_last = (T)0, a_first;
     T fbelow;                                       // face below the first plane
@@ -316,8 +318,8 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
 #pragma unroll
         for (int m = 1; m < 5; ++m) {
             EL(m) = ln[m + 1];
-            EC(m) = cn[m + 1];
-            ER(m) = rn[m + 1];
+            if (m >= 2) EC(m) = cn[m + 1];
+            if (m >= 3) ER(m) = rn[m + 1];
         }
 #pragma unroll
         for (int m = 2; m < 5; ++m) {
@@ -392,11 +394,9 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
         for (int s = 0; s < SSS; ++s) smem[set * SET + ldsS[s]] = pS[s];
     };
     prefetch(v0);
-    if constexpr (DB) {
-        publish(0);
-        prefetch(v0 + 1);
-        __syncthreads();
-    }
+    publish(0);
+    prefetch(v0 + 1);
+    __syncthreads();
 
     // The march is unrolled six planes at a time with the window slots
     // rotating: at phase ph, window position m lives in slot (ph + m) % 6,
@@ -424,7 +424,7 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
             for (int s = 0; s < SUY; ++s) asm volatile("" : "+v"(offY[s]));
 #pragma unroll
             for (int s = 0; s < SSS; ++s) asm volatile("" : "+v"(offS[s]));
-            const int cur = DB ? ph & 1 : 0;
+            const int cur = ph & 1;
             T *const set = smem + cur * SET;
             T *const sA = set + O_A;                   // stage input a, plane with halos
             T *const sUx = set + O_UX;                 // x velocity, rows with x halo
@@ -434,17 +434,12 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
             T *const sS = set + O_S;                   // S plane with a one-cell halo
             T *const sGx = set + O_GX;                 // S face fluxes
             T *const sGy = set + O_GY;
-            if constexpr (!DB) {
-                publish(0);
-                __syncthreads();
-            }
             // loads, in the order they are consumed (the load counter drains in
             // issue order, so waiting for one waits for all issued before it):
             // this cell's C and the vertical pair at v+4, both used at the end of
-            // this plane, then the next lateral plane (with two sets: after this
-            // plane's faces), used only after the next barrier and so in flight across this plane's face computation
-            // (past the chunk it is still a valid plane: the vertical rule maps
-            // it inside)
+            // this plane, which the lateral plane v+2, loaded after its faces, is
+            // in flight past (beyond the chunk it is still a valid plane: the
+            // vertical rule maps it inside)
             T cown = (T)0;
             if (STAGE != 1) cown = at<T>(plane(r.c, v), colb);
             T anext, wnext, snext;
@@ -457,7 +452,6 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
                 s_n = at<T>(plane(sin, vn), colb);
                 us_n = at<T>(plane(uv, vn), colb);
             }
-            if constexpr (!DB) prefetch(v + 1);
 
             // each thread the x face on the left of its cell and (3D) the y
             // face below it; the stage input at the cell is the x stencil's
@@ -528,10 +522,8 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
             fabove = walls && v == g.nv - 1 ? (T)0 : fabove;
             T gabove = (T)0;
             if constexpr (FS) gabove = (walls && v == g.nv - 1) ? (T)0 : sface(s_c, s_n, us_c, us_n);
-            if constexpr (DB) {
-                publish(1 - cur);       // plane v + 1, its loads in flight since the last plane
-                prefetch(v + 2);
-            }
+            publish(1 - cur);           // plane v + 1, its loads in flight since the last plane
+            prefetch(v + 2);
             __syncthreads();
             T L = -(fabove - fbelow);
             L -= sFx[ty * (TX + 1) + tx + 1] - sFx[ty * (TX + 1) + tx];
@@ -573,10 +565,9 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
                 A(0) = anext;
                 W(0) = wnext;
             }
-            // no barrier here: the next publication writes arrays last read
-            // before the barrier above, and the face arrays read since are next
-            // written after another barrier (the next plane's first one, or
-            // with two sets its only one)
+            // no barrier here: the next publication writes the set whose last
+            // readers passed the barrier above, and the face arrays read since
+            // are next written two planes on
         }
     }
 }
