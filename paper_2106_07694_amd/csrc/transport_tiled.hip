@@ -49,6 +49,16 @@ TileShape default_tile(int dim, int precision, const RunDev *runs, int n) {
     return s;
 }
 
+// Estimated us of a step's three stages of a 2D run in single precision:
+// 512 threads to a block, k = ceil(blocks / 256) of them on the busiest CU (up
+// to four run beside each other), `chunk` planes each.  Fitted to 1024x1024 ..
+// 4096x2048, within 5% there: the issue slots of two blocks are filled better by
+// four shorter ones, and one block beyond a multiple of 256 costs a block's time.
+float march2d_us(int64_t k, int chunk) {
+    constexpr float plane[4] = {2.12f, 2.92f, 3.74f, 4.98f}, start[4] = {15.5f, 18.1f, 20.2f, 22.4f};
+    return start[k - 1] + plane[k - 1] * (float)chunk;
+}
+
 // Vertical chunk for runs whose caller chose none: the shortest with which the
 // blocks still start together.  A plane of a march takes 0.7-1.4 us however
 // few blocks there are, so a chip that is not full wants more blocks, down to
@@ -66,6 +76,25 @@ int default_chunk(int dim, int precision, const TileShape &s, const RunDev *runs
         blocks += padded_columns(dim, runs[i], s.tx, s.ty) / (s.tx * s.ty) * planes(dim, runs[i]);
     blocks *= classes;
     constexpr int64_t cus = 256;
+    if (dim == 2 && precision == LBW_FP32_SHIFTED && n == 1) {
+        // 16 waves a CU (below) against the estimate's choice, us per step:
+        // 4096x2048 32 planes 110, 16 planes 100; 300x6000 48 and 42; 1000x3000
+        // 54.6 and 52.4; 2048x2048 63.5 and 62.6; 3000x2000 101.7 and 103.5;
+        // 1024x1280 .. 1024x2048 and 4096x4096 the same chunk
+        int best = 32;
+        float least = 0.f;
+        for (int c = 32; c >= 1; --c) {
+            const int64_t b = padded_columns(dim, runs[0], s.tx, 1) / s.tx * ceil_div(planes(dim, runs[0]), c) * classes;
+            const int64_t k = ceil_div(b * s.tx, 512 * cus);
+            if (k > 4) break;
+            const float us = march2d_us(k, c);
+            if (c == 32 || us < least) {
+                best = c;
+                least = us;
+            }
+        }
+        return best;
+    }
     int64_t full, lo, hi;
     if (dim == 2) {
         full = cus * 16 * 64 / s.tx;
