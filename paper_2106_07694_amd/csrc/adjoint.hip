@@ -28,12 +28,6 @@
 #include "lbm_device.h"
 #include "transport_device.h"
 
-// The one-kernel and the two-kernel form of a reversed stage give the same
-// bits, so multiply-adds are fused only within one source expression (the
-// default fast contraction may also fuse across statements, differently in
-// each kernel).
-#pragma clang fp contract(on)
-
 namespace lbw {
 namespace {
 
@@ -133,9 +127,12 @@ __device__ __forceinline__ void face_vjp(const T a[5], const T w[5], T pb, T kd,
     rcp3(t0 * t0 + (r0 * s0 + eps12), t1 * t1 + (r1 * s1 + eps12), t2 * t2 + (r2 * s2 + eps12), i0, i1, i2);
     const T al0 = i0 * i0, al1 = (T)6 * i1 * i1, al2 = (T)3 * i2 * i2;
     const T iS = rcp<T>(al0 + al1 + al2);
-    const T q0 = (T)(1.0 / 3.0) * h[0] - (T)(7.0 / 6.0) * h[1] + (T)(11.0 / 6.0) * h[2];
-    const T q1 = (T)(5.0 / 6.0) * h[2] - (T)(1.0 / 6.0) * h[1] + (T)(1.0 / 3.0) * h[3];
-    const T q2 = (T)(1.0 / 3.0) * h[2] + (T)(5.0 / 6.0) * h[3] - (T)(1.0 / 6.0) * h[4];
+    // candidates less h_2, from the first differences of h: only q_k - f enters,
+    // which 1 / e_k multiplies, so its rounding is the face's leading error
+    const T y0 = h[1] - h[0], y1 = h[2] - h[1], y2 = h[3] - h[2], y3 = h[4] - h[3];
+    const T q0 = (T)(5.0 / 6.0) * y1 - (T)(1.0 / 3.0) * y0;
+    const T q1 = (T)(1.0 / 6.0) * y1 + (T)(1.0 / 3.0) * y2;
+    const T q2 = (T)(2.0 / 3.0) * y2 - (T)(1.0 / 6.0) * y3;
     const T f = (al0 * q0 + al1 * q1 + al2 * q2) * iS;
     // f = sum al_k q_k / S: df/dq_k = al_k / S, df/dal_k = (q_k - f) / S,
     // dal_k/de_k = -2 al_k / e_k, de_k/dt_k = 2 t_k, de_k/ds_k = 2 (3/13) s_k
