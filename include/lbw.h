@@ -130,7 +130,9 @@ typedef struct {
 typedef struct {
     void *f;           /* Q*N populations (in place, AA order) */
     void *c;           /* N per size class, class after class: C_i */
-    void *c_s1;        /* N per size class: RK stage work buffer */
+    void *c_s1;        /* N per size class: RK stage work buffer (within one
+                          lbw_step call of three or more steps of a 2D run it
+                          may hold C of every other step) */
     void *c_s2;        /* N per size class: RK stage work buffer */
     void *s;           /* N: S (has_s) */
     void *s_tmp;       /* N: S work buffer (has_s) */
@@ -142,7 +144,10 @@ typedef struct {
     size_t scratch_bytes;
 } lbw_buffers;
 
-/* Launch shape of the hot kernels (chosen by the autotuner; 0 = default). */
+/* Launch shape of the hot kernels.  A field never set is chosen by the library:
+ * lbm_block 256, the transport tile and chunk from the grids, and for a small or
+ * medium single 2D run with no tile field set the whole transport of a step in
+ * one launch.  Every tile and chunk gives the same bits. */
 typedef struct {
     int32_t lbm_block;     /* threads per block of the collide-stream kernel */
     int32_t tile_x;        /* transport tile width: 32, 64, 128 (3D) or
@@ -155,7 +160,8 @@ typedef struct {
                               steps (needs a non-null stream; the graph is
                               runtime-owned and rebuilt after lbw_set_launch) */
     int32_t reserved;      /* must be 0 */
-    int32_t tile_rows;     /* transport tile rows (3D): 0 = 256 / tile_x
+    int32_t tile_rows;     /* transport tile rows (3D): 0 with a tile_x set =
+                              256 / tile_x
                               (32x8, 64x4, 128x2 with 256 threads), or 16 with
                               tile_x 32 and 8 with tile_x 64 (512 threads);
                               2D tiles are one row (0 or 1) */
@@ -262,7 +268,9 @@ int lbw_rebind(lbw_handle *h, int32_t run, int32_t field, void *ptr);
  * bound back to the buffers given at creation.  Asynchronous on the handle's
  * stream; the buffers must stay valid until that work has run.  Returns
  * LBW_ERR_INVAL for n < 0 or a NULL array or element where one is needed,
- * LBW_ERR_UNSUPPORTED for a batch (a step advances every run of it). */
+ * LBW_ERR_UNSUPPORTED for a batch (a step advances every run of it).  (Where
+ * a step's transport is one launch, C of step i + 1 is written to c_out[i + 1]
+ * by step i instead of copied, if the records do not overlap.) */
 int lbw_replay(lbw_handle *h, int32_t run, int32_t n, void *const *c_out, void *const *u_out,
                void *const *rho_out, void *const *a1_out, void *const *a2_out);
 
@@ -271,7 +279,11 @@ int lbw_replay(lbw_handle *h, int32_t run, int32_t n, void *const *c_out, void *
  * (sum of the deposit counters of every class), the particle mass and
  * deposited mass m_b of section 4.2.3.
  * Wavefront shuffles, per-block partials, then a fixed-order final pass:
- * the result is bitwise reproducible.  Synchronises the stream.  Returns
+ * the result is bitwise reproducible.  A run's partials (a batch's sums) go
+ * through one of 32 slots of pinned host memory (64 KiB in all, allocated by
+ * the first call and kept by the process) or, when those are taken or the
+ * batch needs more, through the caller's scratch.  Synchronises the stream.
+ * Returns
  * LBW_ERR_NONFINITE if any sum is NaN or Inf (the values are still written). */
 int lbw_reduce(lbw_handle *h, int32_t what, double *out_host);
 

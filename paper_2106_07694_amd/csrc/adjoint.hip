@@ -480,9 +480,10 @@ __global__ void __launch_bounds__(256) k_adj_gather(AdjDev A) {
 // wall hold zeros so that a node adds its six products unchecked.  All the
 // tile's loads are in flight before the first is stored to LDS; LDS holds one
 // axis at a time, and of its products first A, then W (kept in registers
-// meanwhile), so that a CU holds 16 to 32 waves.  us per reverse step: 2D
-// 512x1024 61.5 -> 45 (against the whole set of products in LDS); 3D 64x48x96
-// 81 -> 54 (against the two-kernel form).
+// meanwhile), so that a CU holds 16 to 32 waves (both at once: 2D 0.4% faster,
+// 3D 4% slower).  us per reverse step: 2D 512x1024 61.5 -> 41 (against 32x8 tiles
+// with the whole set of products in LDS); 3D 64x48x96 81 -> 50 (against the
+// two-kernel form).
 // ---------------------------------------------------------------------------
 
 // Stored position of j on a periodic axis, for the at most five cells a line's

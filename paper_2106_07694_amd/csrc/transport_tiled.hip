@@ -189,10 +189,10 @@ hipError_t launch_transport_batched(int dim, int precision, const BatchArgs &b, 
 
 // Grids up to 9 * 2^17 cells (6 * 2^17 in double precision): beyond, three
 // launches of the march fill the chip and the recomputed halo decides.  us per
-// step of transport, fused against march, single precision: 515x1030 20.1, 25.0;
-// 1024x1024 27.7, 29.1; 900x1300 32.9, 36.4; 1024x1280 32.8, 32.1; 1024x1536
-// 36.4, 35.3; double: 256x512 13.5, 18.5; 512x1024 29.7, 30.1; 700x1100 44.3,
-// 47.5; 1024x1024 52.7, 45.0.  A launch shape set by the caller asks for the
+// step of transport, fused against march, single precision: 515x1030 20.0, 27.2;
+// 1024x1024 27.3, 28.2; 900x1300 33.1, 36.3; 1024x1280 32.8, 31.2; 1024x1536
+// 36.4, 34.6; double: 256x512 12.8, 19.1; 512x1024 29.9, 30.6; 700x1100 41.8,
+// 48.0; 1024x1024 52.7, 42.2.  A launch shape set by the caller asks for the
 // march.  One block row per 16 or more grid rows, 65535 at most.
 bool rk3_fused2d_applies(int dim, int precision, const RunDev &r, const lbw_launch &l) {
     const int64_t most = (int64_t)(precision == LBW_FP32_SHIFTED ? 9 : 6) << 17;
