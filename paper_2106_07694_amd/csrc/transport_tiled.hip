@@ -64,10 +64,10 @@ float march2d_us(int64_t k, int chunk) {
 // few blocks there are, so a chip that is not full wants more blocks, down to
 // one plane each; once it is full, shorter chunks only repeat the prologue
 // (seven planes of the vertical stencil).  us per step of transport, measured:
-// 2D 64x128 in double precision 102 at 32 planes, 15 at one; 512x1024 99 at
-// 32, 25 at two; 1024x2048 102 at 32, 46 at eight, 48 at four; 3D 64x48x96 250
-// at 64, 29 at three; 128x128x192 251 at 64, 78 at eight; 256x256x400 620 at
-// 64, 528 at 24, 572 at eight.  Full means 16 waves a CU in 2D and the blocks
+// 2D 64x128 in double precision 102 at 32 planes, 15 at one; 1024x1024 84 at
+// 32, 28 at four; 1024x2048 85 at 32, 41 at eight, 42 at four; 3D 64x48x96 89
+// at 24, 26 at three; 128x128x192 93 at 24, 73 at eight; 256x256x400 (an earlier
+// form) 620 at 64, 528 at 24, 572 at eight.  Full means 16 waves a CU in 2D and the blocks
 // that fit beside each other in 3D (registers: three of 64x8 in single
 // precision, two in double).
 int default_chunk(int dim, int precision, const TileShape &s, const RunDev *runs, int n, int classes) {
