@@ -28,6 +28,12 @@
 #include "lbm_device.h"
 #include "transport_device.h"
 
+// The one-kernel and the two-kernel form of a reversed stage give the same
+// bits, so multiply-adds are fused only within one source expression: the
+// default fast contraction also fuses across statements, differently in each
+// kernel.  What is better fused is written as one expression.
+#pragma clang fp contract(on)
+
 namespace lbw {
 namespace {
 
@@ -113,9 +119,6 @@ __device__ __forceinline__ void rcp3(double e0, double e1, double e2, double &i0
 // written out and the upwind side selected among the results.
 template <typename T>
 __device__ __forceinline__ void face_vjp(const T a[5], const T w[5], T pb, T kd, T eps12, T A[5], T W[5]) {
-    T h[5];
-#pragma unroll
-    for (int s = 0; s < 5; ++s) h[s] = w[s] * a[s];
     const T g0 = a[1] - a[0], g1 = a[2] - a[1], g2 = a[3] - a[2], g3 = a[4] - a[3];
     const T t0 = g1 - g0, t1 = g2 - g1, t2 = g3 - g2;
     const T s0 = t0 + (T)2 * g1;          // a0 - 4 a1 + 3 a2
@@ -129,22 +132,23 @@ __device__ __forceinline__ void face_vjp(const T a[5], const T w[5], T pb, T kd,
     const T iS = rcp<T>(al0 + al1 + al2);
     // candidates less h_2, from the first differences of h: only q_k - f enters,
     // which 1 / e_k multiplies, so its rounding is the face's leading error
-    const T y0 = h[1] - h[0], y1 = h[2] - h[1], y2 = h[3] - h[2], y3 = h[4] - h[3];
+    const T y0 = w[1] * a[1] - w[0] * a[0], y1 = w[2] * a[2] - w[1] * a[1];
+    const T y2 = w[3] * a[3] - w[2] * a[2], y3 = w[4] * a[4] - w[3] * a[3];
     const T q0 = (T)(5.0 / 6.0) * y1 - (T)(1.0 / 3.0) * y0;
     const T q1 = (T)(1.0 / 6.0) * y1 + (T)(1.0 / 3.0) * y2;
     const T q2 = (T)(2.0 / 3.0) * y2 - (T)(1.0 / 6.0) * y3;
-    const T f = (al0 * q0 + al1 * q1 + al2 * q2) * iS;
-    // f = sum al_k q_k / S: df/dq_k = al_k / S, df/dal_k = (q_k - f) / S,
+    const T fS = al0 * q0 + al1 * q1 + al2 * q2;
+    // f = fS / S: df/dq_k = al_k / S, df/dal_k = (q_k - f) / S,
     // dal_k/de_k = -2 al_k / e_k, de_k/dt_k = 2 t_k, de_k/ds_k = 2 (3/13) s_k
     const T p = pb * iS;
     const T b0 = al0 * p, b1 = al1 * p, b2 = al2 * p;
-    const T m0 = (q0 - f) * b0 * ((T)-4 * i0);
-    const T m1 = (q1 - f) * b1 * ((T)-4 * i1);
-    const T m2 = (q2 - f) * b2 * ((T)-4 * i2);
+    const T m0 = (q0 - fS * iS) * b0 * ((T)-4 * i0);
+    const T m1 = (q1 - fS * iS) * b1 * ((T)-4 * i1);
+    const T m2 = (q2 - fS * iS) * b2 * ((T)-4 * i2);
     const T v0 = r0 * m0, v1 = r1 * m1, v2 = r2 * m2;        // of s_k
-    const T d0 = t0 * m0 + v0, u1 = t1 * m1, d2 = t2 * m2 + v2;   // of t_0, t_1, t_2 (s_0, s_2 hold t_0, t_2)
-    const T c1 = (d0 + (T)2 * v0) + (v1 - u1);               // of g_1; of g_0 -d0, of g_3 d2
-    const T c2 = ((v1 + u1) - (d2 + (T)2 * v2)) - kd * pb;   // of g_2
+    const T d0 = t0 * m0 + v0, d2 = t2 * m2 + v2;            // of t_0, t_2 (s_0, s_2 hold them); of t_1 t_1 m_1
+    const T c1 = (d0 + (T)2 * v0) + (v1 - t1 * m1);          // of g_1; of g_0 -d0, of g_3 d2
+    const T c2 = ((v1 + t1 * m1) - (d2 + (T)2 * v2)) - kd * pb;   // of g_2
     W[0] = (T)(1.0 / 3.0) * b0;
     W[1] = (T)(-7.0 / 6.0) * b0 - (T)(1.0 / 6.0) * b1;
     W[2] = (T)(11.0 / 6.0) * b0 + ((T)(5.0 / 6.0) * b1 + (T)(1.0 / 3.0) * b2);
@@ -228,7 +232,7 @@ __global__ void __launch_bounds__(256) k_adj_face(AdjDev A, const T *__restrict_
 // ---------------------------------------------------------------------------
 // Reverse of streaming, collision and moments at node k given the node's
 // total velocity adjoint ub (transport part included); writes fbar and
-// returns the node's contribution to cbar through the force.
+// returns the adjoint of the force's vertical component.
 //
 // With f* = f - omega (f - feq(rho, u)) + G(u, F), g_i = w_i fsb_i (fsb the
 // adjoint of f*) and its moments M0 = sum g, M1 = sum g c, M2 = sum g c c,
@@ -295,14 +299,14 @@ __device__ __forceinline__ T collide_reverse_node(const AdjDev &A, int64_t k, in
         const int o = L::opp[i];
         if (o < i) continue;
         const int c[3] = {L::cx[i], L::cy[i], L::cz[i]};
-        const T w = (T)L::w[i], sum = w * (fsb[i] + fsb[o]), dif = w * (fsb[i] - fsb[o]);
-        m0 += sum;
+        const T w = (T)L::w[i], sum = fsb[i] + fsb[o], dif = fsb[i] - fsb[o];
+        m0 += w * sum;
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-            if (c[d]) m1[d] += c[d] > 0 ? dif : -dif;
+            if (c[d]) m1[d] += (c[d] > 0 ? w : -w) * dif;
 #pragma unroll
             for (int e = d; e < D; ++e)
-                if (c[d] && c[e]) m2[d][e] += c[d] * c[e] > 0 ? sum : -sum;
+                if (c[d] && c[e]) m2[d][e] += (c[d] * c[e] > 0 ? w : -w) * sum;
         }
     }
     T V[3] = {0, 0, 0}, ub[3] = {0, 0, 0}, Vu = 0, Mu = 0;
@@ -328,12 +332,11 @@ __device__ __forceinline__ T collide_reverse_node(const AdjDev &A, int64_t k, in
         mb[d] = ub[d] * irho;
         rb -= mb[d] * u[d];
     }
-    const T Fbv = guo * V[D - 1] + (T)0.5 * mb[D - 1];
     T *fb = (T *)A.fbar;
 #pragma unroll
     for (int i = 0; i < Q; ++i)
         (fb + (int64_t)i * r.N)[k] = ((T)1 - omega) * fsb[i] + (rb + cdot<Q>(i, mb[0], mb[1], mb[2]));
-    return -(T)r.gp_c * Fbv;
+    return guo * V[D - 1] + (T)0.5 * mb[D - 1];
 }
 
 // ---------------------------------------------------------------------------
@@ -345,7 +348,14 @@ __device__ __forceinline__ T collide_reverse_node(const AdjDev &A, int64_t k, in
 // The per-node end of a reversed RK stage, given the node's gathered face
 // products (abar, the velocity parts ubs and the settling part vsp): the
 // absorbing bottom face, the deposit update, the RK combination and, after the
-// last stage, the collision and moments in reverse.
+// last stage, the collision and moments in reverse.  With A_s the transpose of L
+// in stage s, the stage adjoints are a2b = 2/3 cbn + A_3 and a1b = 1/4 a2b + A_2,
+// and cbar = 1/3 cbn + 3/4 a2b + a1b + A_1 = cbn + (A_3 + A_2 + A_1): summed in
+// the last form, the small terms first (cbar holds them between the stages), so
+// that a step rounds a value of cbar's size once, and thirds and quarters of it
+// need not add up again (single precision, error of the gradient against 64
+// bits, mean of four seeds: 512x1024 over 100 steps 8.3e-7 -> 5.3e-7, 64x48x96
+// over 20 steps 5.0e-7 -> 3.0e-7).
 template <int Q, typename T, bool SH, int STAGE>
 __device__ __forceinline__ void gather_finish(const AdjDev &A, int64_t k, int x, int y, int z, T abar,
                                               const T ubs[3], double vsp) {
@@ -370,42 +380,38 @@ __device__ __forceinline__ void gather_finish(const AdjDev &A, int64_t k, int x,
     const T *cbn = (const T *)A.cbar_next;
     T *cb = (T *)A.cbar;
     if constexpr (STAGE == 3) {
-        T a2b = (T)(2.0 / 3.0) * cbn[k] + abar;
-        T cbv = cbn[k] * (T)(1.0 / 3.0);
+        T da = abar, dc = abar;
         if (bottom) {
             // D+ = D + vs (C/6 + a1/6 + 2 a2/3)
-            a2b += (T)(2.0 / 3.0 * r.vs * db);
-            cbv += (T)(r.vs / 6.0 * db);
+            da += (T)(2.0 / 3.0 * r.vs * db);
+            dc += (T)(5.0 / 6.0 * r.vs * db);
             vsp += db * ((double)((const T *)A.c_n)[k] / 6.0 + (double)((const T *)A.a1)[k] / 6.0 +
                          2.0 / 3.0 * (double)((const T *)A.a2)[k]);
         }
-        ((T *)A.abar2)[k] = a2b;
-        cb[k] = cbv;
+        ((T *)A.abar2)[k] = (T)(2.0 / 3.0) * cbn[k] + da;
+        cb[k] = dc;               // cbar - cbn so far
 #pragma unroll
         for (int d = 0; d < D; ++d) ub[(int64_t)d * r.N + k] = ubs[d];
         A.vs_part[k] += vsp;      // accumulates across steps until summed
     } else if constexpr (STAGE == 2) {
-        const T a2b = ((const T *)A.abar2)[k];
-        T a1b = (T)0.25 * a2b + abar;
-        if (bottom) a1b += (T)(r.vs / 6.0 * db);
-        ((T *)A.abar1)[k] = a1b;
-        cb[k] += (T)0.75 * a2b;
+        if (bottom) abar += (T)(r.vs / 6.0 * db);
+        ((T *)A.abar1)[k] = (T)0.25 * ((const T *)A.abar2)[k] + abar;
+        cb[k] += abar;
 #pragma unroll
         for (int d = 0; d < D; ++d) ub[(int64_t)d * r.N + k] += ubs[d];
         A.vs_part[k] += vsp;
     } else {
-        T cbv = cb[k] + ((const T *)A.abar1)[k] + abar;
         A.vs_part[k] += vsp;
-        if (A.frozen) {
-            cb[k] = cbv;
-        } else {
+        T dc = cb[k] + abar;
+        if (!A.frozen) {
             // last stage reversed: the node's velocity adjoint is complete, so
             // the collision and moments are reversed here as well
             T ut[3] = {0, 0, 0};
 #pragma unroll
             for (int d = 0; d < D; ++d) ut[d] = ub[(int64_t)d * r.N + k] + ubs[d];
-            cb[k] = cbv + collide_reverse_node<Q, T, SH>(A, k, x, y, z, ut);
+            dc -= (T)r.gp_c * collide_reverse_node<Q, T, SH>(A, k, x, y, z, ut);
         }
+        cb[k] = cbn[k] + dc;
     }
 }
 
