@@ -92,19 +92,30 @@ __global__ void __launch_bounds__(256) k_adj_moments(AdjDev a) {
 template <typename T> __device__ __forceinline__ T rcp(T x) { return (T)1 / x; }
 template <> __device__ __forceinline__ float rcp<float>(float x) { return __builtin_amdgcn_rcpf(x); }
 
-// Reciprocals of three indicators: one division for all of them in double
-// precision (a division is some ten instructions there), the hardware
-// reciprocal of each in single.
-__device__ __forceinline__ void rcp3(float e0, float e1, float e2, float &i0, float &i1, float &i2) {
+// Reciprocals of three indicators, none of them below `least` (the same for
+// every face): one division for all of them in double precision (a division is
+// some ten instructions there) as long as their products stay in range, which
+// indicators from 1e-100 on and with a product up to 1e200 do; a smaller
+// weno_eps takes a division each.  In single precision the hardware reciprocal
+// of each.
+__device__ __forceinline__ void rcp3(float e0, float e1, float e2, float, float &i0, float &i1, float &i2) {
     i0 = rcp<float>(e0);
     i1 = rcp<float>(e1);
     i2 = rcp<float>(e2);
 }
-__device__ __forceinline__ void rcp3(double e0, double e1, double e2, double &i0, double &i1, double &i2) {
-    const double e12 = e1 * e2, i = 1.0 / (e0 * e12);
-    i0 = i * e12;
-    i1 = i * (e0 * e2);
-    i2 = i * (e0 * e1);
+__device__ __forceinline__ void rcp3(double e0, double e1, double e2, double least, double &i0, double &i1,
+                                     double &i2) {
+    const double e12 = e1 * e2, e = e0 * e12;
+    if (least >= 1e-100 && e <= 1e200) {
+        const double i = 1.0 / e;
+        i0 = i * e12;
+        i1 = i * (e0 * e2);
+        i2 = i * (e0 * e1);
+    } else {
+        i0 = 1.0 / e0;
+        i1 = 1.0 / e1;
+        i2 = 1.0 / e2;
+    }
 }
 
 // Products of one face's local Jacobian with its adjoint pb, for the five
@@ -127,8 +138,10 @@ __device__ __forceinline__ void face_vjp(const T a[5], const T w[5], T pb, T kd,
     constexpr T k = (T)(3.0 / 13.0);
     const T r0 = k * s0, r1 = k * s1, r2 = k * s2;
     T i0, i1, i2;
-    rcp3(t0 * t0 + (r0 * s0 + eps12), t1 * t1 + (r1 * s1 + eps12), t2 * t2 + (r2 * s2 + eps12), i0, i1, i2);
-    const T al0 = i0 * i0, al1 = (T)6 * i1 * i1, al2 = (T)3 * i2 * i2;
+    rcp3(t0 * t0 + (r0 * s0 + eps12), t1 * t1 + (r1 * s1 + eps12), t2 * t2 + (r2 * s2 + eps12), eps12, i0, i1,
+         i2);
+    // weights in the ratio 1 : 6 : 3, their sum below 1 / weno_eps^2
+    const T al0 = (T)0.0625 * i0 * i0, al1 = (T)0.375 * i1 * i1, al2 = (T)0.1875 * i2 * i2;
     const T iS = rcp<T>(al0 + al1 + al2);
     // candidates less h_2, from the first differences of h: only q_k - f enters,
     // which 1 / e_k multiplies, so its rounding is the face's leading error
