@@ -929,7 +929,12 @@ int reduce_on(lbw_handle *h, int32_t what, double *out_host, int plane, int cls,
     hipError_t e = lbw::launch_reduce(h->q, h->precision, cur.data(), h->nbatch, what, h->odd,
                                       one ? slot->dev : part, one ? nullptr : (direct ? slot->dev : sums),
                                       h->stream, plane, cls);
-    if (e != hipSuccess) return hip_fail(e, "reduce launch");
+    if (e != hipSuccess) {
+        // the status may be an older error of this thread, and the kernels
+        // launched all the same
+        if (direct) slot->lost = hipStreamSynchronize(h->stream) != hipSuccess;
+        return hip_fail(e, "reduce launch");
+    }
     if (!direct)
         e = hipMemcpyAsync(out_host, sums, sizeof(double) * h->nbatch, hipMemcpyDeviceToHost, h->stream);
     if (e != hipSuccess) return hip_fail(e, "reduce copy");
