@@ -45,10 +45,13 @@ struct lbw_handle {
     std::vector<lbw::RunDev> views;
     lbw::TileShape shape{0, 0, 0};
     int grid_lbm = 0, grid_tr = 0;
-    // graph replay
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec = nullptr;
-    bool graph_odd = false, graph_sflip = false, graph_fused = false;
+    // graph replay: two steps from each state of (odd, sflip, fused) that came
+    // up, so that calls which change it drop no graph that may still be running
+    struct Replay {
+        hipGraph_t graph = nullptr;
+        hipGraphExec_t exec = nullptr;
+    };
+    Replay replay[2][2][2];
 };
 
 namespace {
@@ -150,11 +153,14 @@ lbw::ClassSet class_set(const lbw_handle *h, int b) {
     return cs;
 }
 
-void release_graph(lbw_handle *h) {
-    if (h->gexec) (void)hipGraphExecDestroy(h->gexec);
-    if (h->graph) (void)hipGraphDestroy(h->graph);
-    h->gexec = nullptr;
-    h->graph = nullptr;
+void release_graphs(lbw_handle *h) {
+    for (auto &of_odd : h->replay)
+        for (auto &of_sflip : of_odd)
+            for (lbw_handle::Replay &r : of_sflip) {
+                if (r.exec) (void)hipGraphExecDestroy(r.exec);
+                if (r.graph) (void)hipGraphDestroy(r.graph);
+                r = {};
+            }
 }
 
 // Work lists of the batched kernels for the current launch shape, copied
@@ -399,7 +405,7 @@ int lbw_create(const lbw_config *cfgs, const lbw_buffers *bufs, int32_t nbatch, 
 void lbw_destroy(lbw_handle *h) {
     if (!h) return;
     for (hipEvent_t ev : h->pool) (void)hipEventDestroy(ev);
-    release_graph(h);
+    release_graphs(h);
     delete h;
 }
 
@@ -438,7 +444,7 @@ int lbw_set_launch(lbw_handle *h, const lbw_launch *l) {
     n.graph = l->graph;
     if (const int rc = check_tile_launch(h, n)) return rc;
     h->launch = n;
-    release_graph(h);
+    release_graphs(h);
     return upload_tables(h);
 }
 
@@ -557,10 +563,13 @@ int enqueue_pair(lbw_handle *h, bool fused) {
     return rc ? rc : enqueue_step(h, fused ? &back : nullptr);
 }
 
-// Capture two steps from the current state into a graph (the state returns
-// to where it was: two steps restore the parity and the S roles).
-int build_graph(lbw_handle *h, bool fused) {
-    release_graph(h);
+// The graph of two steps from the current state (which it leaves as it is: two
+// steps restore the parity and the S roles), captured when the state first
+// comes up.
+int replay_graph(lbw_handle *h, bool fused, hipGraphExec_t *exec) {
+    lbw_handle::Replay &r = h->replay[h->odd][h->sflip][fused];
+    *exec = r.exec;
+    if (r.exec) return LBW_OK;
     const bool odd = h->odd, sflip = h->sflip;
     const int64_t steps = h->steps;
     hipError_t e = hipStreamBeginCapture(h->stream, hipStreamCaptureModeRelaxed);
@@ -571,21 +580,17 @@ int build_graph(lbw_handle *h, bool fused) {
     h->odd = odd;
     h->sflip = sflip;
     h->steps = steps;
-    if (rc) {
-        if (g) (void)hipGraphDestroy(g);
-        return rc;
+    if (!rc && e == hipSuccess) {
+        e = hipGraphInstantiate(&r.exec, g, nullptr, nullptr, 0);
+        if (e == hipSuccess) {
+            r.graph = g;
+            *exec = r.exec;
+            return LBW_OK;
+        }
+        r.exec = nullptr;
     }
-    if (e != hipSuccess) return hip_fail(e, "graph capture end");
-    h->graph = g;
-    e = hipGraphInstantiate(&h->gexec, g, nullptr, nullptr, 0);
-    if (e != hipSuccess) {
-        release_graph(h);
-        return hip_fail(e, "graph instantiate");
-    }
-    h->graph_odd = odd;
-    h->graph_sflip = sflip;
-    h->graph_fused = fused;
-    return LBW_OK;
+    if (g) (void)hipGraphDestroy(g);
+    return rc ? rc : hip_fail(e, "graph capture");
 }
 }  // namespace
 
@@ -601,12 +606,11 @@ int lbw_step(lbw_handle *h, int32_t nsteps) {
     const bool fused = nsteps >= 3 && fused_applies(h);
     int32_t pairs = fused ? (nsteps - 1) / 2 : (graph ? nsteps / 2 : 0);
     nsteps -= 2 * pairs;
-    if (graph && pairs && (!h->gexec || h->graph_odd != h->odd || h->graph_sflip != h->sflip ||
-                           h->graph_fused != fused))
-        if ((rc = build_graph(h, fused))) return rc;
+    hipGraphExec_t exec = nullptr;
+    if (graph && pairs && (rc = replay_graph(h, fused, &exec))) return rc;
     for (; pairs > 0; --pairs) {
         if (graph) {
-            hipError_t e = hipGraphLaunch(h->gexec, h->stream);
+            hipError_t e = hipGraphLaunch(exec, h->stream);
             if (e != hipSuccess) return hip_fail(e, "graph launch");
             h->steps += 2;
         } else if ((rc = enqueue_pair(h, fused))) {
@@ -745,7 +749,7 @@ int lbw_rebind(lbw_handle *h, int32_t run, int32_t field, void *ptr) {
         case LBW_FIELD_STAGE2: r.c2 = ptr ? ptr : b.c_s2; break;
         default: return fail(LBW_ERR_INVAL, "only U, RHO, STAGE1 and STAGE2 can be rebound (field %d)", field);
     }
-    release_graph(h);
+    release_graphs(h);
     return upload_tables(h);
 }
 
