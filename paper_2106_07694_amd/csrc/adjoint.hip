@@ -540,11 +540,7 @@ __global__ void __launch_bounds__(NT, BLOCKS) k_adj_stage(AdjDev A, const T *__r
     const RunDev &r = A.r;
     const int nx = r.nx, ny = r.ny, nz = D == 3 ? r.nz : 1;
     const int gx = (nx + TX - 1) / TX, gy = (ny + TY - 1) / TY;
-    // blocks are dealt round-robin to the 8 XCDs: each takes a contiguous
-    // range of tiles, whose halos then meet in its L2
-    const int nb = (int)gridDim.x;
-    int tile = (int)blockIdx.x;
-    if ((nb & 7) == 0) tile = (tile & 7) * (nb >> 3) + (tile >> 3);
+    const int tile = xcd_order((int)blockIdx.x, (int)gridDim.x);
     const int x0 = tile % gx * TX, y0 = tile / gx % gy * TY, z0 = D == 3 ? tile / gx / gy * TZ : 0;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int WAVES = NT / 64, E = (int)sizeof(T);

@@ -45,18 +45,10 @@ struct TileGeom {
     int bz0;            // first vertical chunk launched
 };
 
-// Position of the block: blocks are dealt round-robin to the 8 XCDs, so the
-// flat index is remapped to give each XCD a contiguous range of tiles whose
-// halos then meet in that XCD's L2, the size classes of one tile next to each
-// other (they read the same velocity).
+// Position of the block, in the order in which tiles meet in one XCD's L2, the
+// size classes of one tile next to each other (they read the same velocity).
 __device__ __forceinline__ void block_tile(const TileGeom &g, int ncls, int &bx, int &by, int &bz, int &cls) {
-    const int nb = g.gx * g.gy * g.gz * ncls;
-    const int b = blockIdx.x;
-    int logical = b;
-    if ((nb & 7) == 0) {
-        const int per = nb >> 3;
-        logical = (b & 7) * per + (b >> 3);
-    }
+    int logical = xcd_order(blockIdx.x, g.gx * g.gy * g.gz * ncls);
     cls = 0;
     if (ncls > 1) {
         cls = logical % ncls;
