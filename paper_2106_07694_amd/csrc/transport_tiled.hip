@@ -26,8 +26,14 @@ int64_t padded_columns(int dim, const RunDev *runs, int n, int tx, int ty) {
 int planes(int dim, const RunDev &r) { return dim == 3 ? r.nz : r.ny; }
 
 // Tile for runs whose caller chose none.  2D: the widest row (512 columns, 256
-// in double precision, whose 512-thread blocks measured 10-15% slower on small
-// grids) that pads the runs' columns no more than a narrower one.  3D: 64x8
+// in double precision, whose 512-thread blocks measured 10-27% slower on grids of
+// few planes) that pads the runs' columns by at most a tenth more than 64-column
+// rows do: a wider row stages fewer halo cells, which a tenth of idle lanes
+// outweighs.  us per step of transport, single precision, each at its best
+// chunk: 3000x2000 64 columns 92.8, 512 (2% more columns) 81.6; 1345x2000 55.0,
+// 512 (9%) 51.3; 700x2000 37.0, 256 (9%) 36.1; 515x3000 40.9, 128 (11%) 41.0;
+// 300x6000 42.7, 128 (20%) 45.7; double: 3000x2000 64 columns 170.7, 256 158.3,
+// 260x5000 58.1, 128 (20%) 60.7.  3D: 64x8
 // (one block of eight waves stages fewer halo columns per cell than 32x8: 59.7
 // against 65.2 us per step's transport on 128x96x160), unless its padding
 // exceeds that of 32x8 by a tenth (200 columns: 42.1 against 40.2 us).
@@ -37,23 +43,23 @@ TileShape default_tile(int dim, int precision, const RunDev *runs, int n) {
         return wide * 10 <= narrow * 11 ? TileShape{64, 8, 0} : TileShape{32, 8, 0};
     }
     TileShape s{64, 1, 0};
-    int64_t least = padded_columns(2, runs, n, 64, 1);
+    const int64_t least = padded_columns(2, runs, n, 64, 1);
     for (int tx : {128, 256, 512}) {
         if (tx == 512 && precision != LBW_FP32_SHIFTED) break;
-        const int64_t c = padded_columns(2, runs, n, tx, 1);
-        if (c <= least) {
-            least = c;
-            s.tx = tx;
-        }
+        if (padded_columns(2, runs, n, tx, 1) * 10 <= least * 11) s.tx = tx;
     }
     return s;
 }
 
 // Estimated us of a step's three stages of a 2D run in single precision:
-// 512 threads to a block, k = ceil(blocks / 256) of them on the busiest CU (up
-// to four run beside each other), `chunk` planes each.  Fitted to 1024x1024 ..
-// 4096x2048, within 5% there: the issue slots of two blocks are filled better by
+// 512 threads to a block (of several narrower tiles, counted by threads),
+// k = ceil(blocks / 256) of them on the busiest CU (up to four run beside each
+// other), `chunk` planes each: the issue slots of two blocks are filled better by
 // four shorter ones, and one block beyond a multiple of 256 costs a block's time.
+// Fitted to 512-column rows on 1024x1024 .. 4096x2048.  On 33 grids of 1.2 to 17
+// million cells it is 7% low to 3% high with those, up to 11% low with narrower
+// rows (129x12000 42.6, measured 47.9), and the shape it chooses takes at most 5%
+// longer than the best of 4 widths by 15 chunks.
 float march2d_us(int64_t k, int chunk) {
     constexpr float plane[4] = {2.12f, 2.92f, 3.74f, 4.98f}, start[4] = {15.5f, 18.1f, 20.2f, 22.4f};
     return start[k - 1] + plane[k - 1] * (float)chunk;
@@ -78,8 +84,8 @@ int default_chunk(int dim, int precision, const TileShape &s, const RunDev *runs
     constexpr int64_t cus = 256;
     if (dim == 2 && precision == LBW_FP32_SHIFTED && n == 1) {
         // 16 waves a CU (below) against the estimate's choice, us per step:
-        // 4096x2048 32 planes 110, 16 planes 100; 300x6000 48 and 42; 1000x3000
-        // 54.6 and 52.4; 2048x2048 63.5 and 62.6; 3000x2000 101.7 and 103.5;
+        // 4096x2048 32 planes 110, 16 planes 100; 129x12000 51.4 and 47.9; 40x50000
+        // 62.4 and 58.7; 200x9000 49.6 and 45.1; 1000x3000 54.6 and 52.4;
         // 1024x1280 .. 1024x2048 and 4096x4096 the same chunk
         int best = 32;
         float least = 0.f;
