@@ -25,3 +25,23 @@ for (nx, ny), width in {WIDTHS[precision]!r}.items():
     lbw.check(lib.lbw_step(h, 1))
     assert [b for _, b, _ in launches("k_stage_batched")] == [width] * 3, (nx, ny)
 """)
+
+
+FUSED = {"fp32_shifted": {(64, 128): True, (20000, 8): True, (100000, 8): False, (100000, 6): False, (73728, 16): True,
+                          (73728, 17): False, (3, 300000): True, (1024, 1152): True, (1024, 1153): False},
+         "fp64": {(64, 128): True, (20000, 8): True, (50000, 8): False, (512, 1024): True, (20000, 33): False}}
+
+
+@pytest.mark.parametrize("precision", sorted(FUSED))
+def test_one_launch_transport_counts_rows_in_whole_tiles(tmp_path, precision):
+    """Grids of few rows leave most of a one-launch tile outside the grid, so they
+    take the march from the size on at which their tiles, not their cells, fill the
+    chip."""
+    run(tmp_path, f"""
+for (nx, ny), fused in {FUSED[precision]!r}.items():
+    h = handle(lbw.RunConfig(nx=nx, ny=ny, precision={precision!r}))
+    lbw.check(lib.lbw_step(h, 4))
+    lines = log()
+    count = lambda part: sum(l.startswith("launch") and part in l for l in lines)
+    assert (count("k_rk3_2d"), count("k_stage_tiled")) == ((2, 6) if fused else (0, 12)), (nx, ny, lines)
+""")
