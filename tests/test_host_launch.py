@@ -29,7 +29,8 @@ for (nx, ny), width in {WIDTHS[precision]!r}.items():
 
 FUSED = {"fp32_shifted": {(64, 128): True, (20000, 8): True, (100000, 8): False, (100000, 6): False, (73728, 16): True,
                           (73728, 17): False, (3, 300000): True, (1024, 1152): True, (1024, 1153): False},
-         "fp64": {(64, 128): True, (20000, 8): True, (50000, 8): False, (512, 1024): True, (20000, 33): False}}
+         "fp64": {(64, 128): True, (20000, 8): True, (50000, 8): False, (512, 1024): True, (512, 1025): False,
+                  (600, 1200): False, (20000, 33): False}}
 
 
 @pytest.mark.parametrize("precision", sorted(FUSED))
