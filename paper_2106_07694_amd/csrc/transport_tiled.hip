@@ -73,14 +73,17 @@ float march2d_us(int64_t k, int chunk) {
 // 2D 64x128 in double precision 102 at 32 planes, 15 at one; 1024x1024 84 at
 // 32, 28 at four; 1024x2048 85 at 32, 41 at eight, 42 at four; 3D 64x48x96 89
 // at 24, 26 at three; 128x128x192 93 at 24, 73 at eight; 256x256x400 (an earlier
-// form) 620 at 64, 528 at 24, 572 at eight.  Full means 16 waves a CU in 2D and the blocks
-// that fit beside each other in 3D (registers: three of 64x8 in single
+// form) 620 at 64, 528 at 24, 572 at eight.  A last chunk cut short counts as a
+// block: 100x100x400 in double precision 242 at 21 planes (520 blocks), 183 at 22
+// (494); 300x100x150 125 at 13, 100 at 14.  Full means 16 waves a CU in 2D and the
+// blocks that fit beside each other in 3D (registers: three of 64x8 in single
 // precision, two in double).
 int default_chunk(int dim, int precision, const TileShape &s, const RunDev *runs, int n, int classes) {
-    int64_t blocks = 0;                 // at one plane per block
-    for (int i = 0; i < n; ++i)
-        blocks += padded_columns(dim, runs[i], s.tx, s.ty) / (s.tx * s.ty) * planes(dim, runs[i]);
-    blocks *= classes;
+    auto blocks = [&](int chunk) {
+        int64_t b = 0;
+        for (int i = 0; i < n; ++i) b += transport_tiles(dim, runs[i], TileShape{s.tx, s.ty, chunk});
+        return b * classes;
+    };
     constexpr int64_t cus = 256;
     if (dim == 2 && precision == LBW_FP32_SHIFTED && n == 1) {
         // 16 waves a CU (below) against the estimate's choice, us per step:
@@ -90,8 +93,7 @@ int default_chunk(int dim, int precision, const TileShape &s, const RunDev *runs
         int best = 32;
         float least = 0.f;
         for (int c = 32; c >= 1; --c) {
-            const int64_t b = padded_columns(dim, runs[0], s.tx, 1) / s.tx * ceil_div(planes(dim, runs[0]), c) * classes;
-            const int64_t k = ceil_div(b * s.tx, 512 * cus);
+            const int64_t k = ceil_div(blocks(c) * s.tx, 512 * cus);
             if (k > 4) break;
             const float us = march2d_us(k, c);
             if (c == 32 || us < least) {
@@ -101,7 +103,8 @@ int default_chunk(int dim, int precision, const TileShape &s, const RunDev *runs
         }
         return best;
     }
-    int64_t full, lo, hi;
+    int64_t full;
+    int lo, hi;
     if (dim == 2) {
         full = cus * 16 * 64 / s.tx;
         lo = 1;
@@ -113,7 +116,9 @@ int default_chunk(int dim, int precision, const TileShape &s, const RunDev *runs
         lo = eight_waves ? 3 : 2;
         hi = eight_waves ? 24 : 16;
     }
-    return (int)std::min(hi, std::max(lo, ceil_div(blocks, full)));
+    int c = lo;
+    while (c < hi && blocks(c) > full) ++c;
+    return c;
 }
 
 }  // namespace

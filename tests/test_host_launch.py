@@ -46,3 +46,17 @@ for (nx, ny), fused in {FUSED[precision]!r}.items():
     count = lambda part: sum(l.startswith("launch") and part in l for l in lines)
     assert (count("k_rk3_2d"), count("k_stage_tiled")) == ((2, 6) if fused else (0, 12)), (nx, ny, lines)
 """)
+
+
+@pytest.mark.parametrize("precision,full,sizes", [("fp32_shifted", 3 * 256, [(300, 100, 150), (128, 96, 160), (128, 128, 192)]),
+                                                  ("fp64", 2 * 256, [(300, 100, 150), (100, 100, 400), (97, 63, 130)])])
+def test_3d_chunks_leave_no_block_for_a_second_round(tmp_path, precision, full, sizes):
+    """The vertical chunk is the shortest whose blocks fit the chip together, a last
+    chunk cut short counted."""
+    run(tmp_path, f"""
+for nx, ny, nz in {sizes!r}:
+    h = handle(lbw.RunConfig(lattice=19, nx=nx, ny=ny, nz=nz, precision={precision!r}))
+    lbw.check(lib.lbw_step(h, 1))
+    got = launches("k_stage_tiled")
+    assert len(got) == 3 and all(b == 512 and {full} * 3 // 4 < g[0] <= {full} for g, b, _ in got), (nx, ny, nz, got)
+""")
