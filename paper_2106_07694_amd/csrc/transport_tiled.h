@@ -97,9 +97,9 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
     // done once as the node enters the column's window; the fluxes and
     // differences stay in registers, the indicators in a per-thread LDS ring
     // (in registers they would cost a block of occupancy).  The lateral faces
-    // keep face6: shared node data there needs an extra LDS round trip and
-    // barrier per plane, which cost more than the arithmetic saves, and 2D
-    // tiles wait on their barriers and loads rather than on instruction issue.
+    // keep the whole stencil (face6_lds): shared node data there needs an extra
+    // LDS round trip and barrier per plane, which cost more than the arithmetic
+    // saves.
     constexpr bool NV = (SCHEME == LBW_WENO5 && D == 3 && sizeof(T) == 4);
     constexpr int SXL = TX + 2;                         // S row with a one-cell x halo
     constexpr int SYL = (D == 3) ? TY + 2 : 1;          // S rows (one-cell y halo in 3D)
@@ -117,7 +117,10 @@ __device__ __forceinline__ void stage_tile(const RunDev &r, const TileGeom &g, i
     // publication and the next plane's faces.  Transport, us per step: 2D
     // 1024x2048 with S 46.4 -> 43.9, 2048x2048 68.3 -> 63.6, 1024x1024 in double
     // precision 44.9 -> 42.2, the 30-run sweep 136 -> 121; 3D 256x256x512 615 ->
-    // 598, four classes of 128x128x192 216 -> 212, the smaller grids even.
+    // 598, four classes of 128x128x192 216 -> 212, the smaller grids even.  With S
+    // in 3D they leave stage 1 a block less a CU (64x8: two in single precision, one
+    // in double) and are still no loss: single precision even, double 128x96x160
+    // 103 -> 98, 256^3 803 -> 746, 97x63x130 71.5 -> 69.8.
     constexpr int SET = O_END + 64;
     __shared__ T smem[2 * SET];
 
