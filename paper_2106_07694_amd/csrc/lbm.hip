@@ -257,15 +257,24 @@ inline unsigned blocks_for(int64_t n, int block) { return (unsigned)((n + block 
 constexpr size_t kStreamingBytes = (size_t)192 << 20;
 inline bool streaming_populations(size_t bytes) { return bytes > kStreamingBytes; }
 
-// LDS the even half reserves (and does not use) when it streams: all its
-// accesses are aligned, and HBM serves them fastest from 16 to 20 waves a CU;
-// with more, the 2Q streams of the waves in flight interleave more finely
-// (256x256x512, blocks of 256, mean of the pair: 987 us at 24 waves a CU, 966
-// at 20, 965 at 16, 1430 at 12).  The odd half wants its waves (957 us at 28,
-// 1002 at 20), and so do runs that stay in the caches.
+// LDS the even half of a single run reserves (and does not use) when it streams:
+// all its accesses are aligned, and HBM serves them fastest from 16 to 20 waves a
+// CU; with more, the 2Q streams of the waves in flight interleave more finely
+// (256x256x512, blocks of 256, mean of the pair: 987 us at 24 waves a CU, 966 at
+// 20, 965 at 16, 1430 at 12).  The odd half wants its waves (957 us at 28, 1002 at
+// 20), and so do runs that stay in the caches.  Only for blocks of 256 threads or
+// more of which two or more make 16 or 20 waves, as many on each SIMD (256, 320,
+// 512 and 640): mean of the pair without and with the reserve, us, 256x256x512 in
+// blocks of 256 974 and 949, of 512 970 and 950; 4096x2048 in blocks of 256 117
+// and 112, of 512 115 and 114.5; 3000x3000 in double precision 251 and 250, 249
+// and 246.5; but 3000x2000 in blocks of 384 (18 waves) 90.4 and 94.7, of 448 (14)
+// 90.5 and 92.8, 2048x2048 in double precision in blocks of 128 123.5 and 126.
+// Larger blocks need more than a block may reserve to keep a second one out.  The
+// batched form sets its waves by its grid; 16 to 20 of them gained nothing (30
+// uneven runs 145).
 inline size_t occupancy_lds(bool odd, bool nt, int block) {
-    if (odd || !nt) return 0;
-    const size_t blocks = std::max(1, 20 * 64 / block);
+    const int waves = block / 64, blocks = 20 / waves;
+    if (odd || !nt || waves < 4 || blocks < 2 || blocks * waves % 4) return 0;
     return std::min((size_t)64 << 10, ((size_t)160 << 10) / blocks & ~(size_t)511);
 }
 

@@ -60,3 +60,21 @@ for nx, ny, nz in {sizes!r}:
     got = launches("k_stage_tiled")
     assert len(got) == 3 and all(b == 512 and {full} * 3 // 4 < g[0] <= {full} for g, b, _ in got), (nx, ny, nz, got)
 """)
+
+
+@pytest.mark.parametrize("grid", ["lattice=19, nx=256, ny=256, nz=512", "nx=4096, ny=2048"])
+def test_streamed_even_half_keeps_16_or_20_waves_or_all(tmp_path, grid):
+    """The LDS the even half reserves lets blocks of 16 or 20 waves stay on a CU, the
+    same number on each of its four SIMDs; where no number of blocks does, for blocks
+    of fewer than four waves and in the odd half, nothing is reserved."""
+    run(tmp_path, f"""
+for block in range(64, 1025, 64):
+    h = handle(lbw.RunConfig({grid}, precision="fp32_shifted"), lbm_block=block)
+    lbw.check(lib.lbw_step(h, 2))
+    (_, even_block, even), (_, odd_block, odd) = launches("k_collide_stream")
+    assert even_block == odd_block == block and odd == 0
+    waves, fits = block // 64, (160 << 10) // even if even else 0
+    want = [n for n in range(2, 6) if n * waves in (16, 20)]
+    assert fits == (max(want) if want else 0), (block, even, fits)
+    assert even <= 64 << 10
+""")
