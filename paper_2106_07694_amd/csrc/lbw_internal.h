@@ -110,15 +110,19 @@ struct BatchArgs {
                                // S-dependent settling speed (each form in its own kernels)
 };
 
-// Work item of block b of a launch of nb blocks: blocks are dealt round-robin to
-// the 8 XCDs, so each XCD is given a contiguous range of items (the first nb % 8
-// of them one more), whose neighbours then meet in its L2.  2D march, us per
-// step, item b for block b where nb is no multiple of 8, and this: 3000x2000 by
-// 64-wide tiles and 4 planes 133, 100; 700x2000 44.1, 37.0; 1153x1100 44.7, 35.5.
-__host__ __device__ __forceinline__ int xcd_order(int b, int nb) {
-    const int xcd = b & 7, extra = nb & 7;
-    return xcd * (nb >> 3) + (xcd < extra ? xcd : extra) + (b >> 3);
+// Blocks are dealt round-robin to the 8 XCDs, so n of them are an eighth to each,
+// the first n % 8 XCDs one more.  First of the n work items that XCD `xcd` takes
+// (the end of its range for xcd + 1), as many as it has blocks in a launch of n.
+__host__ __device__ __forceinline__ int xcd_first(int xcd, int n) {
+    const int extra = n & 7;
+    return xcd * (n >> 3) + (xcd < extra ? xcd : extra);
 }
+
+// Work item of block b of a launch of nb blocks: a contiguous range for each XCD,
+// whose neighbours then meet in its L2.  2D march, us per step, item b for block b
+// where nb is no multiple of 8, and this: 3000x2000 by 64-wide tiles and 4 planes
+// 133, 100; 700x2000 44.1, 37.0; 1153x1100 44.7, 35.5.
+__host__ __device__ __forceinline__ int xcd_order(int b, int nb) { return xcd_first(b & 7, nb) + (b >> 3); }
 
 // Entry of a work list that holds item w, at or after entry b: start[i] is the
 // first item of entry i (n entries, start[n] the total, which exceeds w).

@@ -2,8 +2,9 @@
 // transport, as templates shared by the units that build them (one per
 // dimension, element type and settling form: transport_tiled_unit.hip).
 //
-// RK3 stage kernels of the particle transport, tiled for CDNA: a block owns a TX x TY tile of vertical columns and marches up a
-// chunk of the vertical axis.  Per plane:
+// RK3 stage kernels of the particle transport, tiled for CDNA: a block owns a
+// TX x TY tile of vertical columns and marches up a chunk of the vertical axis.
+// Per plane:
 //   * the plane of the stage input a, with a three-cell lateral halo, and the
 //     lateral velocities sit in LDS; each lateral face flux is computed once
 //     into LDS and differenced by the two cells that share it;
@@ -609,10 +610,9 @@ __global__ void __launch_bounds__(TX *TY) k_stage_batched(const RunDev *__restri
     int first = blockIdx.x, stride = G, hi = total;
     if (G >= 8) {
         const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-        const int per_xcd = (G + 7 - xcd) >> 3;           // blocks on this XCD (>= 1)
-        first = (int)((int64_t)total * xcd / 8) + slot;
-        hi = (int)((int64_t)total * (xcd + 1) / 8);
-        stride = per_xcd;
+        first = xcd_first(xcd, total) + slot;
+        hi = xcd_first(xcd + 1, total);
+        stride = xcd_first(xcd + 1, G) - xcd_first(xcd, G);   // blocks on this XCD (>= 1)
     }
     int b = 0;
     for (int w = first; w < hi; w += stride) {

@@ -21,6 +21,13 @@ int main() {
             }
         if (next != nb) return 1;
     }
+    // a work list walked by as many blocks as it has items: one item each
+    for (int n = 8; n < 2000; ++n)
+        for (int xcd = 0; xcd < 8; ++xcd) {
+            const int blocks = n / 8 + (xcd < n % 8);
+            if (lbw::xcd_first(xcd + 1, n) - lbw::xcd_first(xcd, n) != blocks || lbw::xcd_first(0, n) != 0 ||
+                lbw::xcd_first(8, n) != n) { printf("%d items, XCD %d\n", n, xcd); return 1; }
+        }
     const int big = 0x7fffffff;      // the largest launch: no overflow
     return lbw::xcd_order(big - 1, big) == big - 1 - (big >> 3) ? 0 : 1;
 }
