@@ -200,20 +200,23 @@ hipError_t launch_transport_batched(int dim, int precision, const BatchArgs &b, 
     return hipSuccess;
 }
 
-// Grids up to 9 * 2^17 cells (4 * 2^17 in double precision): beyond, three
-// launches of the march fill the chip and the recomputed halo decides.  us per
-// step of transport, fused against march, single precision: 515x1030 20.7, 25.9;
+// Grids up to 9 * 2^17 cells (in double precision 4 * 2^17, with the first-order
+// flux, whose recomputed halo costs least, 6 * 2^17): beyond, three launches of
+// the march fill the chip and the recomputed halo decides.  us per step of
+// transport, fused against march, single precision: 515x1030 20.7, 25.9;
 // 1024x1024 27.4, 28.1; 900x1300 33.2, 34.2; 1024x1152 29.5, 30.7; 1024x1280
-// 32.8, 31.2; 1024x1536 36.4, 34.6; double: 256x512 13.5, 19.0; 500x800 29.5,
+// 32.4, 31.2; 1024x1536 35.9, 34.2; double: 256x512 13.5, 19.0; 500x800 29.5,
 // 29.1; 512x1024 30.2, 30.7; 600x1000 36.0, 35.4; 600x1200 41.3, 36.1; 700x1100
-// 41.6, 39.9.  Rows count in sixteens, the lowest of the tiles,
-// since a flat grid's tiles are mostly outside it (single precision 100000x8
-// 50.1, 28.6; 20000x8 16.4, 18.3; 60000x16 34.8, 29.4; double 50000x8 44.6, 30.7;
-// 20000x33 51.9, 38.5); columns count as they are, the march's rows being 64 wide
-// (3x300000 196, 223).  A launch shape set by the caller asks for the march.  One
-// block row per 16 or more grid rows, 65535 at most.
+// 41.6, 39.9 (third order 512x1024 27.1, 28.0; 600x1200 38.5, 34.6; first order
+// 512x1024 17.4, 23.4; 768x1024 21.7, 24.2; 900x1000 27.7, 29.0).  Rows count in
+// sixteens, the lowest of the tiles, since a flat grid's tiles are mostly outside
+// it (single precision 100000x8 50.1, 28.6; 20000x8 16.4, 18.3; 60000x16 34.8,
+// 29.4; double 50000x8 44.6, 30.7; 20000x33 51.9, 38.5); columns count as they
+// are, the march's rows being 64 wide (3x300000 196, 223).  A launch shape set by
+// the caller asks for the march.  One block row per 16 or more grid rows, 65535 at
+// most.
 bool rk3_fused2d_applies(int dim, int precision, const RunDev &r, const lbw_launch &l) {
-    const int64_t most = (int64_t)(precision == LBW_FP32_SHIFTED ? 9 : 4) << 17;
+    const int64_t most = (int64_t)(precision == LBW_FP32_SHIFTED ? 9 : (r.scheme == LBW_UPWIND1 ? 6 : 4)) << 17;
     return dim == 2 && l.variant == 0 && !l.tile_x && !l.tile_y && !l.tile_rows &&
            ceil_div(r.ny, 16) * 16 * r.nx * r.ncls <= most && r.ny <= 65535 * 16;
 }

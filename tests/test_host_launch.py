@@ -30,7 +30,8 @@ for (nx, ny), width in {WIDTHS[precision]!r}.items():
 FUSED = {"fp32_shifted": {(64, 128): True, (20000, 8): True, (100000, 8): False, (100000, 6): False, (73728, 16): True,
                           (73728, 17): False, (3, 300000): True, (1024, 1152): True, (1024, 1153): False},
          "fp64": {(64, 128): True, (20000, 8): True, (50000, 8): False, (512, 1024): True, (512, 1025): False,
-                  (600, 1200): False, (20000, 33): False}}
+                  (600, 1200): False, (20000, 33): False, (600, 1200, "weno3"): False,
+                  (768, 1024, "upwind1"): True, (768, 1025, "upwind1"): False}}
 
 
 @pytest.mark.parametrize("precision", sorted(FUSED))
@@ -39,8 +40,8 @@ def test_one_launch_transport_counts_rows_in_whole_tiles(tmp_path, precision):
     take the march from the size on at which their tiles, not their cells, fill the
     chip."""
     run(tmp_path, f"""
-for (nx, ny), fused in {FUSED[precision]!r}.items():
-    h = handle(lbw.RunConfig(nx=nx, ny=ny, precision={precision!r}))
+for (nx, ny, *scheme), fused in {FUSED[precision]!r}.items():
+    h = handle(lbw.RunConfig(nx=nx, ny=ny, precision={precision!r}, scheme_c=(scheme or ["weno5"])[0]))
     lbw.check(lib.lbw_step(h, 4))
     lines = log()
     count = lambda part: sum(l.startswith("launch") and part in l for l in lines)
