@@ -120,8 +120,8 @@ def backward_from_checkpoints(sol: lbw.Solver, ckpt: dict, nsteps: int, seg: int
             sol.import_from("f", f_s)
         sol.import_from("c", c_s)
         # replay the segment in one library call: each step writes its
-        # intermediates straight into that step's buffers (C is copied
-        # before it)
+        # intermediates straight into that step's buffers (C before it is
+        # copied there, or written there by the step before)
         sol.replay([states[i][1] for i in range(n)], [inter[i][2] for i in range(n)],
                    [inter[i][3] for i in range(n)],
                    None if frozen else [inter[i][0] for i in range(n)],

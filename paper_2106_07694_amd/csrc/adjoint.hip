@@ -490,19 +490,21 @@ __global__ void __launch_bounds__(256) k_adj_gather(AdjDev A) {
 // products (6 D values of A and of W per node, written and read) disappears,
 // at the price of the faces neighbouring tiles also evaluate.
 //
-// Vector issue bounds it (2D 512x1024 in single precision: 516 vector
-// instructions per node, 6.9 of a stage's 12.3 us; 790 and 15.5 with the upwind
-// side chosen by selects and per-lane positions), so tiles are as large as
+// Vector issue takes more than half of it (2D 512x1024 in single precision: 513
+// vector instructions per node, 7 of a stage's 12 us; 790 and 15.5 with the
+// upwind side chosen by selects and per-lane positions; 3D 64x48x96 1045, 8.5 of
+// 15), the rest is the loads before the first of its barriers (eight, in 3D
+// twelve) and the end of a launch of one round of blocks, so tiles are as large as
 // occupancy allows (2D 64x8 evaluates 2.7 faces per node, 3D 16x4x4 5.8), a
 // stencil's upwind side is an address, a wave stages one position of 64 lines
 // (its place on the axis, wrap and mirror are scalar work), and faces beyond a
 // wall hold zeros so that a node adds its six products unchecked.  All the
 // tile's loads are in flight before the first is stored to LDS; LDS holds one
 // axis at a time, and of its products first A, then W (kept in registers
-// meanwhile), so that a CU holds 16 to 32 waves (both at once: 2D 0.4% faster,
-// 3D 4% slower).  us per reverse step: 2D 512x1024 61.5 -> 41 (against 32x8 tiles
-// with the whole set of products in LDS); 3D 64x48x96 81 -> 50 (against the
-// two-kernel form).
+// meanwhile), so that a CU holds 32 waves (2D) and 20 to 24 (3D) in single
+// precision, 16 and 12 in double (both at once: 2D 0.4% faster, 3D 4% slower).
+// us per reverse step: 2D 512x1024 61.5 -> 41 (against 32x8 tiles with the whole
+// set of products in LDS); 3D 64x48x96 81 -> 50 (against the two-kernel form).
 // ---------------------------------------------------------------------------
 
 // Stored position of j on a periodic axis, for the at most five cells a line's
@@ -528,8 +530,8 @@ template <int TX, int TY, int TZ, int D> struct AdjTile {
     static constexpr int max_staged = most(staged(0), most(staged(1), D == 3 ? staged(2) : 0));
 };
 
-template <int Q, typename T, bool SH, int STAGE, int TX, int TY, int TZ, int NT, int BLOCKS>
-__global__ void __launch_bounds__(NT, BLOCKS) k_adj_stage(AdjDev A, const T *__restrict__ a,
+template <int Q, typename T, bool SH, int STAGE, int TX, int TY, int TZ, int NT, int WAVES_PER_SIMD>
+__global__ void __launch_bounds__(NT, WAVES_PER_SIMD) k_adj_stage(AdjDev A, const T *__restrict__ a,
                                                           const T *__restrict__ lam, T scale) {
     constexpr int D = Lattice<Q>::D;
     using G = AdjTile<TX, TY, TZ, D>;
@@ -853,14 +855,14 @@ hipError_t adjoint_t(const AdjDev &A, const lbw_launch &l, hipStream_t st) {
     // in the same order, the same bits)
     constexpr bool f32 = sizeof(T) == 4;
     constexpr int TX = D == 2 ? 64 : 16, TY = D == 2 ? 8 : 4, TZ = D == 2 ? 1 : 4;
-    constexpr int NT = D == 2 ? 512 : 256, BLOCKS = D == 2 ? 4 : (f32 ? 5 : 3);
+    constexpr int NT = D == 2 ? 512 : 256, WPS = D == 2 ? 4 : (f32 ? 5 : 3);
     const int64_t tiles = (int64_t)((A.r.nx + TX - 1) / TX) * ((A.r.ny + TY - 1) / TY) *
                           (D == 3 ? (A.r.nz + TZ - 1) / TZ : 1);
     if (l.variant != 1 && tiles * NT < ((int64_t)1 << 32)) {
         const dim3 tg((unsigned)tiles);
-        k_adj_stage<Q, T, SH, 3, TX, TY, TZ, NT, BLOCKS><<<tg, NT, 0, st>>>(A, (const T *)A.a2, (const T *)A.cbar_next, (T)(2.0 / 3.0));
-        k_adj_stage<Q, T, SH, 2, TX, TY, TZ, NT, BLOCKS><<<tg, NT, 0, st>>>(A, (const T *)A.a1, (const T *)A.abar2, (T)0.25);
-        k_adj_stage<Q, T, SH, 1, TX, TY, TZ, NT, BLOCKS><<<tg, NT, 0, st>>>(A, (const T *)A.c_n, (const T *)A.abar1, (T)1);
+        k_adj_stage<Q, T, SH, 3, TX, TY, TZ, NT, WPS><<<tg, NT, 0, st>>>(A, (const T *)A.a2, (const T *)A.cbar_next, (T)(2.0 / 3.0));
+        k_adj_stage<Q, T, SH, 2, TX, TY, TZ, NT, WPS><<<tg, NT, 0, st>>>(A, (const T *)A.a1, (const T *)A.abar2, (T)0.25);
+        k_adj_stage<Q, T, SH, 1, TX, TY, TZ, NT, WPS><<<tg, NT, 0, st>>>(A, (const T *)A.c_n, (const T *)A.abar1, (T)1);
     } else {
         k_adj_face<T, D><<<grid, block, 0, st>>>(A, (const T *)A.a2, (const T *)A.cbar_next, (T)(2.0 / 3.0));
         k_adj_gather<Q, T, SH, 3><<<grid, block, 0, st>>>(A);

@@ -15,9 +15,10 @@
 // neighbouring block still reads the old values for its halo), so the caller
 // alternates two buffers over consecutive steps.  On the smallest grids the
 // block's chain of loads and six barriers bounds it (8 us at 64x128 in double
-// precision); near the upper limit vector issue does (512x1024: 15.7 us, of
-// which 13.5 are its 928 vector instructions per cell).  Faces and combinations are
-// those of the tiled stages, in the same order: the same bits.
+// precision); near the upper limit vector issue does (512x1024 in single
+// precision: the kernel takes 15.5 us, of which 13 are its 896 vector
+// instructions per cell).  Faces and combinations are those of the tiled stages,
+// in the same order: the same bits.
 #include "transport_face.h"
 
 namespace lbw {
@@ -214,14 +215,15 @@ hipError_t fused_tile(const RunDev &r, const ClassSet &cs, void *cout, void *a1,
     return hipGetLastError();
 }
 
-// The tile whose launch is estimated to end first.  A CU holds two blocks at a
-// time, and with k = ceil(blocks / 256) of them to work off it takes about
-// start + k * block us (measured on grids from 128x256 to 1024x1536, each tile
-// on all of them; within 1 us up to k = 4): a small tile recomputes more halo
-// per cell, a large one leaves CUs idle, and one block beyond a multiple of 256
-// costs a whole block's time (515x1030 in single precision: 561 blocks of 32x32
-// take 23.2 us, 442 of 32x40 20.1; 512x1024: 512 of 32x32 16.8, 416 of 32x40
-// 19.6).
+// The tile whose launch is estimated to end first.  A CU holds two blocks (32
+// waves) at a time, one of the two largest tiles in double precision (92 and 111
+// KB of LDS), and with k = ceil(blocks / 256) of them to work off it takes about
+// start + k * block us (measured as the transport of a step, launch included, on
+// grids from 128x256 to 1024x1536, each tile on all of them; within 1 us up to
+// k = 4): a small tile recomputes more halo per cell, a large one leaves CUs idle,
+// and one block beyond a multiple of 256 costs a whole block's time (515x1030 in
+// single precision: 561 blocks of 32x32 take 23.2 us, 442 of 32x40 20.1;
+// 512x1024: 512 of 32x32 16.8, 416 of 32x40 19.6).
 struct FusedTile {
     int tx, ty;
     float start, block;
@@ -230,6 +232,16 @@ constexpr FusedTile kTilesF32[] = {{16, 16, 6.9f, 2.45f}, {32, 16, 6.2f, 3.55f},
                                    {32, 32, 6.5f, 5.25f}, {32, 40, 7.6f, 6.35f}, {32, 48, 8.0f, 7.05f}};
 constexpr FusedTile kTilesF64[] = {{16, 16, 7.5f, 3.85f}, {32, 16, 7.6f, 5.5f}, {32, 24, 5.0f, 10.5f},
                                    {32, 32, 4.0f, 12.7f}};
+
+// LDS of a block of k_rk3_2d, bytes
+constexpr int fused_lds(const FusedTile &t, int element) {
+    const int rx = t.tx + 18, ry = t.ty + 18, px = t.tx + 12, py = t.ty + 12;
+    return element * (ry * rx + py * rx + ry * px + py * px + (t.tx + 6) * (t.ty + 6) + py * (px + 1) + (py + 1) * px);
+}
+constexpr int kLds = 160 << 10;
+static_assert(2 * fused_lds(kTilesF32[5], 4) <= kLds && 2 * fused_lds(kTilesF64[1], 8) <= kLds &&
+                  2 * fused_lds(kTilesF64[2], 8) > kLds && fused_lds(kTilesF64[3], 8) <= kLds,
+              "blocks a CU holds, as said above");
 
 template <typename T, int SCHEME>
 hipError_t fused_scheme(const RunDev &r, const ClassSet &cs, void *cout, void *a1, void *a2, hipStream_t st) {
