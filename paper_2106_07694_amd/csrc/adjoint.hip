@@ -508,7 +508,7 @@ __global__ void __launch_bounds__(256) k_adj_gather(AdjDev A) {
 // meanwhile), so that a CU holds 32 waves (2D) and 20 to 24 (3D) in single
 // precision, 16 and 12 in double (both at once: 2D 0.4% faster, 3D 4% slower).
 // us per reverse step: 2D 512x1024 61.5 -> 41 (against 32x8 tiles with the whole
-// set of products in LDS); 3D 64x48x96 81 -> 50 (against the two-kernel form).
+// set of products in LDS); 3D 64x48x96 81 -> 48 (against the two-kernel form).
 // ---------------------------------------------------------------------------
 
 // Stored position of j on a periodic axis, for the at most five cells a line's
